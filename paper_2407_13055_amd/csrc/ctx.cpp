@@ -82,18 +82,28 @@ uint2 tw_pair(uint64_t w, uint64_t q, uint32_t qinv)
 
 int32_t centred(uint64_t v, uint64_t q) { return (int32_t)(2 * v < q ? (int64_t)v : (int64_t)v - (int64_t)q); }
 
-// Shoup pair of constant w mod q: (w, floor(w 2^32 / q))
-uint2 shoup_pair(uint64_t w, uint64_t q)
+// round(w 2^32 / q) of the centred representative of w mod q (q odd: no ties
+// of the centring; |w| < q/2 keeps the quotient in 32 bits)
+int32_t quot_of(uint64_t w, uint64_t q)
+{
+    const int64_t c = centred(w, q);
+    const uint64_t m = (uint64_t)(c < 0 ? -c : c);
+    const int64_t r = (int64_t)(((m << 32) + q / 2) / q);
+    return (int32_t)(c < 0 ? -r : r);
+}
+
+// centred pair of constant w mod q: (w, round(w 2^32 / q))
+int2 cpair(uint64_t w, uint64_t q)
 {
     w %= q;
-    return make_uint2((uint32_t)w, (uint32_t)((w << 32) / q));
+    return make_int2(centred(w, q), quot_of(w, q));
 }
 
 // constant folded into the last inverse NTT stage: c and c * w1
-uint4 fold_pair(uint64_t c, uint64_t w1, uint64_t q)
+int4 fold_pair(uint64_t c, uint64_t w1, uint64_t q)
 {
-    const uint2 a = shoup_pair(c, q), b = shoup_pair(mm(c, w1, q), q);
-    return make_uint4(a.x, a.y, b.x, b.y);
+    const int2 a = cpair(c, q), b = cpair(mm(c, w1, q), q);
+    return make_int4(a.x, a.y, b.x, b.y);
 }
 
 }  // namespace
@@ -157,15 +167,15 @@ int build_ctx(const ckks_params* p, const int32_t* win_start, const int32_t* win
     const int P = c->n_primes, nq = c->n_q, np = c->n_p, N = c->n, L = c->log_n;
     // host images of every table
     std::vector<uint32_t> mods(P), qinvs(P);
-    std::vector<uint2> tw_f((size_t)P * N), tw_i((size_t)P * N);
-    std::vector<uint32_t> twq_f((size_t)P * N), twq_i((size_t)P * N);
-    std::vector<uint4> ninv(P), up_c_r((size_t)(nq + 1) * nq, make_uint4(0, 0, 0, 0));
-    std::vector<uint4> up_c((size_t)(nq + 1) * nq, make_uint4(0, 0, 0, 0));
+    std::vector<int32_t> tw_f((size_t)P * N), tw_i((size_t)P * N), rcs(P);
+    std::vector<int4> ninv(P), up_c_r((size_t)(nq + 1) * nq, make_int4(0, 0, 0, 0));
+    std::vector<int4> up_c((size_t)(nq + 1) * nq, make_int4(0, 0, 0, 0));
     std::vector<uint64_t> w1(P);  // psi^-brev(1) = psi^-(N/2) per prime
     std::vector<int32_t> up_mat((size_t)(nq + 1) * c->dnum * P * np, 0);
-    std::vector<uint4> dn_c(np + nq);
-    std::vector<uint2> dn_pinv(nq), rinv(nq), p_r2(nq), rs_qinv((size_t)(nq + 1) * nq, make_uint2(0, 0));
-    std::vector<uint2> rs_fin((size_t)(nq + 1) * nq, make_uint2(0, 0));
+    std::vector<int4> dn_c(np + nq);
+    std::vector<uint2> rinv(nq), p_r2(nq);
+    std::vector<int2> dn_pinv(nq), rs_qinv((size_t)(nq + 1) * nq, make_int2(0, 0));
+    std::vector<int2> rs_fin((size_t)(nq + 1) * nq, make_int2(0, 0));
     std::vector<int32_t> rs_mlast((size_t)nq * np), rs_pr(nq);
     std::vector<int32_t> dn_mat((size_t)nq * np);
     std::vector<uint32_t> p_mod_q(nq);
@@ -175,6 +185,7 @@ int build_ctx(const ckks_params* p, const int32_t* win_start, const int32_t* win
         const uint64_t q = c->mod[i];
         mods[i] = (uint32_t)q;
         qinvs[i] = inv32((uint32_t)q);
+        rcs[i] = (int32_t)(((1ull << 32) + q / 2) / q);
         // psi: smallest g >= 2 with g^N = -1
         uint64_t psi = 0;
         for (uint64_t g = 2; g < q; g++)
@@ -188,10 +199,8 @@ int build_ctx(const ckks_params* p, const int32_t* win_start, const int32_t* win
         for (int e = 1; e < N; e++) pf[e] = mm(pf[e - 1], psi, q), pi[e] = mm(pi[e - 1], psi_inv, q);
         for (int k = 0; k < N; k++) {
             const uint32_t e = brev((uint32_t)k, L);
-            tw_f[(size_t)i * N + k] = shoup_pair(pf[e], q);
-            tw_i[(size_t)i * N + k] = shoup_pair(pi[e], q);
-            twq_f[(size_t)i * N + k] = tw_f[(size_t)i * N + k].y;
-            twq_i[(size_t)i * N + k] = tw_i[(size_t)i * N + k].y;
+            tw_f[(size_t)i * N + k] = quot_of(pf[e], q);
+            tw_i[(size_t)i * N + k] = quot_of(pi[e], q);
         }
         w1[i] = pi[N / 2];
         ninv[i] = fold_pair(inv((uint64_t)N, q), w1[i], q);
@@ -244,7 +253,7 @@ int build_ctx(const ckks_params* p, const int32_t* win_start, const int32_t* win
                 if (r != k) ph = mm(ph, c->mod[nq + r], q);
             dn_mat[(size_t)i * np + k] = centred(mm(ph, rinv_q, q), q);
         }
-        dn_pinv[i] = tw_pair(mm(inv(pp, q), r2, q), q, qinvs[i]);
+        dn_pinv[i] = cpair(mm(inv(pp, q), r2, q), q);
         // fused rescale when q_i is the dropped prime
         dn_c[np + i] = fold_pair(mm(mm(inv((uint64_t)N, q), r2, q), inv(pp, q), q), w1[i], q);
         for (int k = 0; k < np; k++) {
@@ -266,16 +275,16 @@ int build_ctx(const ckks_params* p, const int32_t* win_start, const int32_t* win
             uint64_t pp = 1;
             for (int k = 0; k < np; k++) pp = mm(pp, c->mod[nq + k], q);
             const uint64_t qlinv = inv(c->mod[level - 1] % q, q);
-            rs_qinv[(size_t)level * nq + i] = tw_pair(qlinv, q, qinvs[i]);
-            rs_fin[(size_t)level * nq + i] = tw_pair(mm(mm(inv(pp, q), qlinv, q), mm(R(i), R(i), q), q), q, qinvs[i]);
+            rs_qinv[(size_t)level * nq + i] = cpair(qlinv, q);
+            rs_fin[(size_t)level * nq + i] = cpair(mm(mm(inv(pp, q), qlinv, q), mm(R(i), R(i), q), q), q);
         }
 
     for (int i = 0; i < P; i++) r1[i] = tw_pair(R(i), c->mod[i], qinvs[i]);
 
     // merged ModDown + rational rescaling, per window with a window below
-    std::vector<uint4> rr_c, rr2_c;
+    std::vector<int4> rr_c, rr2_c;
     std::vector<int32_t> rr_mat, rr2_mat;
-    std::vector<uint2> rr_fin, rr2_fin;
+    std::vector<int2> rr_fin, rr2_fin;
     for (int level = 1; level <= nq && c->windowed; level++) {
         if (!c->has_level(level)) continue;
         int below = 0;
@@ -321,7 +330,7 @@ int build_ctx(const ckks_params* p, const int32_t* win_start, const int32_t* win
                 rr_mat.push_back(centred(mm(mm(sh, rinv_q, q), f, q), q));
             }
             const uint64_t fin = mm(mm(kept(pid) ? qa : 1, inv(qs, q), q), mm(R(pid), R(pid), q), q);
-            rr_fin.push_back(tw_pair(fin, q, qinvs[pid]));
+            rr_fin.push_back(cpair(fin, q));
         }
         // stand-alone rational rescaling: S = D (the dropped window rows)
         const std::vector<int> D(S.begin() + np, S.end());
@@ -351,15 +360,15 @@ int build_ctx(const ckks_params* p, const int32_t* win_start, const int32_t* win
                     if (t != d) dh = mm(dh, c->mod[t] % q, q);
                 rr2_mat.push_back(centred(mm(mm(dh, R(pid), q), f, q), q));
             }
-            rr2_fin.push_back(tw_pair(mm(kept(pid) ? qa : 1, inv(qd, q), q), q, qinvs[pid]));
+            rr2_fin.push_back(cpair(mm(kept(pid) ? qa : 1, inv(qd, q), q), q));
         }
     }
-    if (rr_c.empty()) rr_c.push_back(make_uint4(0, 0, 0, 0));
+    if (rr_c.empty()) rr_c.push_back(make_int4(0, 0, 0, 0));
     if (rr_mat.empty()) rr_mat.push_back(0);
-    if (rr_fin.empty()) rr_fin.push_back(make_uint2(0, 0));
-    if (rr2_c.empty()) rr2_c.push_back(make_uint4(0, 0, 0, 0));
+    if (rr_fin.empty()) rr_fin.push_back(make_int2(0, 0));
+    if (rr2_c.empty()) rr2_c.push_back(make_int4(0, 0, 0, 0));
     if (rr2_mat.empty()) rr2_mat.push_back(0);
-    if (rr2_fin.empty()) rr2_fin.push_back(make_uint2(0, 0));
+    if (rr2_fin.empty()) rr2_fin.push_back(make_int2(0, 0));
     for (std::vector<int32_t>* m : {&up_mat, &dn_mat, &rs_mlast, &rr_mat, &rr2_mat}) m->resize(m->size() + BCONV_MAT_PAD, 0);
     std::vector<int32_t> lv_tab(4 * (MAX_PRIMES + 1), 0);
     for (int l = 0; l <= MAX_PRIMES; l++) {
@@ -379,10 +388,9 @@ int build_ctx(const ckks_params* p, const int32_t* win_start, const int32_t* win
     std::vector<Piece> pieces = {
         {(void**)&c->mods, mods.data(), mods.size() * 4},
         {(void**)&c->qinvs, qinvs.data(), qinvs.size() * 4},
-        {(void**)&c->tw_fwd, tw_f.data(), tw_f.size() * 8},
-        {(void**)&c->tw_inv, tw_i.data(), tw_i.size() * 8},
-        {(void**)&c->twq_fwd, twq_f.data(), twq_f.size() * 4},
-        {(void**)&c->twq_inv, twq_i.data(), twq_i.size() * 4},
+        {(void**)&c->rcs, rcs.data(), rcs.size() * 4},
+        {(void**)&c->tw_fwd, tw_f.data(), tw_f.size() * 4},
+        {(void**)&c->tw_inv, tw_i.data(), tw_i.size() * 4},
         {(void**)&c->ninv, ninv.data(), ninv.size() * 16},
         {(void**)&c->up_c_r, up_c_r.data(), up_c_r.size() * 16},
         {(void**)&c->up_c, up_c.data(), up_c.size() * 16},

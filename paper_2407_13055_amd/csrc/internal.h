@@ -123,42 +123,39 @@ struct Ctx {
 
     uint32_t* mods = nullptr;       // [n_primes]
     uint32_t* qinvs = nullptr;      // [n_primes] q^-1 mod 2^32
-    // NTT twiddles: Shoup pairs (w, floor(w 2^32 / q))
-    uint2* tw_fwd = nullptr;        // [n_primes][N] psi^brev(k)
-    uint2* tw_inv = nullptr;        // [n_primes][N] psi^-brev(k)
-    // the same twiddles as floor(w 2^32 / q) alone (w recovered in the kernel:
-    // half the bytes; KeyMult's row passes)
-    uint32_t* twq_fwd = nullptr;    // [n_primes][N]
-    uint32_t* twq_inv = nullptr;    // [n_primes][N]
+    int32_t* rcs = nullptr;         // [n_primes] round(2^32 / q)
+    // NTT twiddles as round(w 2^32 / q) of the centred w (the kernels recover w)
+    int32_t* tw_fwd = nullptr;      // [n_primes][N] psi^brev(k)
+    int32_t* tw_inv = nullptr;      // [n_primes][N] psi^-brev(k)
     // constants folded into the last inverse stage: (c, c_s, c w1, (c w1)_s),
-    // w1 = psi^-brev(1) of the limb's prime, Shoup pairs
-    uint4* ninv = nullptr;          // [n_primes] N^-1
-    uint4* up_c_r = nullptr;        // [n_q+1][n_q] N^-1 [Dhat_{j,i}^-1]_{q_i} R, by level and prime id (input carries R^-1)
-    uint4* up_c = nullptr;          // [n_q+1][n_q] N^-1 [Dhat_{j,i}^-1]_{q_i}
+    // w1 = psi^-brev(1) of the limb's prime, centred pairs (mulr)
+    int4* ninv = nullptr;          // [n_primes] N^-1
+    int4* up_c_r = nullptr;        // [n_q+1][n_q] N^-1 [Dhat_{j,i}^-1]_{q_i} R, by level and prime id (input carries R^-1)
+    int4* up_c = nullptr;          // [n_q+1][n_q] N^-1 [Dhat_{j,i}^-1]_{q_i}
     int32_t* up_mat = nullptr;      // [n_q+1][dnum][n_primes][n_p] centred [Dhat_{j,s}]_t, by key digit
-    uint4* dn_c = nullptr;          // [n_p + n_q] N^-1 [Phat_k^-1]_{p_k} R^2, then N^-1 R^2 [P^-1]_{q_i}
+    int4* dn_c = nullptr;          // [n_p + n_q] N^-1 [Phat_k^-1]_{p_k} R^2, then N^-1 R^2 [P^-1]_{q_i}
     int32_t* dn_mat = nullptr;      // [n_q][n_p] centred [Phat_k R^-1]_{q_i}
-    uint2* dn_pinv = nullptr;       // [n_q] P^-1 R^2
+    int2* dn_pinv = nullptr;       // [n_q] P^-1 R^2
     uint32_t* p_mod_q = nullptr;    // [n_q] [P]_{q_i} (plain residue, data operand)
     uint2* rinv = nullptr;          // [n_q] R^-1
     uint2* p_r2 = nullptr;          // [n_q] P R^-2
     uint2* r1 = nullptr;            // [n_q + n_p] R = 2^32 (undoes one Montgomery factor: PMult, plaintext weights)
-    uint2* rs_qinv = nullptr;       // [n_q+1][n_q] [q_{l-1}^-1]_{q_i}
+    int2* rs_qinv = nullptr;       // [n_q+1][n_q] [q_{l-1}^-1]_{q_i}
     int32_t* rs_mlast = nullptr;    // [n_q][n_p] centred [Phat_k P^-1 R]_{q_i}   (q_i the dropped prime)
     int32_t* rs_pr = nullptr;       // [n_q] centred [P R^-1]_{q_i}
-    uint2* rs_fin = nullptr;        // [n_q+1][n_q] [P^-1 q_{l-1}^-1 R^2]_{q_i}
+    int2* rs_fin = nullptr;        // [n_q+1][n_q] [P^-1 q_{l-1}^-1 R^2]_{q_i}
     // merged ModDown + rational rescaling (windowed contexts), S = P u D the
     // dropped primes, A the added ones, per level:
-    uint4* rr_c = nullptr;          // N^-1 [Shat_s^-1]_s Q_A R^2 per s in S (INTT fold)
+    int4* rr_c = nullptr;          // N^-1 [Shat_s^-1]_s Q_A R^2 per s in S (INTT fold)
     int32_t* rr_mat = nullptr;      // centred [Shat_s R^-1 (Q_A^-1 if o is kept)]_o per (o, s)
-    uint2* rr_fin = nullptr;        // [(Q_A if o is kept) Q_S^-1 R^2]_o per output row
+    int2* rr_fin = nullptr;        // [(Q_A if o is kept) Q_S^-1 R^2]_o per output row
     // stand-alone rational rescaling between a window and the window below
     // (S = D only; inputs carry no Montgomery factor): INTT fold
     // N^-1 [Dhat_d^-1]_d Q_A, matrix centred [Dhat_d R (Q_A^-1 if kept)]_o,
     // combine [(Q_A if kept) Q_D^-1]_o; offsets per level as above
-    uint4* rr2_c = nullptr;
+    int4* rr2_c = nullptr;
     int32_t* rr2_mat = nullptr;
-    uint2* rr2_fin = nullptr;
+    int2* rr2_fin = nullptr;
     int rr2_c_off[MAX_PRIMES + 1] = {}, rr2_mat_off[MAX_PRIMES + 1] = {}, rr2_fin_off[MAX_PRIMES + 1] = {};
     // device copy of the per-level window data for batched launches (windowed
     // contexts): [4][MAX_PRIMES + 1] = wbase, rescaling's dropped rows (0: no

@@ -152,7 +152,8 @@ struct LdOwn {
     }
 };
 
-// [t]_q of a lifted (centred) limb stored in the tile-thread layout (rescale)
+// a lifted (centred) limb of another prime, stored in the tile-thread layout
+// (rescale); |t| <= 2^30, a forward value of either class as it is
 struct LdCentred {
     static constexpr bool kTileThread = true;
     const int32_t* t;
@@ -164,11 +165,9 @@ struct LdCentred {
         r.t += (size_t)i * step;
         return r;
     }
-    __device__ void load16(const LaunchMap& M, int l, int j, PrimeC pc, uint32_t (&x)[16]) const
+    __device__ void load16(const LaunchMap& M, int l, int j, PrimeC, uint32_t (&x)[16]) const
     {
         load16_u32(reinterpret_cast<const uint32_t*>(t) + ((size_t)M.in_off[l] << log_n) + j, x);
-#pragma unroll
-        for (int k = 0; k < 16; k++) x[k] = reduce_centred((int32_t)x[k], pc.q);
     }
 };
 
@@ -178,7 +177,7 @@ struct LdCentred {
 struct StPlain {
     static constexpr bool kTileThread = false;
     uint32_t* base;
-    const uint4* fc;  // final constant table (inverse passes), row cidx[l]
+    const int4* fc;  // final constant table (inverse passes), row cidx[l]
     int log_n;
     size_t step = 0;
     __device__ StPlain at(int i) const
@@ -204,19 +203,23 @@ struct StPlain {
     struct Pre {};
     template <int E>
     __device__ Pre prefetch(const LaunchMap&, int, int) const { return {}; }
-    template <int E>
-    __device__ void storev(const LaunchMap& M, int l, int j, const uint32_t (&x)[E], PrimeC pc, Pre) const
+    // canonical residues of forward values (class W)
+    template <int E, bool W>
+    __device__ void store_fwd(const LaunchMap& M, int l, int j, const uint32_t (&x)[E], PrimeC pc, Pre) const
     {
-        storev<E>(M, l, j, x, pc);
+        uint32_t y[E];
+#pragma unroll
+        for (int k = 0; k < E; k++) y[k] = fwd_canon<W>(x[k], pc);
+        storev<E>(M, l, j, y, pc);
     }
-    __device__ uint4 final_const(const LaunchMap& M, int l) const { return fc[M.cidx[l]]; }
+    __device__ int4 final_const(const LaunchMap& M, int l) const { return fc[M.cidx[l]]; }
 };
 
 // centred lift into int32 (input of a base conversion), tile-thread layout
 struct StLift {
     static constexpr bool kTileThread = true;
     int32_t* base;
-    const uint4* fc;
+    const int4* fc;
     int log_n;
     size_t step = 0;
     __device__ StLift at(int i) const
@@ -237,16 +240,18 @@ struct StLift {
     {
         storev<16>(M, l, j, x, pc);
     }
-    __device__ uint4 final_const(const LaunchMap& M, int l) const { return fc[M.cidx[l]]; }
+    __device__ int4 final_const(const LaunchMap& M, int l) const { return fc[M.cidx[l]]; }
 };
 
-// out = (sub - v) * c  (ModDown: c = P^-1 R^2; rescale: c = q_last^-1); sub = 0 where sub_off < 0
+// out = (sub - v) * c  (ModDown: c = P^-1 R^2; rescale: c = q_last^-1); sub = 0 where sub_off < 0.
+// v is a forward value: centred, its difference with the canonical sub lies
+// in (-q, 2q) of a wide prime or (-q, q) of a 31-bit one, an operand of mulr.
 struct StCombine {
     static constexpr bool kTileThread = false;
     uint32_t* out0;
     uint32_t* out1;
     const uint32_t* sub;
-    const uint2* cst;
+    const int2* cst;
     int log_n;
     size_t out_step = 0, sub_step = 0;
     __device__ StCombine at(int i) const
@@ -261,7 +266,7 @@ struct StCombine {
     template <int E>
     struct PreE {
         uint32_t s[E];
-        uint2 c;
+        int2 c;
     };
     template <int E>
     __device__ PreE<E> prefetch(const LaunchMap& M, int l, int j) const
@@ -276,23 +281,17 @@ struct StCombine {
         p.c = cst[M.cidx[l]];
         return p;
     }
-    template <int E>
-    __device__ void storev(const LaunchMap& M, int l, int j, const uint32_t (&x)[E], PrimeC pc,
-                           const PreE<E>& p) const
+    template <int E, bool W>
+    __device__ void store_fwd(const LaunchMap& M, int l, int j, const uint32_t (&x)[E], PrimeC pc,
+                              const PreE<E>& p) const
     {
         uint32_t o[E];
 #pragma unroll
-        for (int k = 0; k < E; k++) o[k] = mulc(p.s[k] + pc.q - x[k], p.c, pc.q);
+        for (int k = 0; k < E; k++) {
+            const int32_t d = (int32_t)(p.s[k] - (uint32_t)fwd_centre<W>(x[k], pc));
+            o[k] = fix_signed((uint32_t)mulr(d, p.c, pc.nq), pc.q);
+        }
         storev_u32<E>((M.grp[l] ? out1 : out0) + ((size_t)M.out_off[l] << log_n) + j, o);
-    }
-    template <int E>
-    __device__ void storev(const LaunchMap& M, int l, int j, const uint32_t (&x)[E], PrimeC pc) const
-    {
-        storev<E>(M, l, j, x, pc, prefetch<E>(M, l, j));
-    }
-    __device__ void store16(const LaunchMap& M, int l, int j, const uint32_t (&x)[16], PrimeC pc) const
-    {
-        storev<16>(M, l, j, x, pc);
     }
 };
 
@@ -452,8 +451,9 @@ __global__ void __launch_bounds__(CT) k_bconv_ntt_cols(NttTables T, BS bs, const
         if (t >= n_tg) break;
         const int tg = first + t;
         const int pid = B.pid[tg];
-        const uint32_t q = T.mods[pid], qinv = T.qinvs[pid];
-        const uint2* tw = T.tw + ((size_t)pid << T.log_n);
+        const PrimeC pc = T.prime(pid);
+        const uint32_t q = pc.q, qinv = pc.qinv;
+        const TwTable tw{T.tw + ((size_t)pid << T.log_n), q};
         uint32_t x[16];
         if constexpr (RS) {
             const int64_t mp = X.pr[pid];
@@ -461,11 +461,11 @@ __global__ void __launch_bounds__(CT) k_bconv_ntt_cols(NttTables T, BS bs, const
             for (int k = 0; k < 16; k++) acc[t][k] = range_fix(acc[t][k], t31[t], t32[t]) + (int64_t)tl[k] * mp;
         }
 #pragma unroll
-        for (int k = 0; k < 16; k++) x[k] = canon_signed(smr64(range_fix(acc[t][k], t31[t], t32[t]), q, qinv), q);
+        for (int k = 0; k < 16; k++) x[k] = (uint32_t)smr64(range_fix(acc[t][k], t31[t], t32[t]), q, qinv);
         uint32_t* dst = out + (size_t)B.out_off[tg] * n + col;
         by_class(q, [&](auto tag) {
             constexpr bool W = decltype(tag)::value;
-            ct_stages<4, W>(x, q, [&](int u, int b) { return tw[(1 << u) + b]; });
+            ct_stages<4, W>(x, pc, [&](int u, int b) { return tw[(1 << u) + b]; });
             if constexpr (G::NS2 > 0) {
                 if (t) __syncthreads();  // previous target's LDS reads are done
 #pragma unroll
@@ -473,7 +473,7 @@ __global__ void __launch_bounds__(CT) k_bconv_ntt_cols(NttTables T, BS bs, const
                 __syncthreads();
 #pragma unroll
                 for (int k = 0; k < 16; k++) x[k] = lds[col_lds<G::C>(16 * r + k, c)];
-                ct_stages<G::NS2, W>(x, q, [&](int u, int b) {
+                ct_stages<G::NS2, W>(x, pc, [&](int u, int b) {
                     return tw[(1 << (4 + u)) + (r << (4 - G::NS2 + u)) + b];
                 });
             }
@@ -513,7 +513,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_bconv_ntt_cols4(NttTables T, BS
     const int32_t* y = y0 + (size_t)blockIdx.z * step;
     uint32_t* out = out0 + (size_t)blockIdx.z * step;
     __shared__ uint32_t lds[TPW * G::WORDS];
-    __shared__ uint2 twl[TPW << LOG1];
+    __shared__ int2 twl[TPW << LOG1];
     const int c = threadIdx.x % G::C, t = threadIdx.x / G::C;
     const int tile = col4_tile<LOG1>(T.xcd_pair), col = tile * G::C + c;
     const size_t n = (size_t)1 << T.log_n;
@@ -523,18 +523,18 @@ __global__ void __launch_bounds__(NTT_THREADS) k_bconv_ntt_cols4(NttTables T, BS
     const uint32_t toff = threadIdx.x * 4;
 
     // targets (a group's missing targets repeat its first; they are not stored)
-    uint32_t tq[TPW], tqi[TPW];
-    const uint2* tws[TPW];
+    PrimeC tp[TPW];
+    const int32_t* tws[TPW];
     const int32_t* tm[TPW];
     int64_t t31[TPW], t32[TPW];
 #pragma unroll
     for (int i = 0; i < TPW; i++) {
         const int k = first + (i < n_tg ? i : 0);
         const int pid = B.pid[k];
-        tq[i] = T.mods[pid], tqi[i] = T.qinvs[pid];
+        tp[i] = T.prime(pid);
         tws[i] = T.tw + ((size_t)pid << T.log_n);
         tm[i] = mat + B.mat_off[k];
-        t31[i] = (int64_t)tq[i] << 31, t32[i] = (int64_t)tq[i] << 32;
+        t31[i] = (int64_t)tp[i].q << 31, t32[i] = (int64_t)tp[i].q << 32;
     }
     // fused rescale: row e (after the inputs) and the conversion to q_{l-1}
     const int ql_pid = RS ? (items ? items[blockIdx.z].level : X.level) - 1 : 0;
@@ -547,7 +547,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_bconv_ntt_cols4(NttTables T, BS
         for (int s = 0; s < CH; s++) loadv_u32<4>(ybase + (size_t)min(s0 + s, n_in - 1) * n + toff, yv[s]);
     };
     if (n_in > 0) load_rows(0);
-    col4_stage_twiddles<LOG1, TPW>(twl, tws);
+    col4_stage_twiddles<LOG1, TPW>(twl, tws, tp);
 
     int64_t acc[TPW][4];
 #pragma unroll
@@ -627,14 +627,28 @@ __global__ void __launch_bounds__(NTT_THREADS) k_bconv_ntt_cols4(NttTables T, BS
     for (int i = 0; i < TPW; i++) {
         int64_t mp = 0;
         if constexpr (RS) mp = X.pr[B.pid[first + (i < n_tg ? i : 0)]];
+        // A sum is at most t 2^32 (8 products, or t 2^31 after a fix and 4
+        // more: |y| <= 2^30, |m| < t/2), and the rescaling's product adds less
+        // than t 2^29: the reduction leaves |x| < (1 + 1/8 + 1/2) t < 2^31 for
+        // a wide prime, a forward value as it is.  A 31-bit prime's forward
+        // values end at q, which takes the sum within t 2^31.
+        if (wide_prime(tp[i].q)) {
 #pragma unroll
-        for (int k = 0; k < 4; k++) {
-            int64_t a = acc[i][k];
-            if constexpr (RS) a = range_fix(a, t31[i], t32[i]) + (int64_t)tl[k] * mp;
-            x[i][k] = canon_signed(smr64(range_fix(a, t31[i], t32[i]), tq[i], tqi[i]), tq[i]);
+            for (int k = 0; k < 4; k++) {
+                int64_t a = acc[i][k];
+                if constexpr (RS) a += (int64_t)tl[k] * mp;
+                x[i][k] = (uint32_t)smr64(a, tp[i].q, tp[i].qinv);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                int64_t a = acc[i][k];
+                if constexpr (RS) a = range_fix(a, t31[i], t32[i]) + (int64_t)tl[k] * mp;
+                x[i][k] = (uint32_t)smr64(range_fix(a, t31[i], t32[i]), tp[i].q, tp[i].qinv);
+            }
         }
     }
-    col4_fwd<LOG1, TPW>(x, tq, lds, twl, c, t);
+    col4_fwd<LOG1, TPW>(x, tp, lds, twl, c, t);
 #pragma unroll
     for (int i = 0; i < TPW; i++) {
         if (i >= n_tg) break;
@@ -686,7 +700,7 @@ struct KmArgs {
 // when rescale follows) start ModDown with the INTT row pass, then store.
 template <int LOG1>
 __device__ __forceinline__ void keymult_store(const NttTables& Ti, const KmArgs& A, int r, int pid, int h, int rp,
-                                              int rr, uint32_t q, uint32_t* lds, const uint32_t (&acc0)[16],
+                                              int rr, const PrimeC& pc, uint32_t* lds, const uint32_t (&acc0)[16],
                                               const uint32_t (&acc1)[16])
 {
     const int log_n = Ti.log_n;
@@ -699,16 +713,16 @@ __device__ __forceinline__ void keymult_store(const NttTables& Ti, const KmArgs&
         store16_u32(A.ks_q + (size_t)r * n + j0, acc0);
         store16_u32(A.ks_q + ((size_t)A.level + r) * n + j0, acc1);
     } else {
-        const uint2* twi = Ti.tw + ((size_t)pid << log_n);
+        const TwTable twi{Ti.tw + ((size_t)pid << log_n), pc.q};
         const int slot = r >= A.level ? r - A.level : A.n_p + (r < A.dlo ? r : A.dlo + (r - dhi));
 #pragma unroll
         for (int poly = 0; poly < 2; poly++) {
             uint32_t x[16];
 #pragma unroll
             for (int k = 0; k < 16; k++) x[k] = poly ? acc1[k] : acc0[k];
-            by_class(q, [&](auto tag) {
+            by_class(pc.q, [&](auto tag) {
                 constexpr bool W = decltype(tag)::value;
-                gs_stages<4, W, false>(x, q, [&](int u, int b) {
+                gs_stages<4, W, false>(x, pc, [&](int u, int b) {
                     return twi[(1 << (LOG1 + 4 + u)) + (h << (4 + u)) + (rp << u) + b];
                 });
 #pragma unroll
@@ -717,7 +731,7 @@ __device__ __forceinline__ void keymult_store(const NttTables& Ti, const KmArgs&
 #pragma unroll
                 for (int k = 0; k < 16; k++) x[k] = lds[row_lds(rr, rp + 16 * k)];
                 __syncthreads();
-                gs_stages<4, W, false>(x, q, [&](int u, int b) { return twi[(1 << (LOG1 + u)) + (h << u) + b]; });
+                gs_stages<4, W, false>(x, pc, [&](int u, int b) { return twi[(1 << (LOG1 + u)) + (h << u) + b]; });
             });
             uint32_t* dst = A.ks_p + ((size_t)poly * (A.n_p + A.rs) + slot) * n + (size_t)h * ROW;
 #pragma unroll
@@ -772,12 +786,12 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult(NttTables Tf, NttTables
     const int beta = (woff + A.level + A.n_p - 1) / A.n_p;
     const int log_n = Tf.log_n;
     const int pid = r < A.level ? A.base + r : A.n_q + (r - A.level);  // also the key row
-    const uint32_t q = Tf.mods[pid], qinv = Tf.qinvs[pid];
+    const PrimeC pc = Tf.prime(pid);
+    const uint32_t q = pc.q, qinv = pc.qinv;
     const int rp = threadIdx.x % 16, rr = threadIdx.x / 16;
     const int h = blockIdx.x * ROWS_PER_WG + rr;
     const int j0 = h * ROW + 16 * rp;
     const size_t n = (size_t)1 << log_n;
-    const uint2* twf = Tf.tw + ((size_t)pid << log_n);
     const int rows = A.level + A.n_p, key_rows = A.n_q + A.n_p;
 
     uint32_t acc0[16], acc1[16];
@@ -785,9 +799,9 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult(NttTables Tf, NttTables
     for (int k = 0; k < 16; k++) acc0[k] = acc1[k] = 0;
 
     // The row's prime is the same for every digit: its row-pass twiddles are
-    // generated into LDS once, ahead of the digit loop.
-    __shared__ uint2 tws[OWN == Own::Hoisted ? 1 : ROWS_PER_WG * ROW_TW_SLOTS];
-    if constexpr (OWN != Own::Hoisted) stage_row_twiddles<LOG1>(tws, twf, blockIdx.x * ROWS_PER_WG, q);
+    // staged in LDS once, ahead of the digit loop.
+    __shared__ int2 tws[OWN == Own::Hoisted ? 1 : ROWS_PER_WG * ROW_TW_SLOTS];
+    if constexpr (OWN != Own::Hoisted) stage_row_twiddles<LOG1>(tws, Tf.tw + ((size_t)pid << log_n), blockIdx.x * ROWS_PER_WG, q);
 
     for (int j = 0; j < beta; j++) {
         // this digit's key rows are loaded first and arrive while x is formed
@@ -841,14 +855,16 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult(NttTables Tf, NttTables
             for (int k = 0; k < 16; k++) x[k] = src[rp + 16 * k];
             by_class(q, [&](auto tag) {
                 constexpr bool W = decltype(tag)::value;
-                ct_stages<4, W>(x, q, [&](int u, int b) { return row_tw1(tws, rr, u, b); });
+                ct_stages<4, W>(x, pc, [&](int u, int b) { return row_tw1(tws, rr, u, b); });
 #pragma unroll
                 for (int k = 0; k < 16; k++) lds[row_lds(rr, rp + 16 * k)] = x[k];
                 __syncthreads();
 #pragma unroll
                 for (int k = 0; k < 16; k++) x[k] = lds[row_lds(rr, 16 * rp + k)];
                 __syncthreads();
-                ct_stages<4, W>(x, q, [&](int u, int b) { return row_tw2(tws, rr, rp, u, b); });
+                ct_stages<4, W>(x, pc, [&](int u, int b) { return row_tw2(tws, rr, rp, u, b); });
+#pragma unroll
+                for (int k = 0; k < 16; k++) x[k] = fwd_canon<W>(x[k], pc);
             });
         }
 #pragma unroll
@@ -866,7 +882,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult(NttTables Tf, NttTables
                 acc0[k] = add_mod(acc0[k], mulc(A.b0[(size_t)r * n + aut_src(j0 + k, A.galois, log_n)], c, q), q);
         }
     }
-    keymult_store<LOG1>(Ti, A, r, pid, h, rp, rr, q, lds, acc0, acc1);
+    keymult_store<LOG1>(Ti, A, r, pid, h, rp, rr, pc, lds, acc0, acc1);
 }
 
 // ---------------------------------------------------------------------------
@@ -876,32 +892,51 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult(NttTables Tf, NttTables
 //  * The ModUp rows finish their NTT row pass as four radix-4 rounds with
 //    three exchanges through the wave's own LDS rows (as k_fwd_rows4); the
 //    row's twelve twiddles per thread stay in registers across the digits.
-//  * The digit products of a coefficient (each below q^2 < 2^62) are summed
-//    exactly in 64 bits and reduced once: x 2^-32 of the sum is the same
-//    residue as the sum of per-digit Montgomery products.  At most four
-//    products (or a folded value and three products) are summed before a
-//    fold (hi 2^32 + lo -> [hi 2^32]_q + lo), which keeps the sum below
-//    2q 2^32, the input range of redc64.
+//  * The digit products of a coefficient are summed exactly in 64 bits and
+//    reduced once: x 2^-32 of the sum is the same residue as the sum of
+//    per-digit Montgomery products (KmSum below).
 //  * P rows (and the rows a following rescaling drops) run ModDown's INTT
 //    row pass the same way before they are stored.
 // ---------------------------------------------------------------------------
-// sum x 2^-32 mod q for a sum below 2q 2^32 (odd q < 2^31, qinv = q^-1 mod
-// 2^32): m = lo qinv makes sum - m q divisible by 2^32 with equal low words,
-// so the quotient is hi - mulhi(m, q), in (-q, 2q); two corrections end in
-// [0, q).
-__device__ __forceinline__ uint32_t redc64(uint64_t sum, uint32_t q, uint32_t qinv)
-{
-    const uint32_t lo = (uint32_t)sum, hi = (uint32_t)(sum >> 32);
-    const uint32_t t = __umulhi(lo * qinv, q);
-    const uint32_t r = hi >= t ? hi - t : hi - t + q;
-    return red2(r, q);
-}
-
-// hi 2^32 + lo -> lo + [hi 2^32]_q (same residue, below 2^32 + q)
-__device__ __forceinline__ uint64_t fold64(uint64_t sum, uint2 r1, uint32_t q)
-{
-    return (uint64_t)(uint32_t)sum + mulc((uint32_t)(sum >> 32), r1, q);
-}
+// Sums of products x k of one coefficient, k a canonical key residue.  A wide
+// prime (q < 2^30) takes x as the row pass leaves it, any forward value
+// (|x| < 0.97 2^31): the sum is signed, a row product counts 2 quarters of
+// q 2^32 and a product of canonical residues 1, and up to 6 quarters the signed
+// Montgomery reduction ends in (-2q, 2q).  A 31-bit prime takes canonical x:
+// four products below q^2 fit unsigned, and redc64 reduces a sum below
+// 2q 2^32.  Before the limit is passed the sum is folded:
+// hi 2^32 + lo -> lo + [hi 2^32]_q, counted 1.
+template <bool W>
+struct KmSum {
+    static constexpr int ROW = W ? 2 : 1, CANON = 1, LIMIT = W ? 6 : 4;
+    uint64_t s;
+    __device__ __forceinline__ void mac(uint32_t x, uint32_t k)
+    {
+        if constexpr (W) s += (uint64_t)((int64_t)(int32_t)x * (int64_t)(int32_t)k);
+        else s += (uint64_t)x * k;
+    }
+    __device__ __forceinline__ void fold(uint2 r1, uint32_t q)
+    {
+        // a wide prime's high word lies in (-2q, 2q): 2q more is the same residue
+        const uint32_t hi = (uint32_t)(s >> 32) + (W ? 2 * q : 0u);
+        s = (uint64_t)(uint32_t)s + mulc(hi, r1, q);
+    }
+    // sum x 2^-32 in [0, q)
+    __device__ __forceinline__ uint32_t reduce(uint32_t q, uint32_t qinv) const
+    {
+        if constexpr (W) {
+            const uint32_t r = (uint32_t)smr64((int64_t)s, q, qinv);
+            return red2(min(r, r + 2 * q), q);
+        } else {
+            // m = lo qinv makes s - m q divisible by 2^32 with equal low words,
+            // so the quotient is hi - mulhi(m, q), in (-q, 2q)
+            const uint32_t lo = (uint32_t)s, hi = (uint32_t)(s >> 32);
+            const uint32_t t = __umulhi(lo * qinv, q);
+            const uint32_t r = hi >= t ? hi - t : hi - t + q;
+            return red2(r, q);
+        }
+    }
+};
 
 template <int LOG1, Own OWN, Extra EX>
 __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTables Ti, KmArgs A)
@@ -917,7 +952,8 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
     const int beta = (woff + A.level + A.n_p - 1) / A.n_p;
     const int log_n = Tf.log_n;
     const int pid = r < A.level ? A.base + r : A.n_q + (r - A.level);  // also the key row
-    const uint32_t q = Tf.mods[pid], qinv = Tf.qinvs[pid];
+    const PrimeC pc = Tf.prime(pid);
+    const uint32_t q = pc.q, qinv = pc.qinv;
     const int t = threadIdx.x & 63, w = wave_id();
     const int h = blockIdx.x * ROWS4 + w;
     const int j0 = h * ROW + 4 * t;  // this thread's residues: row h, positions 4t .. 4t+3
@@ -928,12 +964,15 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
     const size_t n = (size_t)1 << log_n;
     const int rows = A.level + A.n_p, key_rows = A.n_q + A.n_p;
 
-    uint2 twf[4][3];
-    if constexpr (OWN != Own::Hoisted) row4_twiddles_q<LOG1, false>(Tf.twq + ((size_t)pid << log_n), q, h, t, twf);
-    uint64_t s0[4], s1[4];
+    by_class(q, [&](auto tag) {
+    constexpr bool W = decltype(tag)::value;
+    using Sum = KmSum<W>;
+    int2 twf[4][3];
+    if constexpr (OWN != Own::Hoisted) row4_twiddles<LOG1, false>(Tf.tw + ((size_t)pid << log_n), q, h, t, twf);
+    Sum s0[4], s1[4];
 #pragma unroll
-    for (int k = 0; k < 4; k++) s0[k] = s1[k] = 0;
-    int terms = 0;  // products in s0 / s1 since the last fold
+    for (int k = 0; k < 4; k++) s0[k].s = s1[k].s = 0;
+    int terms = 0;  // what s0 / s1 hold, in KmSum's count
     const uint2 r1 = A.r1[pid];
     constexpr bool EXTRA = OWN == Own::Tensor && EX == Extra::HMult;
 
@@ -981,11 +1020,13 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
     auto step = [&](int j, Dig& cur, Dig& nxt) {
         if (j + 1 < beta) issue(j + 1, nxt);
         const bool own = j == jown;
-        if (terms + 1 + (EXTRA && own ? 1 : 0) > 4) {  // uniform across the launch
+        const int more = own || OWN == Own::Hoisted ? Sum::CANON + (EXTRA ? Sum::CANON : 0) : Sum::ROW;
+        if (terms + more > Sum::LIMIT) {  // uniform across the row
 #pragma unroll
-            for (int k = 0; k < 4; k++) s0[k] = fold64(s0[k], r1, q), s1[k] = fold64(s1[k], r1, q);
-            terms = 1;  // the folded value (below 2^32 + q) counts as one product
+            for (int k = 0; k < 4; k++) s0[k].fold(r1, q), s1[k].fold(r1, q);
+            terms = 1;
         }
+        terms += more;
         uint32_t x[4];
         if (own) {
             if constexpr (OWN == Own::Tensor) {
@@ -996,10 +1037,9 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
                     for (int k = 0; k < 4; k++) {
                         const uint32_t d0 = mont(o2[k], o3[k], q, qinv);
                         const uint32_t d1 = add_mod(mont(o2[k], o1[k], q, qinv), mont(o0[k], o3[k], q, qinv), q);
-                        s0[k] += (uint64_t)d0 * pq;
-                        s1[k] += (uint64_t)d1 * pq;
+                        s0[k].mac(d0, pq);
+                        s1[k].mac(d1, pq);
                     }
-                    terms++;
                 }
 #pragma unroll
                 for (int k = 0; k < 4; k++) x[k] = mont(o0[k], o1[k], q, qinv);
@@ -1011,15 +1051,19 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
         } else {
 #pragma unroll
             for (int k = 0; k < 4; k++) x[k] = cur.x[k];
-            if constexpr (OWN != Own::Hoisted)
-                by_class(q, [&](auto tag) { row4_fwd<decltype(tag)::value>(x, q, lds, w, t, twf); });
+            if constexpr (OWN != Own::Hoisted) {
+                row4_fwd<W>(x, pc, lds, w, t, twf);
+                if constexpr (!W) {
+#pragma unroll
+                    for (int k = 0; k < 4; k++) x[k] = fwd_canon<W>(x[k], pc);
+                }
+            }
         }
 #pragma unroll
         for (int k = 0; k < 4; k++) {
-            s0[k] += (uint64_t)x[k] * cur.kb[k];
-            s1[k] += (uint64_t)x[k] * cur.ka[k];
+            s0[k].mac(x[k], cur.kb[k]);
+            s1[k].mac(x[k], cur.ka[k]);
         }
-        terms++;
     };
     Dig da, db;
     issue(0, da);
@@ -1030,7 +1074,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
 
     uint32_t acc0[4], acc1[4];
 #pragma unroll
-    for (int k = 0; k < 4; k++) acc0[k] = redc64(s0[k], q, qinv), acc1[k] = redc64(s1[k], q, qinv);
+    for (int k = 0; k < 4; k++) acc0[k] = s0[k].reduce(q, qinv), acc1[k] = s1[k].reduce(q, qinv);
     if (r < A.level) {
         if constexpr (EX == Extra::HRot) {
             const uint2 c = A.p_r2[pid];
@@ -1049,19 +1093,20 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
         storev_u32<4>(A.ks_q + (((size_t)A.level + r) * n + hrow) + l4, acc1);
         return;
     }
-    uint2 twi[4][3];
-    row4_twiddles_q<LOG1, true>(Ti.twq + ((size_t)pid << log_n), q, h, t, twi);
+    int2 twi[4][3];
+    row4_twiddles<LOG1, true>(Ti.tw + ((size_t)pid << log_n), q, h, t, twi);
     const int slot = r >= A.level ? r - A.level : A.n_p + (r < A.dlo ? r : A.dlo + (r - dhi));
 #pragma unroll
     for (int poly = 0; poly < 2; poly++) {
         uint32_t x[4];
 #pragma unroll
         for (int k = 0; k < 4; k++) x[k] = poly ? acc1[k] : acc0[k];
-        by_class(q, [&](auto tag) { row4_inv<decltype(tag)::value>(x, q, lds, w, t, twi); });
+        row4_inv<W>(x, pc, lds, w, t, twi);
         uint32_t* dst = A.ks_p + ((size_t)poly * (A.n_p + A.rs) + slot) * n + (size_t)h * ROW;
 #pragma unroll
         for (int k = 0; k < 4; k++) dst[t + 64 * k] = x[k];
     }
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -1085,7 +1130,8 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult_sum(NttTables Tf, NttTa
     const int beta = (woff + A.level + A.n_p - 1) / A.n_p;
     const int log_n = Tf.log_n;
     const int pid = r < A.level ? A.base + r : A.n_q + (r - A.level);  // also the key and plaintext row
-    const uint32_t q = Tf.mods[pid], qinv = Tf.qinvs[pid];
+    const PrimeC pc = Tf.prime(pid);
+    const uint32_t q = pc.q, qinv = pc.qinv;
     const int rp = threadIdx.x % 16, rr = threadIdx.x / 16;
     const int h = blockIdx.x * ROWS_PER_WG + rr;
     const int j0 = h * ROW + 16 * rp;
@@ -1142,7 +1188,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult_sum(NttTables Tf, NttTa
             }
         }
     }
-    keymult_store<LOG1>(Ti, A, r, pid, h, rp, rr, q, lds, acc0, acc1);
+    keymult_store<LOG1>(Ti, A, r, pid, h, rp, rr, pc, lds, acc0, acc1);
 }
 
 // ---------------------------------------------------------------------------
@@ -1256,8 +1302,7 @@ __global__ void k_bconv_matrix(const int32_t* y, const uint32_t* mods, const uin
 // ---------------------------------------------------------------------------
 static NttTables tables(const Ctx& c, bool inverse)
 {
-    return NttTables{inverse ? c.tw_inv : c.tw_fwd, inverse ? c.twq_inv : c.twq_fwd, c.mods, c.qinvs, c.log_n,
-                     c.xcd_pair};
+    return NttTables{inverse ? c.tw_inv : c.tw_fwd, c.mods, c.qinvs, c.rcs, c.log_n, c.xcd_pair};
 }
 
 #define CKKS_DISPATCH_LOG1(log1, CALL)                  \

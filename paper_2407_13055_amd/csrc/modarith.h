@@ -10,6 +10,8 @@
 //                      Montgomery quotient needs no product of x with a
 //                      data-dependent value: 3 multiplies, 3 adds, output
 //                      canonical in [0, q) for any 32-bit x.
+//  * mulr(x, w, nq)    x*w mod q for a known constant and any signed 32-bit x,
+//                      in (-3q/4, 3q/4): 3 multiply-adds (the NTT butterflies).
 //  * smr64(x, t, tinv) signed Montgomery reduction (Seiler's signed variant
 //                      of Montgomery's method) of a 64-bit signed sum: the
 //                      reduction Sec. 4.1 picks for base conversion.
@@ -50,18 +52,43 @@ __device__ __forceinline__ uint32_t mont(uint32_t a, uint32_t b, uint32_t q, uin
     return fix_signed(hi - t, q);
 }
 
-// Shoup multiplication by a constant w < q with ws = floor(w 2^32 / q):
-// x*w - floor(x ws / 2^32) q lies in [0, 2q) for any 32-bit x (2 multiplies
-// by known constants, one by the quotient estimate).
-__device__ __forceinline__ uint32_t mul_shoup(uint32_t x, uint32_t w, uint32_t ws, uint32_t q)
-{
-    return x * w - __umulhi(x, ws) * q;
-}
+// A prime as the kernels use it: q, q^-1 mod 2^32, -q mod 2^32, round(2^32 / q).
+struct PrimeC {
+    uint32_t q, qinv, nq;
+    int32_t rc;
+};
 
-// the same product negated modulo 2^32: 2^32 - (x w mod q in [0, 2q)), or 0
-__device__ __forceinline__ uint32_t mul_shoup_neg(uint32_t x, uint32_t w, uint32_t ws, uint32_t q)
+// Product by a constant w, centred: the constant is the pair (w, ws) with w
+// the centred representative (|w| < q/2) and ws = round(w 2^32 / q).  With
+// e = round(x ws / 2^32) the result x w - e q has
+//   |x w - e q| <= q/2 + |x| q / 2^33  (rounding of e, and of ws times x),
+// so below 3q/4 for every 32-bit signed x: no correction, and the sign bit
+// is kept for the sums that follow.  Three multiply-add instructions:
+// v_mad_i64_i32 with 2^31 added in (its high word is e), v_mul_lo, and
+// v_mad_u64_u32 with -q for the low word.
+__device__ __forceinline__ int32_t round_quot(int32_t x, int32_t ws)
 {
-    return __umulhi(x, ws) * q - x * w;
+    return (int32_t)(((int64_t)x * ws + 0x80000000ll) >> 32);
+}
+__device__ __forceinline__ int32_t mulr(int32_t x, int2 w, uint32_t nq)
+{
+    return (int32_t)((uint32_t)round_quot(x, w.y) * nq + (uint32_t)x * (uint32_t)w.x);
+}
+// the same plus c (the multiply-add of x w takes it: no instruction more)
+__device__ __forceinline__ uint32_t mulr_add(int32_t x, int2 w, uint32_t nq, uint32_t c)
+{
+    return (uint32_t)round_quot(x, w.y) * nq + ((uint32_t)x * (uint32_t)w.x + c);
+}
+// mulr by 1: any 32-bit signed x to its residue in (-3q/4, 3q/4)
+__device__ __forceinline__ int32_t centre(int32_t x, const PrimeC& p)
+{
+    return (int32_t)((uint32_t)round_quot(x, p.rc) * p.nq + (uint32_t)x);
+}
+// The pair of a constant kept as ws alone: ws q = w 2^32 + d q with
+// |d| <= 1/2, so w = round(ws q / 2^32) (one v_mad_i64_i32; q < 2^31).
+__device__ __forceinline__ int2 const_from_quot(int32_t ws, uint32_t q)
+{
+    return make_int2(round_quot(ws, (int32_t)q), ws);
 }
 
 // [0, 2m) -> [0, m)
@@ -87,17 +114,5 @@ __device__ __forceinline__ uint32_t canon_signed(int32_t y, uint32_t t) { return
 
 // centred representative of v in [0, q): v if 2v < q else v - q
 __device__ __forceinline__ int32_t lift(uint32_t v, uint32_t q) { return (int32_t)(v > (q >> 1) ? v - q : v); }
-
-// reduce a centred int32 into [0, t); one conditional add when |y| < t (the
-// case for lifted residues of a prime of the same size), a division otherwise
-__device__ __forceinline__ uint32_t reduce_centred(int32_t y, uint32_t t)
-{
-    uint32_t u = y < 0 ? (uint32_t)(y + (int32_t)t) : (uint32_t)y;
-    if (u >= t) {
-        int32_t r = y % (int32_t)t;
-        u = (uint32_t)(r < 0 ? r + (int32_t)t : r);
-    }
-    return u;
-}
 
 }  // namespace ckks

@@ -32,93 +32,106 @@ constexpr int NTT_THREADS = 256;
 constexpr int ROWS_PER_WG = NTT_THREADS / 16;  // row pass: 16 threads per row
 
 // ---------------------------------------------------------------------------
-// Butterflies with Shoup twiddles (w, floor(w 2^32/q)) and lazy ranges.
-// Two classes of primes, chosen per work-group (uniform branch):
-//   q < 2^30 ("wide"): forward stages keep values in [0, 4q), inverse
-//     stages in [0, 2q): 3 multiplies + 5 or 6 adds per butterfly.
-//   q >= 2^30 (31-bit): 4q overflows 32 bits, so forward values stay in
-//     [0, 2q) and inverse values canonical: 3 multiplies + 7 adds.
-// Pass boundaries: a forward column pass hands the row pass values in the
-// forward range; a forward row pass and an inverse column pass end with a
-// reduction to [0, q); an inverse row pass hands the column pass values in
-// the inverse range.  Inputs read from memory are canonical.
+// Butterflies.  Twiddles are centred pairs (w, round(w 2^32 / q)) and a
+// product (mulr) lands in (-3q/4, 3q/4) for any signed 32-bit operand.  Two
+// classes of primes, chosen per work-group (uniform branch):
+//   q < 2^30 ("wide"): forward values are signed 32-bit integers.  A stage
+//     that first centres its a (two multiply-adds) and one that does not
+//     alternate: from any 32-bit input, a centring stage leaves at most
+//     (3/2) q and the stage after it at most 2^31 again (a centred, the sum
+//     grows by |t| <= q/2 + |x| q / 2^33 per stage).  A butterfly is 3
+//     instructions for the product, 2 for the sums and on average 1 for the
+//     centring.  Inverse values lie in [0, 2q): the difference is signed by
+//     itself and the product's multiply-add adds q: 3 + 1, and 3 for the sum
+//     and its reduction.
+//   q >= 2^30 (31-bit): no headroom for sums.  Forward values lie in [-q, q):
+//     both operands are corrected to [0, q) (one min each), the sum takes -q
+//     with it; inverse values are canonical: 9 instructions.
+// Against Shoup's product in [0, 2q) these are 8 -> 6 and 11 -> 9 instructions
+// forward, 9 -> 7 and 11 -> 9 inverse (a loop of forward butterflies: 9.1 ->
+// 7.6 CU cycles per wave), and one table word per twiddle instead of two:
+// HMult + rescale at N = 2^16, 24 limbs 86.5 -> 83.3 us, 64 of them at 4 to 24
+// limbs 2302 -> 2205 us, 32 hoisted rotations 1114 -> 1071 us.
+// Pass boundaries: a forward pass takes canonical or centred residues or
+// another forward pass's values and leaves forward values (fwd_canon gives
+// [0, q)); an inverse row pass hands the column pass values in the inverse
+// range, an inverse column pass ends canonical.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ bool wide_prime(uint32_t q) { return q < (1u << 30); }
 
 // in-register radix-2 stages over the low NS bits of the register index k
-// (x[k], k < E; E = 16, or 4 in the wave-per-row passes).  tw(u, b) returns the Shoup twiddle of stage u for
-// register block b = k >> (NS - u).
+// (x[k], k < E; E = 16, or 4 in the wave-per-row passes).  tw(u, b) returns
+// the twiddle of stage u for register block b = k >> (NS - u).
 template <int NS, bool WIDE, class TW, int E>
-__device__ __forceinline__ void ct_stages(uint32_t (&x)[E], uint32_t q, TW&& tw)
+__device__ __forceinline__ void ct_stages(uint32_t (&x)[E], const PrimeC& p, TW&& tw)
 {
-    const uint32_t q2 = 2 * q;
 #pragma unroll
     for (int u = 0; u < NS; u++) {
         const int half = 1 << (NS - 1 - u), span = 2 * half;
 #pragma unroll
         for (int b = 0; b < E / span; b++) {
-            const uint2 w = tw(u, b);
+            const int2 w = tw(u, b);
 #pragma unroll
             for (int m = 0; m < half; m++) {
                 const int k = b * span + m;
-                if constexpr (WIDE) {  // [0, 4q) -> [0, 4q)
-                    // nt = -t (mod 2^32) for the Shoup product t in [0, 2q):
-                    // a + t = a - nt, and a - t + 2q is one three-input add
-                    const uint32_t a = red2(x[k], q2);
-                    const uint32_t nt = mul_shoup_neg(x[k + half], w.x, w.y, q);
-                    x[k] = a - nt;
-                    x[k + half] = a + nt + q2;
-                } else {               // [0, 2q) -> [0, 2q)
-                    const uint32_t a = red2(x[k], q);
-                    const uint32_t t = red2(mul_shoup(x[k + half], w.x, w.y, q), q);
+                const uint32_t t = (uint32_t)mulr((int32_t)x[k + half], w, p.nq);
+                if constexpr (WIDE) {
+                    const uint32_t a = (u & 1) ? x[k] : (uint32_t)centre((int32_t)x[k], p);
                     x[k] = a + t;
-                    x[k + half] = a - t + q;
+                    x[k + half] = a - t;
+                } else {  // [-q, q) -> [-q, q)
+                    const uint32_t a = fix_signed(x[k], p.q), c = fix_signed(t, p.q);
+                    x[k] = a + c + p.nq;
+                    x[k + half] = a - c;
                 }
             }
         }
     }
 }
 
-// forward range -> [0, q)
-template <bool WIDE, int E>
-__device__ __forceinline__ void ct_canon(uint32_t (&x)[E], uint32_t q)
+// forward range -> a residue small enough for one signed sum with a canonical
+// one: (-q, q)
+template <bool WIDE>
+__device__ __forceinline__ int32_t fwd_centre(uint32_t x, const PrimeC& p)
 {
-#pragma unroll
-    for (int k = 0; k < E; k++) x[k] = red2(WIDE ? red2(x[k], 2 * q) : x[k], q);
+    return WIDE ? centre((int32_t)x, p) : (int32_t)fix_signed(x, p.q);
+}
+// forward range -> [0, q)
+template <bool WIDE>
+__device__ __forceinline__ uint32_t fwd_canon(uint32_t x, const PrimeC& p)
+{
+    return fix_signed(WIDE ? (uint32_t)centre((int32_t)x, p) : x, p.q);
 }
 
 // Gentleman-Sande inverse stages, u = NS-1 .. 0.  If FOLD, stage u == 0 also
-// multiplies both outputs by a constant: c = (c, c_shoup, c w, (c w)_shoup)
-// with w the stage-0 twiddle, and ends canonical.
+// multiplies both outputs by a constant: c = (c, c_s, c w, (c w)_s) with w the
+// stage-0 twiddle, and ends canonical.
 template <int NS, bool WIDE, bool FOLD, class TW, int E>
-__device__ __forceinline__ void gs_stages(uint32_t (&x)[E], uint32_t q, TW&& tw, uint4 c = uint4{0, 0, 0, 0})
+__device__ __forceinline__ void gs_stages(uint32_t (&x)[E], const PrimeC& p, TW&& tw, int4 c = int4{0, 0, 0, 0})
 {
-    const uint32_t q2 = 2 * q;
+    const uint32_t q2 = 2 * p.q;
 #pragma unroll
     for (int u = NS - 1; u >= 0; u--) {
         const int half = 1 << (NS - 1 - u), span = 2 * half;
 #pragma unroll
         for (int b = 0; b < E / span; b++) {
-            const uint2 w = (FOLD && u == 0) ? make_uint2(c.z, c.w) : tw(u, b);
+            const int2 w = (FOLD && u == 0) ? make_int2(c.z, c.w) : tw(u, b);
 #pragma unroll
             for (int m = 0; m < half; m++) {
                 const int k = b * span + m;
                 const uint32_t a = x[k], y = x[k + half];
-                if constexpr (WIDE) {  // [0, 2q) -> [0, 2q)
-                    if (FOLD && u == 0) {
-                        x[k] = red2(mul_shoup(a + y, c.x, c.y, q), q);
-                        x[k + half] = red2(mul_shoup(a + q2 - y, w.x, w.y, q), q);
-                    } else {
-                        x[k] = red2(a + y, q2);
-                        x[k + half] = mul_shoup(a + q2 - y, w.x, w.y, q);
-                    }
-                } else {               // [0, q) -> [0, q)
-                    if (FOLD && u == 0) {
-                        x[k] = red2(mul_shoup(a + y, c.x, c.y, q), q);
-                    } else {
-                        x[k] = red2(a + y, q);
-                    }
-                    x[k + half] = red2(mul_shoup(a + q - y, w.x, w.y, q), q);
+                const int32_t d = (int32_t)(a - y);  // (-2q, 2q), or (-q, q)
+                if (FOLD && u == 0) {
+                    // a + y less 2q (or q), so that the sum is a signed operand too
+                    const int32_t s = (int32_t)(a + y + (WIDE ? 2 * p.nq : p.nq));
+                    x[k] = fix_signed((uint32_t)mulr(s, make_int2(c.x, c.y), p.nq), p.q);
+                    x[k + half] = fix_signed((uint32_t)mulr(d, w, p.nq), p.q);
+                } else if constexpr (WIDE) {  // [0, 2q) -> [0, 2q)
+                    x[k] = red2(a + y, q2);
+                    x[k + half] = mulr_add(d, w, p.nq, p.q);
+                } else {                      // [0, q) -> [0, q)
+                    x[k] = red2(a + y, p.q);
+                    x[k + half] = fix_signed((uint32_t)mulr(d, w, p.nq), p.q);
                 }
             }
         }
@@ -194,10 +207,6 @@ __host__ __device__ constexpr int row_tiles() { return (1 << LOG1) / ROWS_PER_WG
 // St::store16 consume outputs (fused epilogues); St::final_const(M, limb) is
 // the constant folded into the last inverse stage.  M.pid[limb] is the prime.
 // ---------------------------------------------------------------------------
-struct PrimeC {
-    uint32_t q, qinv;
-};
-
 // Launch maps reach the kernels either by value (kernel argument; the
 // stand-alone NTT call with caller-chosen primes) or as a pointer to a map
 // precomputed in device memory at context creation (every internal launch:
@@ -231,13 +240,27 @@ struct MapDir {
     }
 };
 
+__device__ __forceinline__ PrimeC prime_c(const uint32_t* mods, const uint32_t* qinvs, const int32_t* rcs, int pid)
+{
+    const uint32_t q = mods[pid];
+    return PrimeC{q, qinvs[pid], 0u - q, rcs[pid]};
+}
+
 struct NttTables {
-    const uint2* tw;        // [n_primes][N] Shoup pairs of Psi (forward) or Psi^-1 (inverse)
-    const uint32_t* twq;    // [n_primes][N] the same twiddles as floor(w 2^32 / q) alone
+    const int32_t* tw;      // [n_primes][N] Psi (forward) or Psi^-1 (inverse) as round(w 2^32 / q)
     const uint32_t* mods;   // [n_primes]
     const uint32_t* qinvs;  // [n_primes] q^-1 mod 2^32
+    const int32_t* rcs;     // [n_primes] round(2^32 / q)
     int log_n;
     int xcd_pair;           // column-tile order (col_tile)
+    __device__ PrimeC prime(int pid) const { return prime_c(mods, qinvs, rcs, pid); }
+};
+
+// a prime's twiddle table, read as pairs
+struct TwTable {
+    const int32_t* p;
+    uint32_t q;
+    __device__ __forceinline__ int2 operator[](int i) const { return const_from_quot(p[i], q); }
 };
 
 // Row-pass twiddles of a work-group's ROWS_PER_WG rows, staged in LDS (one
@@ -246,39 +269,23 @@ struct NttTables {
 // (stage u = log2(s+1), block s+1-2^u: read at (1 << u) - 1 + b); s >= 16 is
 // the second round (stage u = log2(s)-4, local index (rp << u) + b: read at
 // (16 << u) + (rp << u) + b).  Ends with a barrier.
-//
-// The entries are generated, not loaded (on-the-fly twiddles, Sec. 4.2): the
-// table holds psi^brev(i), and the index of a row-pass twiddle splits into
-// disjoint bit fields, high = 2^(LOG1+lg) + (h << lg) and low = loc < 2^lg,
-// so psi^brev(i) = psi^brev(high) * psi^brev(low): two table entries shared
-// by many slots, one Shoup product, and the Shoup companion
-// floor(w 2^32 / q) from a double-precision estimate corrected exactly by
-// one step.  The work-group reads 2 KB of table instead of 32 KB.
 constexpr int ROW_TW_SLOTS = 256;
 template <int LOG1>
-__device__ __forceinline__ void stage_row_twiddles(uint2* tws, const uint2* tw, int h0, uint32_t q)
+__device__ __forceinline__ void stage_row_twiddles(int2* tws, const int32_t* tw, int h0, uint32_t q)
 {
     static_assert(NTT_THREADS == ROW_TW_SLOTS, "one slot per thread");
     const int sl = threadIdx.x;
     if (sl != 15) {
         const int lg = 31 - __clz(sl < 15 ? sl + 1 : sl);
         const int loc = sl < 15 ? sl + 1 - (1 << lg) : sl - (1 << lg);
-        const uint2 lo = tw[loc];
-        const double rq = 4294967296.0 / (double)q;
 #pragma unroll 4
-        for (int i = 0; i < ROWS_PER_WG; i++) {
-            const uint32_t hi = tw[(1 << (LOG1 + lg)) + ((h0 + i) << lg)].x;
-            const uint32_t w = red2(mul_shoup(hi, lo.x, lo.y, q), q);
-            uint32_t ws = (uint32_t)((double)w * rq);  // floor(w 2^32 / q) or one off
-            const int64_t r = (int64_t)((uint64_t)w << 32) - (int64_t)((uint64_t)ws * q);
-            ws = r < 0 ? ws - 1 : (r >= (int64_t)q ? ws + 1 : ws);
-            tws[i * ROW_TW_SLOTS + sl] = make_uint2(w, ws);
-        }
+        for (int i = 0; i < ROWS_PER_WG; i++)
+            tws[i * ROW_TW_SLOTS + sl] = const_from_quot(tw[(1 << (LOG1 + lg)) + ((h0 + i) << lg) + loc], q);
     }
     __syncthreads();
 }
-__device__ __forceinline__ uint2 row_tw1(const uint2* tws, int rr, int u, int b) { return tws[rr * ROW_TW_SLOTS + (1 << u) - 1 + b]; }
-__device__ __forceinline__ uint2 row_tw2(const uint2* tws, int rr, int rp, int u, int b)
+__device__ __forceinline__ int2 row_tw1(const int2* tws, int rr, int u, int b) { return tws[rr * ROW_TW_SLOTS + (1 << u) - 1 + b]; }
+__device__ __forceinline__ int2 row_tw2(const int2* tws, int rr, int rp, int u, int b)
 {
     return tws[rr * ROW_TW_SLOTS + (16 << u) + (rp << u) + b];
 }
@@ -296,9 +303,8 @@ __global__ void __launch_bounds__(CT) k_fwd_cols(NttTables T, MS ms, Ld ld0, St 
     using G = ColGeom<LOG1, CT>;
     __shared__ uint32_t lds[G::LDS];
     const int limb = blockIdx.y, pid = M.pid[limb];
-    const uint32_t q = T.mods[pid];
-    const PrimeC pc{q, T.qinvs[pid]};
-    const uint2* tw = T.tw + ((size_t)pid << T.log_n);
+    const PrimeC pc = T.prime(pid);
+    const TwTable tw{T.tw + ((size_t)pid << T.log_n), pc.q};
     const int c = threadIdx.x % G::C, r = threadIdx.x / G::C;
     const int col = col_tile<LOG1, CT>(T.xcd_pair) * G::C + c;
     uint32_t x[16];
@@ -308,16 +314,16 @@ __global__ void __launch_bounds__(CT) k_fwd_cols(NttTables T, MS ms, Ld ld0, St 
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = ld.load(M, limb, (r + G::R * k) * ROW + col, pc);
     }
-    by_class(q, [&](auto tag) {
+    by_class(pc.q, [&](auto tag) {
         constexpr bool W = decltype(tag)::value;
-        ct_stages<4, W>(x, q, [&](int u, int b) { return tw[(1 << u) + b]; });
+        ct_stages<4, W>(x, pc, [&](int u, int b) { return tw[(1 << u) + b]; });
         if constexpr (G::NS2 > 0) {
 #pragma unroll
             for (int k = 0; k < 16; k++) lds[col_lds<G::C>(r + G::R * k, c)] = x[k];
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < 16; k++) x[k] = lds[col_lds<G::C>(16 * r + k, c)];
-            ct_stages<G::NS2, W>(x, q, [&](int u, int b) {
+            ct_stages<G::NS2, W>(x, pc, [&](int u, int b) {
                 return tw[(1 << (4 + u)) + (r << (4 - G::NS2 + u)) + b];
             });
 #pragma unroll
@@ -329,7 +335,7 @@ __global__ void __launch_bounds__(CT) k_fwd_cols(NttTables T, MS ms, Ld ld0, St 
     });
 }
 
-// forward, row pass (stages LOG1 .. LOG1+7); ends canonical
+// forward, row pass (stages LOG1 .. LOG1+7); the storer takes forward values
 template <int LOG1, class MS, class Ld, class St>
 __global__ void __launch_bounds__(NTT_THREADS) k_fwd_rows(NttTables T, MS ms, Ld ld0, St st0)
 {
@@ -341,28 +347,27 @@ __global__ void __launch_bounds__(NTT_THREADS) k_fwd_rows(NttTables T, MS ms, Ld
     const St st = st0.at(blockIdx.z);
     __shared__ uint32_t lds[ROW_LDS_WORDS];
     const int limb = blockIdx.y, pid = M.pid[limb];
-    const uint32_t q = T.mods[pid];
-    const PrimeC pc{q, T.qinvs[pid]};
-    const uint2* tw = T.tw + ((size_t)pid << T.log_n);
+    const PrimeC pc = T.prime(pid);
+    const TwTable tw{T.tw + ((size_t)pid << T.log_n), pc.q};
     const int rp = threadIdx.x % 16, rr = threadIdx.x / 16;
     const int h = blockIdx.x * ROWS_PER_WG + rr;  // 2^LOG1 rows, LOG1 >= 4: exact grid
     uint32_t x[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) x[k] = ld.load(M, limb, h * ROW + rp + 16 * k, pc);
-    by_class(q, [&](auto tag) {
+    by_class(pc.q, [&](auto tag) {
         constexpr bool W = decltype(tag)::value;
-        ct_stages<4, W>(x, q, [&](int u, int b) { return tw[(1 << (LOG1 + u)) + (h << u) + b]; });
+        ct_stages<4, W>(x, pc, [&](int u, int b) { return tw[(1 << (LOG1 + u)) + (h << u) + b]; });
 #pragma unroll
         for (int k = 0; k < 16; k++) lds[row_lds(rr, rp + 16 * k)] = x[k];
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = lds[row_lds(rr, 16 * rp + k)];
-        ct_stages<4, W>(x, q, [&](int u, int b) {
+        ct_stages<4, W>(x, pc, [&](int u, int b) {
             return tw[(1 << (LOG1 + 4 + u)) + (h << (4 + u)) + (rp << u) + b];
         });
-        ct_canon<W>(x, q);
+        st.template store_fwd<16, W>(M, limb, h * ROW + 16 * rp, x, pc,
+                                     st.template prefetch<16>(M, limb, h * ROW + 16 * rp));
     });
-    st.store16(M, limb, h * ROW + 16 * rp, x, pc);
 }
 
 // inverse, row pass (stages LOG1+7 .. LOG1)
@@ -377,16 +382,15 @@ __global__ void __launch_bounds__(NTT_THREADS) k_inv_rows(NttTables T, MS ms, Ld
     const St st = st0.at(blockIdx.z);
     __shared__ uint32_t lds[ROW_LDS_WORDS];
     const int limb = blockIdx.y, pid = M.pid[limb];
-    const uint32_t q = T.mods[pid];
-    const PrimeC pc{q, T.qinvs[pid]};
-    const uint2* tw = T.tw + ((size_t)pid << T.log_n);
+    const PrimeC pc = T.prime(pid);
+    const TwTable tw{T.tw + ((size_t)pid << T.log_n), pc.q};
     const int rp = threadIdx.x % 16, rr = threadIdx.x / 16;
     const int h = blockIdx.x * ROWS_PER_WG + rr;
     uint32_t x[16];
     ld.load16(M, limb, h * ROW + 16 * rp, pc, x);
-    by_class(q, [&](auto tag) {
+    by_class(pc.q, [&](auto tag) {
         constexpr bool W = decltype(tag)::value;
-        gs_stages<4, W, false>(x, q, [&](int u, int b) {
+        gs_stages<4, W, false>(x, pc, [&](int u, int b) {
             return tw[(1 << (LOG1 + 4 + u)) + (h << (4 + u)) + (rp << u) + b];
         });
 #pragma unroll
@@ -394,7 +398,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_inv_rows(NttTables T, MS ms, Ld
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = lds[row_lds(rr, rp + 16 * k)];
-        gs_stages<4, W, false>(x, q, [&](int u, int b) { return tw[(1 << (LOG1 + u)) + (h << u) + b]; });
+        gs_stages<4, W, false>(x, pc, [&](int u, int b) { return tw[(1 << (LOG1 + u)) + (h << u) + b]; });
     });
 #pragma unroll
     for (int k = 0; k < 16; k++) st.store(M, limb, h * ROW + rp + 16 * k, x[k], pc);
@@ -448,15 +452,15 @@ __device__ __forceinline__ void quad_transpose(uint32_t (&x)[4], int lane)
 }
 
 // Forward row pass of the row a wave holds: x[k] = row[t + 64 k] on entry,
-// row[4 t + k] on exit (canonical); tw[j][i]: round j's twiddles (stage 0,
+// row[4 t + k] on exit (forward values); tw[j][i]: round j's twiddles (stage 0,
 // then the two of stage 1).  The exchanges after rounds 0 and 1 go through
 // the wave's LDS row; between rounds 2 and 3 the 16 points of a quad of
 // lanes (lane a of quad m holds 16m + a + 4k, and needs 16m + 4a + k) change
 // places with a quad transpose in registers.  SYNC0: order the pass after a
 // previous pass over the same LDS row.
 template <bool W, bool SYNC0 = true>
-__device__ __forceinline__ void row4_fwd(uint32_t (&x)[4], uint32_t q, uint32_t* lds, int w, int t,
-                                         const uint2 (&tw)[4][3])
+__device__ __forceinline__ void row4_fwd(uint32_t (&x)[4], const PrimeC& p, uint32_t* lds, int w, int t,
+                                         const int2 (&tw)[4][3])
 {
     if (SYNC0) wave_lds_sync();
 #pragma unroll
@@ -470,13 +474,12 @@ __device__ __forceinline__ void row4_fwd(uint32_t (&x)[4], uint32_t q, uint32_t*
 #pragma unroll
             for (int k = 0; k < 4; k++) x[k] = lds[row4_lds(w, l0 + (k << sh))];
         }
-        ct_stages<2, W>(x, q, [&](int u, int b) { return tw[j][u ? 1 + b : 0]; });
+        ct_stages<2, W>(x, p, [&](int u, int b) { return tw[j][u ? 1 + b : 0]; });
         if (j < 2) {
 #pragma unroll
             for (int k = 0; k < 4; k++) lds[row4_lds(w, l0 + (k << sh))] = x[k];
         }
     }
-    ct_canon<W>(x, q);
 }
 
 // Inverse row pass: x[k] = row[4 t + k] on entry, row[t + 64 k] on exit
@@ -484,8 +487,8 @@ __device__ __forceinline__ void row4_fwd(uint32_t (&x)[4], uint32_t q, uint32_t*
 // exchange between rounds 0 and 1 is the quad transpose (the forward pass's
 // last one, undone).
 template <bool W, bool SYNC0 = true>
-__device__ __forceinline__ void row4_inv(uint32_t (&x)[4], uint32_t q, uint32_t* lds, int w, int t,
-                                         const uint2 (&tw)[4][3])
+__device__ __forceinline__ void row4_inv(uint32_t (&x)[4], const PrimeC& p, uint32_t* lds, int w, int t,
+                                         const int2 (&tw)[4][3])
 {
     if (SYNC0) wave_lds_sync();
 #pragma unroll
@@ -499,7 +502,7 @@ __device__ __forceinline__ void row4_inv(uint32_t (&x)[4], uint32_t q, uint32_t*
 #pragma unroll
             for (int k = 0; k < 4; k++) x[k] = lds[row4_lds(w, l0 + (k << sh))];
         }
-        gs_stages<2, W, false>(x, q, [&](int u, int b) { return tw[j][u ? 1 + b : 0]; });
+        gs_stages<2, W, false>(x, p, [&](int u, int b) { return tw[j][u ? 1 + b : 0]; });
         if (j >= 1 && j < 3) {
 #pragma unroll
             for (int k = 0; k < 4; k++) lds[row4_lds(w, l0 + (k << sh))] = x[k];
@@ -507,48 +510,20 @@ __device__ __forceinline__ void row4_inv(uint32_t (&x)[4], uint32_t q, uint32_t*
     }
 }
 
-// The Shoup pair (w, ws) of a twiddle stored as ws = floor(w 2^32 / q)
-// alone (0 <= w < q < 2^32): w 2^32 lies in [ws q, ws q + q), so w lies in
-// [ws q / 2^32, (ws q + q) / 2^32), an interval shorter than 1; the one
-// integer there is ceil(ws q / 2^32).
-__device__ __forceinline__ uint2 shoup_from_quot(uint32_t ws, uint32_t q)
-{
-    const uint32_t lo = ws * q, hi = __umulhi(ws, q);
-    return make_uint2(hi + (lo != 0u ? 1u : 0u), ws);
-}
-
 // the twiddles thread t uses in row h (forward: round j covers stages
 // LOG1 + 2j, LOG1 + 2j + 1; inverse: the same stages in reverse order).
 // h is the same in every lane of a wave, so each entry's address is a
 // wave-uniform base plus a 32-bit lane offset (scalar-base loads).
 template <int LOG1, bool INV>
-__device__ __forceinline__ void row4_twiddles(const uint2* tw, int h, int t, uint2 (&out)[4][3])
+__device__ __forceinline__ void row4_twiddles(const int32_t* tw, uint32_t q, int h, int t, int2 (&out)[4][3])
 {
+    int32_t ws[4][3];
 #pragma unroll
     for (int j = 0; j < 4; j++) {
         const int g = INV ? 6 - 2 * j : 2 * j;         // stage offset of the round's first stage
         const uint32_t blk = (uint32_t)t >> (INV ? 2 * j : 6 - 2 * j);
-        const uint2* s0 = tw + ((1u << (LOG1 + g)) + ((uint32_t)h << g));
-        const uint2* s1 = tw + ((1u << (LOG1 + g + 1)) + ((uint32_t)h << (g + 1)));
-        out[j][0] = s0[blk];
-#pragma unroll
-        for (int b = 0; b < 2; b++) out[j][1 + b] = s1[(blk << 1) + (uint32_t)b];
-    }
-}
-
-// the same twiddles read from the quotient-only table twq of prime q (4
-// bytes per entry; two multiplies per twiddle recover w): for a kernel that
-// reuses them (KeyMult, once per digit), where the halved table traffic pays
-template <int LOG1, bool INV>
-__device__ __forceinline__ void row4_twiddles_q(const uint32_t* twq, uint32_t q, int h, int t, uint2 (&out)[4][3])
-{
-    uint32_t ws[4][3];
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-        const int g = INV ? 6 - 2 * j : 2 * j;         // stage offset of the round's first stage
-        const uint32_t blk = (uint32_t)t >> (INV ? 2 * j : 6 - 2 * j);
-        const uint32_t* s0 = twq + ((1u << (LOG1 + g)) + ((uint32_t)h << g));
-        const uint32_t* s1 = twq + ((1u << (LOG1 + g + 1)) + ((uint32_t)h << (g + 1)));
+        const int32_t* s0 = tw + ((1u << (LOG1 + g)) + ((uint32_t)h << g));
+        const int32_t* s1 = tw + ((1u << (LOG1 + g + 1)) + ((uint32_t)h << (g + 1)));
         ws[j][0] = s0[blk];
 #pragma unroll
         for (int b = 0; b < 2; b++) ws[j][1 + b] = s1[(blk << 1) + (uint32_t)b];
@@ -556,22 +531,21 @@ __device__ __forceinline__ void row4_twiddles_q(const uint32_t* twq, uint32_t q,
 #pragma unroll
     for (int j = 0; j < 4; j++)
 #pragma unroll
-        for (int i = 0; i < 3; i++) out[j][i] = shoup_from_quot(ws[j][i], q);
+        for (int i = 0; i < 3; i++) out[j][i] = const_from_quot(ws[j][i], q);
 }
 
 // Launch-map entries of a work-group's limb (scalar loads issued together;
 // the entries of limbs at or above count are in bounds and unused).
 struct LimbInfo {
     int count, pid;
-    uint32_t q, qinv;
+    PrimeC pc;
 };
 __device__ __forceinline__ LimbInfo limb_info(const NttTables& T, const LaunchMap& M, int limb)
 {
     LimbInfo r;
     r.count = M.count;
     r.pid = M.pid[limb];
-    r.q = T.mods[r.pid];
-    r.qinv = T.qinvs[r.pid];
+    r.pc = T.prime(r.pid);
     return r;
 }
 
@@ -590,17 +564,20 @@ __global__ void __launch_bounds__(NTT_THREADS) k_fwd_rows4(NttTables T, MS ms, L
     const Ld ld = ld0.at(blockIdx.z);
     const St st = st0.at(blockIdx.z);
     __shared__ uint32_t lds[ROWS4 * ROW4_PITCH];
-    const PrimeC pc{I.q, I.qinv};
+    const PrimeC pc = I.pc;
     const int t = threadIdx.x & 63, w = wave_id();
     const int h = blockIdx.x * ROWS4 + w;  // exact grid
     uint32_t x[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) x[k] = ld.load(M, limb, h * ROW + t + 64 * k, pc);
-    uint2 tw[4][3];
-    row4_twiddles<LOG1, false>(T.tw + ((size_t)I.pid << T.log_n), h, t, tw);
+    int2 tw[4][3];
+    row4_twiddles<LOG1, false>(T.tw + ((size_t)I.pid << T.log_n), pc.q, h, t, tw);
     const auto pre = st.template prefetch<4>(M, limb, h * ROW + 4 * t);
-    by_class(I.q, [&](auto tag) { row4_fwd<decltype(tag)::value, false>(x, I.q, lds, w, t, tw); });
-    st.template storev<4>(M, limb, h * ROW + 4 * t, x, pc, pre);
+    by_class(pc.q, [&](auto tag) {
+        constexpr bool W = decltype(tag)::value;
+        row4_fwd<W, false>(x, pc, lds, w, t, tw);
+        st.template store_fwd<4, W>(M, limb, h * ROW + 4 * t, x, pc, pre);
+    });
 }
 
 template <int LOG1, class MS, class Ld, class St>
@@ -615,14 +592,14 @@ __global__ void __launch_bounds__(NTT_THREADS) k_inv_rows4(NttTables T, MS ms, L
     const Ld ld = ld0.at(blockIdx.z);
     const St st = st0.at(blockIdx.z);
     __shared__ uint32_t lds[ROWS4 * ROW4_PITCH];
-    const PrimeC pc{I.q, I.qinv};
+    const PrimeC pc = I.pc;
     const int t = threadIdx.x & 63, w = wave_id();
     const int h = blockIdx.x * ROWS4 + w;
     uint32_t x[4];
     ld.template loadv<4>(M, limb, h * ROW + 4 * t, pc, x);
-    uint2 tw[4][3];
-    row4_twiddles<LOG1, true>(T.tw + ((size_t)I.pid << T.log_n), h, t, tw);
-    by_class(I.q, [&](auto tag) { row4_inv<decltype(tag)::value, false>(x, I.q, lds, w, t, tw); });
+    int2 tw[4][3];
+    row4_twiddles<LOG1, true>(T.tw + ((size_t)I.pid << T.log_n), pc.q, h, t, tw);
+    by_class(pc.q, [&](auto tag) { row4_inv<decltype(tag)::value, false>(x, pc, lds, w, t, tw); });
 #pragma unroll
     for (int k = 0; k < 4; k++) st.store(M, limb, h * ROW + t + 64 * k, x[k], pc);
 }
@@ -679,20 +656,21 @@ __device__ __forceinline__ int col4_tile(int pair)
 
 // A column pass uses the first 2^LOG1 - 1 twiddles of its prime's table
 // (Psi[1 .. 2^LOG1 - 1], shared by every column): a work-group stages them
-// in LDS once (one load per thread, 2 KB at N = 2^16) and every round reads
-// them there.  Entry e of the staged copy is table entry e.  Ends with a
+// in LDS once as pairs (one load per thread, 2 KB at N = 2^16) and every
+// round reads them there.  Entry e of the staged copy is table entry e.  Ends with a
 // barrier.
 template <int LOG1, int NT>
-__device__ __forceinline__ void col4_stage_twiddles(uint2* twl, const uint2* const (&tw)[NT])
+__device__ __forceinline__ void col4_stage_twiddles(int2* twl, const int32_t* const (&tw)[NT], const PrimeC (&p)[NT])
 {
 #pragma unroll
     for (int i = 0; i < NT; i++)
-        for (int e = threadIdx.x; e < (1 << LOG1); e += NTT_THREADS) twl[i * (1 << LOG1) + e] = tw[i][e];
+        for (int e = threadIdx.x; e < (1 << LOG1); e += NTT_THREADS)
+            twl[i * (1 << LOG1) + e] = const_from_quot(tw[i][e], p[i].q);
     __syncthreads();
 }
 // twiddle of stage u of round j (sh: the round's shift) for pair block b
 template <int LOG1>
-__device__ __forceinline__ uint2 col4_tw(const uint2* twl, int t, int sh, int u, int b)
+__device__ __forceinline__ int2 col4_tw(const int2* twl, int t, int sh, int u, int b)
 {
     if (sh < 0) return twl[(1 << (LOG1 - 1)) + 2 * t + b];  // radix-2 round: stage LOG1-1
     const int s0 = LOG1 - 2 - sh, blk = t >> sh;             // radix-4 round: stages s0, s0 + 1
@@ -700,14 +678,14 @@ __device__ __forceinline__ uint2 col4_tw(const uint2* twl, int t, int sh, int u,
 }
 
 // Forward column pass of NT targets held by the work-group: x[i] enters with
-// points t + k TC of column c, leaves with 4t + k (canonical); lds holds
+// points t + k TC of column c, leaves with 4t + k (forward values); lds holds
 // one buffer of Col4::WORDS words per target (a round stores its results
 // where it read its inputs, so one barrier per exchange suffices), twl the
 // staged twiddles of each target
 // (2^LOG1 entries apart).
 template <int LOG1, int NT>
-__device__ __forceinline__ void col4_fwd(uint32_t (&x)[NT][4], const uint32_t (&q)[NT], uint32_t* lds,
-                                         const uint2* twl, int c, int t)
+__device__ __forceinline__ void col4_fwd(uint32_t (&x)[NT][4], const PrimeC (&p)[NT], uint32_t* lds,
+                                         const int2* twl, int c, int t)
 {
     using G = Col4<LOG1>;
 #pragma unroll
@@ -722,14 +700,13 @@ __device__ __forceinline__ void col4_fwd(uint32_t (&x)[NT][4], const uint32_t (&
         }
 #pragma unroll
         for (int i = 0; i < NT; i++) {
-            const uint2* tl = twl + i * (1 << LOG1);
-            by_class(q[i], [&](auto tag) {
+            const int2* tl = twl + i * (1 << LOG1);
+            by_class(p[i].q, [&](auto tag) {
                 constexpr bool W = decltype(tag)::value;
                 if (sh < 0)
-                    ct_stages<1, W>(x[i], q[i], [&](int, int b) { return col4_tw<LOG1>(tl, t, sh, 0, b); });
+                    ct_stages<1, W>(x[i], p[i], [&](int, int b) { return col4_tw<LOG1>(tl, t, sh, 0, b); });
                 else
-                    ct_stages<2, W>(x[i], q[i], [&](int u, int b) { return col4_tw<LOG1>(tl, t, sh, u, b); });
-                if (j == G::NR - 1) ct_canon<W>(x[i], q[i]);
+                    ct_stages<2, W>(x[i], p[i], [&](int u, int b) { return col4_tw<LOG1>(tl, t, sh, u, b); });
             });
         }
         if (j < G::NR - 1) {
@@ -746,8 +723,8 @@ __device__ __forceinline__ void col4_fwd(uint32_t (&x)[NT][4], const uint32_t (&
 // gs_stages with FOLD).  lds: one buffer of Col4::WORDS words; twl: the
 // staged inverse twiddles.
 template <int LOG1, bool W>
-__device__ __forceinline__ void col4_inv(uint32_t (&x)[4], uint32_t q, uint32_t* lds, const uint2* twl, int c, int t,
-                                         uint4 cst)
+__device__ __forceinline__ void col4_inv(uint32_t (&x)[4], const PrimeC& p, uint32_t* lds, const int2* twl, int c, int t,
+                                         int4 cst)
 {
     using G = Col4<LOG1>;
 #pragma unroll
@@ -761,11 +738,11 @@ __device__ __forceinline__ void col4_inv(uint32_t (&x)[4], uint32_t q, uint32_t*
         const bool last = j == G::NR - 1;
         auto tw = [&](int u, int b) { return col4_tw<LOG1>(twl, t, sh, u, b); };
         if (sh < 0) {
-            gs_stages<1, W, false>(x, q, [&](int, int b) { return tw(0, b); });
+            gs_stages<1, W, false>(x, p, [&](int, int b) { return tw(0, b); });
         } else if (last) {
-            gs_stages<2, W, true>(x, q, tw, cst);
+            gs_stages<2, W, true>(x, p, tw, cst);
         } else {
-            gs_stages<2, W, false>(x, q, tw);
+            gs_stages<2, W, false>(x, p, tw);
         }
         if (!last) {
 #pragma unroll
@@ -790,17 +767,18 @@ __global__ void __launch_bounds__(NTT_THREADS) k_inv_cols4(NttTables T, MS ms, L
     const Ld ld = ld0.at(blockIdx.z);
     const St st = st0.at(blockIdx.z);
     __shared__ uint32_t lds[G::WORDS];
-    __shared__ uint2 twl[1 << LOG1];
-    const PrimeC pc{I.q, I.qinv};
+    __shared__ int2 twl[1 << LOG1];
+    const PrimeC pc = I.pc;
     const int c = threadIdx.x % G::C, t = threadIdx.x / G::C;
     const int tile = col4_tile<LOG1>(T.xcd_pair), col = tile * G::C + c;
     uint32_t x[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) x[k] = ld.load(M, limb, (4 * t + k) * ROW + col, pc);
-    const uint4 cst = st.final_const(M, limb);
-    const uint2* const tws[1] = {T.tw + ((size_t)I.pid << T.log_n)};
-    col4_stage_twiddles<LOG1, 1>(twl, tws);
-    by_class(I.q, [&](auto tag) { col4_inv<LOG1, decltype(tag)::value>(x, I.q, lds, twl, c, t, cst); });
+    const int4 cst = st.final_const(M, limb);
+    const int32_t* const tws[1] = {T.tw + ((size_t)I.pid << T.log_n)};
+    const PrimeC pcs[1] = {pc};
+    col4_stage_twiddles<LOG1, 1>(twl, tws, pcs);
+    by_class(pc.q, [&](auto tag) { col4_inv<LOG1, decltype(tag)::value>(x, pc, lds, twl, c, t, cst); });
     if constexpr (St::kTileThread) {
         st.template storev<4>(M, limb, tile * G::TILE + threadIdx.x * 4, x, pc);
     } else {
@@ -824,12 +802,11 @@ __global__ void __launch_bounds__(CT) k_inv_cols(NttTables T, MS ms, Ld ld0, St 
     using G = ColGeom<LOG1, CT>;
     __shared__ uint32_t lds[G::LDS];
     const int limb = blockIdx.y, pid = M.pid[limb];
-    const uint32_t q = T.mods[pid];
-    const PrimeC pc{q, T.qinvs[pid]};
-    const uint2* tw = T.tw + ((size_t)pid << T.log_n);
+    const PrimeC pc = T.prime(pid);
+    const TwTable tw{T.tw + ((size_t)pid << T.log_n), pc.q};
     const int c = threadIdx.x % G::C, r = threadIdx.x / G::C;
     const int col = col_tile<LOG1, CT>(T.xcd_pair) * G::C + c;
-    const uint4 cst = st.final_const(M, limb);
+    const int4 cst = st.final_const(M, limb);
     uint32_t x[16];
     if constexpr (G::NS2 > 0) {
 #pragma unroll
@@ -838,10 +815,10 @@ __global__ void __launch_bounds__(CT) k_inv_cols(NttTables T, MS ms, Ld ld0, St 
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = ld.load(M, limb, (r + G::R * k) * ROW + col, pc);
     }
-    by_class(q, [&](auto tag) {
+    by_class(pc.q, [&](auto tag) {
         constexpr bool W = decltype(tag)::value;
         if constexpr (G::NS2 > 0) {
-            gs_stages<G::NS2, W, false>(x, q, [&](int u, int b) {
+            gs_stages<G::NS2, W, false>(x, pc, [&](int u, int b) {
                 return tw[(1 << (4 + u)) + (r << (4 - G::NS2 + u)) + b];
             });
 #pragma unroll
@@ -850,7 +827,7 @@ __global__ void __launch_bounds__(CT) k_inv_cols(NttTables T, MS ms, Ld ld0, St 
 #pragma unroll
             for (int k = 0; k < 16; k++) x[k] = lds[col_lds<G::C>(r + G::R * k, c)];
         }
-        gs_stages<4, W, true>(x, q, [&](int u, int b) { return tw[(1 << u) + b]; }, cst);
+        gs_stages<4, W, true>(x, pc, [&](int u, int b) { return tw[(1 << u) + b]; }, cst);
     });
     if constexpr (St::kTileThread) {
         // internal layout shared with the next column pass: thread tid of
