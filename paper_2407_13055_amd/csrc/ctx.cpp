@@ -14,7 +14,7 @@ namespace ckks {
 namespace {
 
 // --- host modular arithmetic (moduli < 2^32) ---
-inline uint64_t mm(uint64_t a, uint64_t b, uint64_t m) { return (uint64_t)((unsigned __int128)a * b % m); }
+inline uint64_t mm(uint64_t a, uint64_t b, uint64_t m) { return a * b % m; }  // a, b < 2^32
 
 uint64_t pw(uint64_t a, uint64_t e, uint64_t m)
 {
@@ -64,13 +64,6 @@ uint32_t brev(uint32_t x, int bits)
     uint32_t r = 0;
     for (int i = 0; i < bits; i++, x >>= 1) r = (r << 1) | (x & 1);
     return r;
-}
-
-uint32_t inv32(uint32_t q)  // q^-1 mod 2^32 (q odd), Newton iteration
-{
-    uint32_t x = q;
-    for (int i = 0; i < 5; i++) x *= 2 - q * x;
-    return x;
 }
 
 // twisted Montgomery pair of constant w mod q
@@ -177,7 +170,7 @@ int build_ctx(const ckks_params* p, const int32_t* win_start, const int32_t* win
     std::vector<int2> dn_pinv(nq), rs_qinv((size_t)(nq + 1) * nq, make_int2(0, 0));
     std::vector<int2> rs_fin((size_t)(nq + 1) * nq, make_int2(0, 0));
     std::vector<int32_t> rs_mlast((size_t)nq * np), rs_pr(nq);
-    std::vector<int32_t> dn_mat((size_t)nq * np);
+    std::vector<int32_t> dn_mat((size_t)nq * np), rs_mat(nq);
     std::vector<uint32_t> p_mod_q(nq);
     std::vector<uint2> r1(P);
 
@@ -205,6 +198,13 @@ int build_ctx(const ckks_params* p, const int32_t* win_start, const int32_t* win
         w1[i] = pi[N / 2];
         ninv[i] = fold_pair(inv((uint64_t)N, q), w1[i], q);
     }
+    c->prime_mod.resize((size_t)P * P);
+    c->prime_inv.resize((size_t)P * P);
+    for (int i = 0; i < P; i++)
+        for (int k = 0; k < P; k++) {
+            c->prime_mod[(size_t)i * P + k] = (uint32_t)(c->mod[i] % c->mod[k]);
+            c->prime_inv[(size_t)i * P + k] = i == k ? 0u : (uint32_t)inv(c->mod[i], c->mod[k]);
+        }
     const auto R = [&](int i) { return (1ull << 32) % c->mod[i]; };  // 2^32 mod prime i
 
     // ModUp constants per level and digit (prime ids lo..hi-1 of key digit jk)
@@ -263,6 +263,7 @@ int build_ctx(const ckks_params* p, const int32_t* win_start, const int32_t* win
             rs_mlast[(size_t)i * np + k] = centred(mm(mm(ph, inv(pp, q), q), R(i), q), q);
         }
         rs_pr[i] = centred(mm(pp, rinv_q, q), q);
+        rs_mat[i] = centred(R(i), q);
         p_mod_q[i] = (uint32_t)pp;
         rinv[i] = tw_pair(rinv_q, q, qinvs[i]);
         p_r2[i] = tw_pair(mm(pp, mm(rinv_q, rinv_q, q), q), q, qinvs[i]);
@@ -369,7 +370,7 @@ int build_ctx(const ckks_params* p, const int32_t* win_start, const int32_t* win
     if (rr2_c.empty()) rr2_c.push_back(make_int4(0, 0, 0, 0));
     if (rr2_mat.empty()) rr2_mat.push_back(0);
     if (rr2_fin.empty()) rr2_fin.push_back(make_int2(0, 0));
-    for (std::vector<int32_t>* m : {&up_mat, &dn_mat, &rs_mlast, &rr_mat, &rr2_mat}) m->resize(m->size() + BCONV_MAT_PAD, 0);
+    for (std::vector<int32_t>* m : {&up_mat, &dn_mat, &rs_mlast, &rs_mat, &rr_mat, &rr2_mat}) m->resize(m->size() + BCONV_MAT_PAD, 0);
     std::vector<int32_t> lv_tab(4 * (MAX_PRIMES + 1), 0);
     for (int l = 0; l <= MAX_PRIMES; l++) {
         const bool ok = c->windowed && l >= 1 && l <= nq && c->has_level(l);
@@ -405,6 +406,7 @@ int build_ctx(const ckks_params* p, const int32_t* win_start, const int32_t* win
         {(void**)&c->rs_qinv, rs_qinv.data(), rs_qinv.size() * 8},
         {(void**)&c->rs_mlast, rs_mlast.data(), rs_mlast.size() * 4},
         {(void**)&c->rs_pr, rs_pr.data(), rs_pr.size() * 4},
+        {(void**)&c->rs_mat, rs_mat.data(), rs_mat.size() * 4},
         {(void**)&c->rs_fin, rs_fin.data(), rs_fin.size() * 8},
         {(void**)&c->rr_c, rr_c.data(), rr_c.size() * 16},
         {(void**)&c->rr_mat, rr_mat.data(), rr_mat.size() * 4},
@@ -450,26 +452,34 @@ void free_ctx(Ctx* c)
     delete c;
 }
 
-// Constants of the stand-alone base conversion (the values the device set-up
-// kernel computes): cs[s] = twisted [Shat_s^-1]_{q_s}; ms[t n_in + s] =
-// centred [Shat_s 2^32]_{q_t}.
+// Constants of the stand-alone base conversion: cs[s] = twisted
+// [Shat_s^-1]_{q_s}; ms[t n_in + s] = centred [Shat_s 2^32]_{q_t}.  From the
+// context's residues and inverses of its primes modulo each other, a target
+// takes 2 n_in + 1 products: Shat_s is the whole product times s^-1.
 void bconv_consts(const Ctx& c, const int32_t* in_ids, int n_in, const int32_t* out_ids, int n_out, uint2* cs,
                   int32_t* ms)
 {
-    for (int s = 0; s < n_in; s++) {
-        const uint64_t qs = c.mod[in_ids[s]];
-        uint64_t prod = 1;
+    const int P = c.n_primes;
+    for (int s = 0; s < n_in && cs; s++) {
+        const int i = in_ids[s];
+        const uint64_t qs = c.mod[i];
+        uint64_t v = 1;
         for (int r = 0; r < n_in; r++)
-            if (r != s) prod = mm(prod, c.mod[in_ids[r]] % qs, qs);
-        cs[s] = tw_pair(inv(prod, qs), qs, inv32((uint32_t)qs));
+            if (r != s) v = mm(v, c.prime_inv[(size_t)in_ids[r] * P + i], qs);
+        cs[s] = tw_pair(v, qs, inv32((uint32_t)qs));
     }
     for (int t = 0; t < n_out; t++) {
-        const uint64_t qt = c.mod[out_ids[t]];
+        const int o = out_ids[t];
+        const uint64_t qt = c.mod[o];
+        uint64_t v = (1ull << 32) % qt;
+        int own = -1;  // the input prime that is the target itself: every other Shat_s is 0 modulo it
+        for (int r = 0; r < n_in; r++) {
+            if (in_ids[r] == o) own = r;
+            else v = mm(v, c.prime_mod[(size_t)in_ids[r] * P + o], qt);
+        }
         for (int s = 0; s < n_in; s++) {
-            uint64_t prod = 1;
-            for (int r = 0; r < n_in; r++)
-                if (r != s) prod = mm(prod, c.mod[in_ids[r]] % qt, qt);
-            ms[t * n_in + s] = centred(mm(prod, (1ull << 32) % qt, qt), qt);
+            const uint64_t m = own < 0 ? mm(v, c.prime_inv[(size_t)in_ids[s] * P + o], qt) : (s == own ? v : 0);
+            ms[t * n_in + s] = centred(m, qt);
         }
     }
 }

@@ -117,6 +117,7 @@ struct Ctx {
     int log_n = 0, n = 0;
     int n_q = 0, n_p = 0, dnum = 0, n_primes = 0;
     uint64_t mod[MAX_PRIMES] = {};  // host copy: q_0..q_{n_q-1}, p_0..p_{n_p-1}
+    std::vector<uint32_t> prime_mod, prime_inv;  // host, [n_primes][n_primes]: prime i and its inverse modulo prime k
 
     void* dev_block = nullptr;  // one allocation holding every table below
     size_t dev_bytes = 0;
@@ -143,6 +144,7 @@ struct Ctx {
     int2* rs_qinv = nullptr;       // [n_q+1][n_q] [q_{l-1}^-1]_{q_i}
     int32_t* rs_mlast = nullptr;    // [n_q][n_p] centred [Phat_k P^-1 R]_{q_i}   (q_i the dropped prime)
     int32_t* rs_pr = nullptr;       // [n_q] centred [P R^-1]_{q_i}
+    int32_t* rs_mat = nullptr;      // [n_q] centred [R]_{q_i} (conversion of one dropped prime)
     int2* rs_fin = nullptr;        // [n_q+1][n_q] [P^-1 q_{l-1}^-1 R^2]_{q_i}
     // merged ModDown + rational rescaling (windowed contexts), S = P u D the
     // dropped primes, A the added ones, per level:
@@ -225,6 +227,13 @@ struct Ctx {
         return d;
     }
 };
+
+inline uint32_t inv32(uint32_t q)  // q^-1 mod 2^32 (q odd), Newton iteration
+{
+    uint32_t x = q;
+    for (int i = 0; i < 5; i++) x *= 2 - q * x;
+    return x;
+}
 
 // error reporting (thread-local message, see ckks_last_error)
 int set_error(int code, const std::string& msg);
@@ -348,7 +357,7 @@ int launch_rescale_rational_window(const Ctx& c, int level, const uint32_t* ct, 
 int launch_rescale_rational(const Ctx& c, const uint32_t* ct, int n_in, const int32_t* in_ids, int n_out,
                             const int32_t* out_ids, uint32_t* out, void* ws, hipStream_t s);
 size_t rescale_rational_ws_bytes(const Ctx& c, int n_in, int n_out);
-// host copy of the stand-alone base conversion's constants (ctx.cpp)
+// constants of the stand-alone base conversion (ctx.cpp); cs may be null
 void bconv_consts(const Ctx& c, const int32_t* in_ids, int n_in, const int32_t* out_ids, int n_out, uint2* cs,
                   int32_t* ms);
 

@@ -1192,109 +1192,77 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult_sum(NttTables Tf, NttTa
 }
 
 // ---------------------------------------------------------------------------
-// stand-alone base conversion (coefficient domain)
+// stand-alone base conversion (coefficient domain), one launch: a thread
+// holds BC_VEC coefficients, forms the centred products of the input rows
+// (a multiplication by [Shat_s^-1]_s and the lift) as they arrive, and adds
+// them to BC_TG targets' int64 sums with the range fixes of Sec. 4.2 (|y_s| <=
+// 2^30, |M_s| < t/2: after 8 products, then every 4), one signed Montgomery
+// reduction each.  The constants come by value (a kernel argument holds 512
+// matrix entries: 8 inputs to 64 targets, 64 inputs to 8; a larger conversion
+// is several launches), so nothing is set up on the device.  Bound by the
+// launch and the load latency; 8 targets of 2 coefficients keep 32 sum
+// registers and the most work-groups that the products' recomputation per
+// target group is worth.
 // ---------------------------------------------------------------------------
-// BConv matrix multiplication with lazy reduction (Sec. 4.2): centred inputs
-// y_s (|y_s| < 2^30) times centred constants M_s (|M_s| < t/2) accumulate in
-// int64; after 8 products and then after every 4 more, add or subtract
-// 2^32 t to stay in [-2^31 t, 2^31 t); one signed Montgomery reduction at the
-// end.  The reduction's 2^-32 is absorbed by the constants.
-__device__ __forceinline__ uint32_t bconv_point(const int32_t* y, size_t stride, int n_in, const int32_t* m,
-                                                uint32_t t, uint32_t tinv)
-{
-    const int64_t t31 = (int64_t)t << 31, t32 = (int64_t)t << 32;
-    int64_t acc = 0;
-    int s = 0;
-    for (; s < n_in && s < 8; s++) acc += (int64_t)y[s * stride] * m[s];
-    while (s < n_in) {
-        acc = acc >= t31 ? acc - t32 : (acc < -t31 ? acc + t32 : acc);
-        for (int e = 0; e < 4 && s < n_in; e++, s++) acc += (int64_t)y[s * stride] * m[s];
-    }
-    acc = acc >= t31 ? acc - t32 : (acc < -t31 ? acc + t32 : acc);
-    return canon_signed(smr64(acc, t, tinv), t);
-}
-
-__device__ uint64_t dev_mulmod(uint64_t a, uint64_t b, uint64_t m) { return (a % m) * (b % m) % m; }
-__device__ uint64_t dev_powmod(uint64_t a, uint64_t e, uint64_t m)
-{
-    uint64_t r = 1;
-    a %= m;
-    while (e) {
-        if (e & 1) r = dev_mulmod(r, a, m);
-        a = dev_mulmod(a, a, m);
-        e >>= 1;
-    }
-    return r;
-}
-
-struct BconvIds {
-    int8_t in[MAX_PRIMES];
-    int8_t out[MAX_PRIMES];
-    int n_in, n_out;
+constexpr int BC_VEC = 2, BC_TG = 8, BC_CONSTS = 512;
+struct BconvArgs {
+    int n_in, n_tg, log_n;
+    uint32_t iq[MAX_PRIMES];        // input primes
+    uint2 ic[MAX_PRIMES];           // [Shat_s^-1]_s twisted
+    uint32_t tq[MAX_PRIMES], tqinv[MAX_PRIMES];  // targets
+    int32_t m[BC_CONSTS];           // [n_tg][n_in] centred [Shat_s 2^32]_t
 };
+static_assert(sizeof(BconvArgs) + 16 <= 4096, "the constants must fit a kernel argument");
 
-// constants: ws_c[s] = [Shat_s^-1]_s twisted; ws_m[t * n_in + s] = centred [Shat_s * 2^32]_t
-// constants computed on the host, written to the workspace by one small
-// launch (no host-to-device copy, so the call stays capture-safe)
-constexpr int BCONV_FILL_MAX = 512;
-struct BconvFill {
-    int n_c, n_m;
-    uint2 c[MAX_PRIMES];
-    int32_t m[BCONV_FILL_MAX];
-};
-__global__ void k_bconv_fill(BconvFill F, uint2* ws_c, int32_t* ws_m)
+__global__ void __launch_bounds__(256) k_bconv(BconvArgs A, const uint32_t* in, uint32_t* out)
 {
-    for (int i = threadIdx.x; i < F.n_m; i += blockDim.x) ws_m[i] = F.m[i];
-    for (int i = threadIdx.x; i < F.n_c; i += blockDim.x) ws_c[i] = F.c[i];
-}
-
-__global__ void k_bconv_setup(const uint32_t* mods, const uint32_t* qinvs, BconvIds ids, uint2* ws_c, int32_t* ws_m)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;  // one thread per (target or -1 = inputs)
-    if (t > ids.n_out) return;
-    if (t == ids.n_out) {
-        for (int s = 0; s < ids.n_in; s++) {
-            const uint64_t qs = mods[ids.in[s]];
-            uint64_t prod = 1;
-            for (int r = 0; r < ids.n_in; r++)
-                if (r != s) prod = dev_mulmod(prod, mods[ids.in[r]], qs);
-            const uint64_t inv = dev_powmod(prod, qs - 2, qs);
-            const uint32_t W = (uint32_t)((inv << 32) % qs);
-            ws_c[s] = make_uint2(W, W * qinvs[ids.in[s]]);
+    constexpr int CH = 4;  // input rows in flight
+    const size_t n = (size_t)1 << A.log_n;
+    const size_t j = ((size_t)blockIdx.x * 256 + threadIdx.x) * BC_VEC;  // exact grid
+    const int t0 = blockIdx.y * BC_TG;
+    int64_t acc[BC_TG][BC_VEC];
+#pragma unroll
+    for (int g = 0; g < BC_TG; g++)
+#pragma unroll
+        for (int k = 0; k < BC_VEC; k++) acc[g][k] = 0;
+    for (int s0 = 0; s0 < A.n_in; s0 += CH) {
+        uint2 v[CH];
+#pragma unroll
+        for (int i = 0; i < CH; i++)
+            v[i] = *reinterpret_cast<const uint2*>(in + (size_t)min(s0 + i, A.n_in - 1) * n + j);
+        if (s0 >= 8) {
+#pragma unroll
+            for (int g = 0; g < BC_TG; g++) {
+                const uint32_t q = A.tq[min(t0 + g, A.n_tg - 1)];
+#pragma unroll
+                for (int k = 0; k < BC_VEC; k++)
+                    acc[g][k] = range_fix(acc[g][k], (int64_t)q << 31, (int64_t)q << 32);
+            }
         }
-        return;
+#pragma unroll
+        for (int i = 0; i < CH; i++) {
+            if (s0 + i >= A.n_in) break;
+            const uint32_t q = A.iq[s0 + i];
+            const uint2 c = A.ic[s0 + i];
+            const int32_t y[BC_VEC] = {lift(mulc(v[i].x, c, q), q), lift(mulc(v[i].y, c, q), q)};
+#pragma unroll
+            for (int g = 0; g < BC_TG; g++) {  // past the last target: the last one again, not stored
+                const int32_t m = A.m[min(t0 + g, A.n_tg - 1) * A.n_in + s0 + i];
+#pragma unroll
+                for (int k = 0; k < BC_VEC; k++) acc[g][k] += (int64_t)y[k] * m;
+            }
+        }
     }
-    const uint64_t qt = mods[ids.out[t]];
-    for (int s = 0; s < ids.n_in; s++) {
-        uint64_t prod = 1;
-        for (int r = 0; r < ids.n_in; r++)
-            if (r != s) prod = dev_mulmod(prod, mods[ids.in[r]], qt);
-        const uint64_t v = (prod << 32) % qt;
-        ws_m[t * ids.n_in + s] = (int32_t)(2 * v < qt ? (int64_t)v : (int64_t)v - (int64_t)qt);
+#pragma unroll
+    for (int g = 0; g < BC_TG; g++) {
+        if (t0 + g >= A.n_tg) break;
+        const uint32_t q = A.tq[t0 + g], qinv = A.tqinv[t0 + g];
+        uint32_t r[BC_VEC];
+#pragma unroll
+        for (int k = 0; k < BC_VEC; k++)
+            r[k] = canon_signed(smr64(range_fix(acc[g][k], (int64_t)q << 31, (int64_t)q << 32), q, qinv), q);
+        *reinterpret_cast<uint2*>(out + (size_t)(t0 + g) * n + j) = make_uint2(r[0], r[1]);
     }
-}
-
-__global__ void k_bconv_lift(const uint32_t* in, const uint32_t* mods, BconvIds ids, const uint2* ws_c, int32_t* y,
-                             int log_n)
-{
-    const size_t n = (size_t)1 << log_n;
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n * ids.n_in) return;
-    const int s = (int)(i >> log_n);
-    const uint32_t q = mods[ids.in[s]];
-    y[i] = lift(mulc(in[i], ws_c[s], q), q);
-}
-
-__global__ void k_bconv_matrix(const int32_t* y, const uint32_t* mods, const uint32_t* qinvs, BconvIds ids,
-                               const int32_t* ws_m, uint32_t* out, int log_n)
-{
-    const size_t n = (size_t)1 << log_n;
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n * ids.n_out) return;
-    const int t = (int)(i >> log_n);
-    const size_t j = i & (n - 1);
-    const int pid = ids.out[t];
-    out[i] = bconv_point(y + j, n, ids.n_in, ws_m + t * ids.n_in, mods[pid], qinvs[pid]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1486,32 +1454,25 @@ size_t bconv_ws_bytes(const Ctx& c, int n_in, int n_out)
 }
 
 int launch_bconv(const Ctx& c, const uint32_t* in, const int32_t* in_ids, int n_in, uint32_t* out,
-                 const int32_t* out_ids, int n_out, void* ws, hipStream_t s)
+                 const int32_t* out_ids, int n_out, void*, hipStream_t s)
 {
-    BconvIds ids{};
-    ids.n_in = n_in;
-    ids.n_out = n_out;
-    for (int i = 0; i < n_in; i++) ids.in[i] = (int8_t)in_ids[i];
-    for (int i = 0; i < n_out; i++) ids.out[i] = (int8_t)out_ids[i];
-    char* w = static_cast<char*>(ws);
-    uint2* ws_c = reinterpret_cast<uint2*>(w);                        // <= 64 entries, 512 B
-    int32_t* ws_m = reinterpret_cast<int32_t*>(w + 1024);              // n_out * n_in <= 3 KiB below 4096
-    int32_t* y = reinterpret_cast<int32_t*>(w + 4096 + (size_t)n_in * n_out * 4);
-    if (n_in * n_out * 4 > 4096 - 1024) ws_m = reinterpret_cast<int32_t*>(w + 4096), y = ws_m + n_in * n_out;
     KTimer tm(c, "bconv", s);
-    if (n_in * n_out <= BCONV_FILL_MAX) {
-        BconvFill F{};
-        F.n_c = n_in, F.n_m = n_in * n_out;
-        bconv_consts(c, in_ids, n_in, out_ids, n_out, F.c, F.m);
-        CKKS_LAUNCH(k_bconv_fill, dim3(1), dim3(256), 0, s, F, ws_c, ws_m);
-    } else {
-        CKKS_LAUNCH(k_bconv_setup, dim3(1), dim3(128), 0, s, c.mods, c.qinvs, ids, ws_c, ws_m);
-    }
     const size_t n = (size_t)1 << c.log_n;
-    CKKS_LAUNCH(k_bconv_lift, dim3((unsigned)((n * n_in + 255) / 256)), dim3(256), 0, s, in, c.mods, ids, ws_c,
-                       y, c.log_n);
-    CKKS_LAUNCH(k_bconv_matrix, dim3((unsigned)((n * n_out + 255) / 256)), dim3(256), 0, s, y, c.mods, c.qinvs,
-                       ids, ws_m, out, c.log_n);
+    const int per = std::min(MAX_PRIMES, BC_CONSTS / n_in);  // targets per launch (n_in <= MAX_PRIMES: 8 or more)
+    BconvArgs A;
+    A.n_in = n_in;
+    A.log_n = c.log_n;
+    for (int i = 0; i < n_in; i++) A.iq[i] = (uint32_t)c.mod[in_ids[i]];
+    for (int t0 = 0; t0 < n_out; t0 += per) {
+        A.n_tg = std::min(per, n_out - t0);
+        bconv_consts(c, in_ids, n_in, out_ids + t0, A.n_tg, t0 ? nullptr : A.ic, A.m);
+        for (int t = 0; t < A.n_tg; t++) {
+            const uint32_t q = (uint32_t)c.mod[out_ids[t0 + t]];
+            A.tq[t] = q, A.tqinv[t] = inv32(q);
+        }
+        CKKS_LAUNCH(k_bconv, dim3((unsigned)(n / (256 * BC_VEC)), (unsigned)((A.n_tg + BC_TG - 1) / BC_TG)), dim3(256), 0,
+                    s, A, in, out + (size_t)t0 * n);
+    }
     return launched("bconv");
 }
 
