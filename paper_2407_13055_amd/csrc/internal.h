@@ -69,7 +69,8 @@ struct KsPlan {             // key switching at one level (and rescale flag)
     MapRef dn_rows;           // ModDown NTT row pass + combine
 };
 struct RsPlan {             // stand-alone rescale at one level
-    MapRef rows, cols, ncols, nrows;
+    MapRef rows, cols, nrows;     // INTT passes of the dropped rows; NTT row pass + combine
+    std::vector<BcRef> bc;        // BConv dropped -> kept primes + NTT column pass
 };
 struct RrPlan {             // stand-alone rational rescaling from a window to the window below
     MapRef rows, cols, nrows;     // INTT passes of the dropped rows; NTT row pass + combine

@@ -152,25 +152,6 @@ struct LdOwn {
     }
 };
 
-// a lifted (centred) limb of another prime, stored in the tile-thread layout
-// (rescale); |t| <= 2^30, a forward value of either class as it is
-struct LdCentred {
-    static constexpr bool kTileThread = true;
-    const int32_t* t;
-    int log_n;
-    size_t step = 0;
-    __device__ LdCentred at(int i) const
-    {
-        LdCentred r = *this;
-        r.t += (size_t)i * step;
-        return r;
-    }
-    __device__ void load16(const LaunchMap& M, int l, int j, PrimeC, uint32_t (&x)[16]) const
-    {
-        load16_u32(reinterpret_cast<const uint32_t*>(t) + ((size_t)M.in_off[l] << log_n) + j, x);
-    }
-};
-
 // ---------------------------------------------------------------------------
 // storers
 // ---------------------------------------------------------------------------
@@ -488,6 +469,34 @@ __global__ void __launch_bounds__(CT) k_bconv_ntt_cols(NttTables T, BS bs, const
     }
 }
 
+// The sums of one target to forward values of its column pass; a fused rescale
+// adds tl times mp first.  A sum is at most t 2^32 (8 products, or t 2^31 after
+// a fix and 4 more: |y| <= 2^30, |m| < t/2), and the rescaling's product adds
+// less than t 2^29: the reduction leaves |x| < (1 + 1/8 + 1/2) t < 2^31 for a
+// wide prime, a forward value as it is.  A 31-bit prime's forward values end
+// at q, which takes the sum within t 2^31.
+template <bool RS>
+__device__ __forceinline__ void bconv_reduce(const int64_t (&acc)[4], const int32_t (&tl)[RS ? 4 : 1], int64_t mp,
+                                             const PrimeC& p, uint32_t (&x)[4])
+{
+    const int64_t t31 = (int64_t)p.q << 31, t32 = (int64_t)p.q << 32;
+    if (wide_prime(p.q)) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            int64_t a = acc[k];
+            if constexpr (RS) a += (int64_t)tl[k] * mp;
+            x[k] = (uint32_t)smr64(a, p.q, p.qinv);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            int64_t a = acc[k];
+            if constexpr (RS) a = range_fix(a, t31, t32) + (int64_t)tl[k] * mp;
+            x[k] = (uint32_t)smr64(range_fix(a, t31, t32), p.q, p.qinv);
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // BConv + NTT column pass with 4 residues per thread (Col4 geometry; lifted
 // inputs in the 4-residue tile-thread layout of k_inv_cols4).  The group's
@@ -627,27 +636,132 @@ __global__ void __launch_bounds__(NTT_THREADS) k_bconv_ntt_cols4(NttTables T, BS
     for (int i = 0; i < TPW; i++) {
         int64_t mp = 0;
         if constexpr (RS) mp = X.pr[B.pid[first + (i < n_tg ? i : 0)]];
-        // A sum is at most t 2^32 (8 products, or t 2^31 after a fix and 4
-        // more: |y| <= 2^30, |m| < t/2), and the rescaling's product adds less
-        // than t 2^29: the reduction leaves |x| < (1 + 1/8 + 1/2) t < 2^31 for
-        // a wide prime, a forward value as it is.  A 31-bit prime's forward
-        // values end at q, which takes the sum within t 2^31.
-        if (wide_prime(tp[i].q)) {
+        bconv_reduce<RS>(acc[i], tl, mp, tp[i], x[i]);
+    }
+    col4_fwd<LOG1, TPW>(x, tp, lds, twl, c, t);
 #pragma unroll
-            for (int k = 0; k < 4; k++) {
-                int64_t a = acc[i][k];
-                if constexpr (RS) a += (int64_t)tl[k] * mp;
-                x[i][k] = (uint32_t)smr64(a, tp[i].q, tp[i].qinv);
-            }
-        } else {
+    for (int i = 0; i < TPW; i++) {
+        if (i >= n_tg) break;
+        uint32_t* dst = out + (size_t)B.out_off[first + i] * n + col;
 #pragma unroll
-            for (int k = 0; k < 4; k++) {
-                int64_t a = acc[i][k];
-                if constexpr (RS) a = range_fix(a, t31[i], t32[i]) + (int64_t)tl[k] * mp;
-                x[i][k] = (uint32_t)smr64(range_fix(a, t31[i], t32[i]), tp[i].q, tp[i].qinv);
+        for (int k = 0; k < 4; k++) dst[(size_t)(4 * t + k) * ROW] = x[i][k];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// INTT column pass, BConv and NTT column pass in one launch, for conversions
+// of a few rows (a rescaling's dropped primes, narrow digits).  All three act
+// on the columns of one tile: a work-group runs its group's input rows through
+// the inverse column pass one after the other, lifts each and adds it to its
+// targets' sums, and goes on as k_bconv_ntt_cols4.  The input rows' passes are
+// repeated by every group of targets; that is what the launch it saves must
+// outweigh (fuse_cols).  Launch limb in_off + s of M is input row s.
+// ---------------------------------------------------------------------------
+template <int LOG1, int TPW, bool RS>
+__global__ void __launch_bounds__(NTT_THREADS) k_inv_bconv_ntt_cols4(NttTables Tf, NttTables Ti, const LaunchMap* Mp,
+                                                                     const BcMap* Bp, const uint32_t* w0,
+                                                                     const int4* fc, const int32_t* mat,
+                                                                     uint32_t* out, BcRescale X)
+{
+    using G = Col4<LOG1>;
+    const LaunchMap& M = *Mp;
+    const BcMap& B = *Bp;
+    const int g = blockIdx.y;  // grid.y = groups
+    const int n_in = B.n_in[g], n_tg = B.n_tg[g], first = B.first[g], l0 = B.in_off[g];
+    __shared__ uint32_t lds[TPW * G::WORDS];
+    __shared__ int2 twl[TPW << LOG1];
+    __shared__ int2 twi[1 << LOG1];
+    const int c = threadIdx.x % G::C, t = threadIdx.x / G::C;
+    const int tile = col4_tile<LOG1>(Tf.xcd_pair), col = tile * G::C + c;
+    const size_t n = (size_t)1 << Tf.log_n;
+    auto load_row = [&](int l, uint32_t (&x)[4]) {
+        const uint32_t* src = w0 + (size_t)M.in_off[l] * n + col;
+#pragma unroll
+        for (int k = 0; k < 4; k++) x[k] = src[(4 * t + k) * ROW];
+    };
+    uint32_t nx[4];
+    load_row(l0, nx);
+
+    PrimeC tp[TPW];
+    const int32_t* tws[TPW];
+    const int32_t* tm[TPW];
+    int64_t t31[TPW], t32[TPW];
+#pragma unroll
+    for (int i = 0; i < TPW; i++) {  // a group's missing targets repeat its first; they are not stored
+        const int k = first + (i < n_tg ? i : 0);
+        const int pid = B.pid[k];
+        tp[i] = Tf.prime(pid);
+        tws[i] = Tf.tw + ((size_t)pid << Tf.log_n);
+        tm[i] = mat + B.mat_off[k];
+        t31[i] = (int64_t)tp[i].q << 31, t32[i] = (int64_t)tp[i].q << 32;
+    }
+    const int ql_pid = RS ? X.level - 1 : 0;
+    const int32_t* mlast = X.mlast + (size_t)ql_pid * X.n_p;
+    PrimeC pl{};
+    int64_t l31 = 0, l32 = 0;
+    if constexpr (RS) pl = Tf.prime(ql_pid), l31 = (int64_t)pl.q << 31, l32 = (int64_t)pl.q << 32;
+
+    int64_t acc[TPW][4], accl[RS ? 4 : 1];
+#pragma unroll
+    for (int i = 0; i < TPW; i++)
+#pragma unroll
+        for (int k = 0; k < 4; k++) acc[i][k] = 0;
+    if constexpr (RS) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) accl[k] = 0;
+    }
+    int32_t tl[RS ? 4 : 1];
+    const int rows = n_in + (RS ? 1 : 0);  // fused rescale: row n_in is e (BcRescale)
+    for (int s = 0; s < rows; s++) {
+        uint32_t x[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) x[k] = nx[k];
+        const int pid = M.pid[l0 + s];
+        const PrimeC pc = Ti.prime(pid);
+        const int4 cst = fc[M.cidx[l0 + s]];
+        const int32_t* const twsi[1] = {Ti.tw + ((size_t)pid << Ti.log_n)};
+        const PrimeC pci[1] = {pc};
+        if (s + 1 < rows) load_row(l0 + s + 1, nx);
+        if (s) __syncthreads();  // the previous row's reads of lds and twi are done
+        else col4_stage_twiddles<LOG1, TPW>(twl, tws, tp);
+        col4_stage_twiddles<LOG1, 1>(twi, twsi, pci);
+        by_class(pc.q, [&](auto tag) { col4_inv<LOG1, decltype(tag)::value>(x, pc, lds, twi, c, t, cst); });
+        int32_t y[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) y[k] = lift(x[k], pc.q);
+        if (RS && s == n_in) {
+            if constexpr (RS) {
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const uint32_t cl = canon_signed(smr64(range_fix(accl[k], l31, l32), pl.q, pl.qinv), pl.q);
+                    const uint32_t ec = y[k] < 0 ? (uint32_t)(y[k] + (int32_t)pl.q) : (uint32_t)y[k];
+                    tl[k] = lift(sub_mod(ec, cl, pl.q), pl.q);
+                }
             }
+            break;
+        }
+        const bool fix = s >= 8 && (s & 3) == 0;
+#pragma unroll
+        for (int i = 0; i < TPW; i++) {
+            const int64_t m = tm[i][s];
+#pragma unroll
+            for (int k = 0; k < 4; k++)
+                acc[i][k] = (fix ? range_fix(acc[i][k], t31[i], t32[i]) : acc[i][k]) + (int64_t)y[k] * m;
+        }
+        if constexpr (RS) {
+            const int64_t m = mlast[s];
+#pragma unroll
+            for (int k = 0; k < 4; k++) accl[k] = (fix ? range_fix(accl[k], l31, l32) : accl[k]) + (int64_t)y[k] * m;
         }
     }
+    uint32_t x[TPW][4];
+#pragma unroll
+    for (int i = 0; i < TPW; i++) {
+        int64_t mp = 0;
+        if constexpr (RS) mp = X.pr[B.pid[first + (i < n_tg ? i : 0)]];
+        bconv_reduce<RS>(acc[i], tl, mp, tp[i], x[i]);
+    }
+    __syncthreads();  // the last row's reads of lds are done
     col4_fwd<LOG1, TPW>(x, tp, lds, twl, c, t);
 #pragma unroll
     for (int i = 0; i < TPW; i++) {
@@ -1327,15 +1441,14 @@ static void inv_rows(const Ctx& c, MS ms, int n, Ld ld, St st, hipStream_t s, in
                            s, tables(c, true), ms, ld, st);
 }
 template <int L1, class MS, class Ld, class St>
-static void inv_cols(const Ctx& c, MS ms, int n, Ld ld, St st, hipStream_t s, int items_n = 1, int ct_force = 0,
-                     bool c4 = false)
+static void inv_cols(const Ctx& c, MS ms, int n, Ld ld, St st, hipStream_t s, int items_n = 1, bool c4 = false)
 {
     if (c4) {  // 4 residues per thread (its BConv consumer must be k_bconv_ntt_cols4)
         CKKS_LAUNCH((k_inv_cols4<L1, MS, Ld, St>), dim3(Col4<L1>::TILES, n, items_n), dim3(NTT_THREADS), 0, s,
                     tables(c, true), ms, ld, st);
         return;
     }
-    const int ct = ct_force ? ct_force : c.col_threads;  // a producer and its BConv consumer must agree
+    const int ct = c.col_threads;  // a producer and its BConv consumer must agree
     if constexpr (L1 >= 5) {
         if (ct == 512) {
             CKKS_LAUNCH((k_inv_cols<L1, MS, Ld, St, 512>), dim3(col_tiles<L1, 512>(), n, items_n), dim3(512), 0, s,
@@ -1362,15 +1475,14 @@ static bool col4(const Ctx& c, int items_n) { return (items_n > 1 ? c.col_ept : 
 
 template <int L1, int TPW, bool RS, class BS>
 static void bconv_ntt(const Ctx& c, BS bs, int groups, int items_n, const int32_t* y, const int32_t* mat,
-                      uint32_t* out, const BcRescale& X, size_t step, const BatchItem* items, hipStream_t s,
-                      int ct_force = 0, bool c4 = false)
+                      uint32_t* out, const BcRescale& X, size_t step, const BatchItem* items, hipStream_t s, bool c4)
 {
     if (c4) {
         CKKS_LAUNCH((k_bconv_ntt_cols4<L1, TPW, RS, BS>), dim3(Col4<L1>::TILES, groups, items_n), dim3(NTT_THREADS),
                     0, s, tables(c, false), bs, y, mat, out, X, step, items);
         return;
     }
-    const int ct = ct_force ? ct_force : c.col_threads;
+    const int ct = c.col_threads;
     if constexpr (L1 >= 5) {
         if (ct == 512) {
             CKKS_LAUNCH((k_bconv_ntt_cols<L1, TPW, 0, RS, BS, 512>), dim3(col_tiles<L1, 512>(), groups, items_n),
@@ -1394,25 +1506,70 @@ static void bconv_ntt(const Ctx& c, BS bs, int groups, int items_n, const int32_
 template <bool RS, class BS>
 static int launch_bconv_ntt(const Ctx& c, int tpw, BS bs, int groups, int items_n, const int32_t* y,
                             const int32_t* mat, uint32_t* out, const BcRescale& X, size_t step,
-                            const BatchItem* items, hipStream_t s, int ct_force = 0, bool c4 = false)
+                            const BatchItem* items, hipStream_t s, bool c4)
 {
     const int log1 = c.log_n - ROW_LOG;
-    if (tpw == 1) { CKKS_DISPATCH_LOG1(log1, (bconv_ntt<L1, 1, RS>(c, bs, groups, items_n, y, mat, out, X, step, items, s, ct_force, c4))); }
-    else if (tpw == 2) { CKKS_DISPATCH_LOG1(log1, (bconv_ntt<L1, 2, RS>(c, bs, groups, items_n, y, mat, out, X, step, items, s, ct_force, c4))); }
-    else { CKKS_DISPATCH_LOG1(log1, (bconv_ntt<L1, 4, RS>(c, bs, groups, items_n, y, mat, out, X, step, items, s, ct_force, c4))); }
+    if (tpw == 1) { CKKS_DISPATCH_LOG1(log1, (bconv_ntt<L1, 1, RS>(c, bs, groups, items_n, y, mat, out, X, step, items, s, c4))); }
+    else if (tpw == 2) { CKKS_DISPATCH_LOG1(log1, (bconv_ntt<L1, 2, RS>(c, bs, groups, items_n, y, mat, out, X, step, items, s, c4))); }
+    else { CKKS_DISPATCH_LOG1(log1, (bconv_ntt<L1, 4, RS>(c, bs, groups, items_n, y, mat, out, X, step, items, s, c4))); }
     return launched("bconv+ntt cols");
 }
 
 template <bool RS>
 static int launch_bconv_list(const Ctx& c, int tpw, const std::vector<BcRef>& bs, const int32_t* y,
-                             const int32_t* mat, uint32_t* out, const BcRescale& X, hipStream_t s, int ct_force = 0,
-                             bool c4 = false)
+                             const int32_t* mat, uint32_t* out, const BcRescale& X, hipStream_t s, bool c4)
 {
     for (const BcRef& B : bs)
-        if (int e = launch_bconv_ntt<RS>(c, tpw, BcByPtr{B.dev}, B.groups, 1, y, mat, out, X, 0, nullptr, s, ct_force,
-                                         c4))
+        if (int e = launch_bconv_ntt<RS>(c, tpw, BcByPtr{B.dev}, B.groups, 1, y, mat, out, X, 0, nullptr, s, c4))
             return e;
     return 0;
+}
+
+// Conversions that run as one launch from the INTT row pass to the NTT column
+// pass (k_inv_bconv_ntt_cols4) instead of two.  It saves a launch (about 3 us
+// of a dependent sequence, as much host time) and costs the input rows' column
+// passes again for every group of targets and a chain of n_in passes in every
+// work-group.  Measured, HMult + rescale, two launches -> one: one-prime digits
+// 28.6 -> 23.5 us at N = 2^12 and 32.5 -> 29.4 at 2^16 (3 limbs), two-prime
+// digits 28.6 -> 26.3 and 49.6 -> 49.9 (8 limbs), four-prime digits 28.5 ->
+// 28.8 and 45.3 -> 50.2: the line lies at two primes per digit and 2^20
+// repeated residues.  Rescalings convert 1 to 3 dropped primes to one window:
+// rational 20.1 -> 18.6 us with 3 at N = 2^16, single 30.5 -> 28.2 at 24 limbs
+// and 17.6 -> 15.5 at 8 limbs of N = 2^12.
+constexpr int FUSE_MAX_IN = 2, RR_FUSE_MAX_IN = 3;
+constexpr size_t FUSE_MAX_REPEAT = (size_t)1 << 20;
+// targets per work-group of the rescalings' conversions: 1 repeats the input
+// rows' passes twice as often, 4 leaves 5 work-groups per CU (rational
+// rescaling 18.6 us with 2, 20.2 with 4)
+constexpr int RS_TPW = 2;
+static bool fuse_cols(const Ctx& c, int n_in, int groups)
+{
+    return n_in <= FUSE_MAX_IN && (((size_t)n_in * groups) << c.log_n) <= FUSE_MAX_REPEAT;
+}
+static bool fuse_list(const Ctx& c, const std::vector<BcRef>& bs)
+{
+    int n_in = 0, groups = 0;
+    for (const BcRef& B : bs) n_in = std::max(n_in, B.n_in_max), groups += B.groups;
+    return fuse_cols(c, n_in, groups);
+}
+
+template <bool RS>
+static int launch_inv_bconv_list(const Ctx& c, int tpw, const MapRef& cols, const std::vector<BcRef>& bs,
+                                 const uint32_t* w0, const int4* fc, const int32_t* mat, uint32_t* out,
+                                 const BcRescale& X, hipStream_t s)
+{
+    const int log1 = c.log_n - ROW_LOG;
+    for (const BcRef& B : bs) {
+#define CKKS_FUSED(TPW)                                                                                          \
+    CKKS_DISPATCH_LOG1(log1, CKKS_LAUNCH((k_inv_bconv_ntt_cols4<L1, TPW, RS>), dim3(Col4<L1>::TILES, B.groups),    \
+                                         dim3(NTT_THREADS), 0, s, tables(c, false), tables(c, true), cols.dev,   \
+                                         B.dev, w0, fc, mat, out, X))
+        if (tpw == 1) { CKKS_FUSED(1) }
+        else if (tpw == 2) { CKKS_FUSED(2) }
+        else { CKKS_FUSED(4) }
+#undef CKKS_FUSED
+    }
+    return launched("intt cols + bconv + ntt cols");
 }
 
 // ---------------------------------------------------------------------------
@@ -1608,18 +1765,24 @@ static int modup_phase(const KsRun& R, Own own, const KsIn& in, size_t s0, size_
         }
         if (int e = launched("modup intt rows")) return e;
     }
+    const int4* up_c = own == Own::Tensor ? c.up_c_r : c.up_c;
+    if (!R.D && c4 && fuse_list(c, R.P->up_bc)) {
+        KTimer t(c, "modup_cols", s);
+        return launch_inv_bconv_list<false>(c, c.tpw_up, R.P->up_cols, R.P->up_bc, R.w0, up_c, c.up_mat, R.w2,
+                                            BcRescale{}, s);
+    }
     {
         LdPlain ld{R.w0, c.log_n, R.wst};
-        StLift st{R.w1, own == Own::Tensor ? c.up_c_r : c.up_c, c.log_n, R.wst};
+        StLift st{R.w1, up_c, c.log_n, R.wst};
         KTimer t(c, "modup_intt_cols", s);
-        KS_MAP(R, up_cols, CKKS_DISPATCH_LOG1(log1, (inv_cols<L1>(c, ms, R.g.up_cols, ld, st, s, R.zn, 0, c4))));
+        KS_MAP(R, up_cols, CKKS_DISPATCH_LOG1(log1, (inv_cols<L1>(c, ms, R.g.up_cols, ld, st, s, R.zn, c4))));
         if (int e = launched("modup intt cols")) return e;
     }
     {
         KTimer t(c, "modup_bconv_ntt_cols", s);
         int e;
-        if (R.D) e = launch_bconv_ntt<false>(c, c.tpw_up, BcDir{R.D->up_bc, R.items, R.lo, R.hi, R.nk, R.ns}, R.g.up_bc, R.zn, R.w1, c.up_mat, R.w2, BcRescale{}, R.wst, R.items, s, 0, c4);
-        else e = launch_bconv_list<false>(c, c.tpw_up, R.P->up_bc, R.w1, c.up_mat, R.w2, BcRescale{}, s, 0, c4);
+        if (R.D) e = launch_bconv_ntt<false>(c, c.tpw_up, BcDir{R.D->up_bc, R.items, R.lo, R.hi, R.nk, R.ns}, R.g.up_bc, R.zn, R.w1, c.up_mat, R.w2, BcRescale{}, R.wst, R.items, s, c4);
+        else e = launch_bconv_list<false>(c, c.tpw_up, R.P->up_bc, R.w1, c.up_mat, R.w2, BcRescale{}, s, c4);
         if (e) return e;
     }
     return 0;
@@ -1634,28 +1797,36 @@ static int moddown_phase(const KsRun& R, int level, bool rescale, uint32_t* out0
     const int log1 = c.log_n - ROW_LOG;
     const bool rr = rescale && c.windowed;  // merged ModDown + rational rescaling
     const bool c4 = col4(c, R.zn);
+    const int4* dn_c = rr ? c.rr_c : c.dn_c;
+    const int32_t* dn_mat = rr ? c.rr_mat : c.dn_mat;
+    const BcRescale X{c.rs_mlast, c.rs_pr, c.n_p, level};
+    if (!R.D && c4 && fuse_list(c, R.P->dn_bc)) {
+        KTimer t(c, "moddown_cols", s);
+        if (int e = rescale && !rr
+                        ? launch_inv_bconv_list<true>(c, c.tpw_dn, R.P->dn_cols, R.P->dn_bc, R.w0, dn_c, dn_mat, R.w2, X, s)
+                        : launch_inv_bconv_list<false>(c, c.tpw_dn, R.P->dn_cols, R.P->dn_bc, R.w0, dn_c, dn_mat, R.w2, X, s))
+            return e;
+    } else {
     {
         LdPlain ld{R.w0, c.log_n, R.wst};
-        StLift st{R.w1, rr ? c.rr_c : c.dn_c, c.log_n, R.wst};
+        StLift st{R.w1, dn_c, c.log_n, R.wst};
         KTimer t(c, "moddown_intt_cols", s);
-        KS_MAP(R, dn_cols, CKKS_DISPATCH_LOG1(log1, (inv_cols<L1>(c, ms, R.g.dn_cols, ld, st, s, R.zn, 0, c4))));
+        KS_MAP(R, dn_cols, CKKS_DISPATCH_LOG1(log1, (inv_cols<L1>(c, ms, R.g.dn_cols, ld, st, s, R.zn, c4))));
         if (int e = launched("moddown intt cols")) return e;
     }
     {
         KTimer t(c, "moddown_bconv_ntt_cols", s);
-        const BcRescale X{c.rs_mlast, c.rs_pr, c.n_p, level};
         int e;
         if (R.D) {
             const BcDir bd{R.D->dn_bc, R.items, R.lo, R.hi, R.nk, R.ns};
-            if (rr) e = launch_bconv_ntt<false>(c, c.tpw_dn, bd, R.g.dn_bc, R.zn, R.w1, c.rr_mat, R.w2, X, R.wst, R.items, s, 0, c4);
-            else if (rescale) e = launch_bconv_ntt<true>(c, c.tpw_dn, bd, R.g.dn_bc, R.zn, R.w1, c.dn_mat, R.w2, X, R.wst, R.items, s, 0, c4);
-            else e = launch_bconv_ntt<false>(c, c.tpw_dn, bd, R.g.dn_bc, R.zn, R.w1, c.dn_mat, R.w2, X, R.wst, R.items, s, 0, c4);
+            if (rescale && !rr) e = launch_bconv_ntt<true>(c, c.tpw_dn, bd, R.g.dn_bc, R.zn, R.w1, dn_mat, R.w2, X, R.wst, R.items, s, c4);
+            else e = launch_bconv_ntt<false>(c, c.tpw_dn, bd, R.g.dn_bc, R.zn, R.w1, dn_mat, R.w2, X, R.wst, R.items, s, c4);
         } else {
-            if (rr) e = launch_bconv_list<false>(c, c.tpw_dn, R.P->dn_bc, R.w1, c.rr_mat, R.w2, X, s, 0, c4);
-            else if (rescale) e = launch_bconv_list<true>(c, c.tpw_dn, R.P->dn_bc, R.w1, c.dn_mat, R.w2, X, s, 0, c4);
-            else e = launch_bconv_list<false>(c, c.tpw_dn, R.P->dn_bc, R.w1, c.dn_mat, R.w2, X, s, 0, c4);
+            if (rescale && !rr) e = launch_bconv_list<true>(c, c.tpw_dn, R.P->dn_bc, R.w1, dn_mat, R.w2, X, s, c4);
+            else e = launch_bconv_list<false>(c, c.tpw_dn, R.P->dn_bc, R.w1, dn_mat, R.w2, X, s, c4);
         }
         if (e) return e;
+    }
     }
     {
         LdPlain ld{R.w2, c.log_n, R.wst};
@@ -1867,29 +2038,23 @@ int launch_rescale(const Ctx& c, const uint32_t* in, int level_in, uint32_t* out
     const int log1 = c.log_n - ROW_LOG;
     const RsPlan& P = c.rs_plan[level_in];
     if (!P.rows.dev) return set_error(-5, "no launch plan for this level");
-    uint32_t* W = static_cast<uint32_t*>(ws);
-    uint32_t* w0 = W;                                               // [2] INTT row pass of the last limbs
-    int32_t* w1 = reinterpret_cast<int32_t*>(W + 2 * (size_t)c.n);  // [2] lifted t
-    uint32_t* w2 = W + 4 * (size_t)c.n;                             // [2 (l-1)] NTT column pass of [t]_{q_i}
+    uint32_t* w0 = static_cast<uint32_t*>(ws);  // [2] INTT row pass of the last limbs
+    uint32_t* w2 = w0 + 4 * (size_t)c.n;        // [2 (l-1)] NTT column pass of [t]_{q_i}
     {
         LdPlain ld{in, c.log_n};
         StPlain st{w0, nullptr, c.log_n};
-        { KTimer t(c, "rescale_intt_rows", s); CKKS_DISPATCH_LOG1(log1, (inv_rows<L1>(c, ptr(P.rows), 2, ld, st, s))); }
-        LdPlain ld2{w0, c.log_n};
-        StLift st2{w1, c.ninv, c.log_n};
-        { KTimer t(c, "rescale_intt_cols", s); CKKS_DISPATCH_LOG1(log1, (inv_cols<L1>(c, ptr(P.cols), 2, ld2, st2, s))); }
-        if (int e = launched("rescale intt")) return e;
+        KTimer t(c, "rescale_intt_rows", s);
+        CKKS_DISPATCH_LOG1(log1, (inv_rows<L1>(c, ptr(P.rows), 2, ld, st, s)));
+        if (int e = launched("rescale intt rows")) return e;
     }
     {
-        LdCentred ld{w1, c.log_n};
-        StPlain st{w2, nullptr, c.log_n};
-        KTimer t(c, "rescale_ntt_cols", s);
-        CKKS_DISPATCH_LOG1(log1, (fwd_cols<L1>(c, ptr(P.ncols), P.ncols.n, ld, st, s)));
-        if (int e = launched("rescale ntt cols")) return e;
+        KTimer t(c, "rescale_cols", s);
+        if (int e = launch_inv_bconv_list<false>(c, RS_TPW, P.cols, P.bc, w0, c.ninv, c.rs_mat, w2, BcRescale{}, s))
+            return e;
     }
     {
         LdPlain ld{w2, c.log_n};
-        StCombine st{out, out, in, c.rs_qinv, c.log_n};
+        StCombine st{out, out + (size_t)(level_in - 1) * c.n, in, c.rs_qinv, c.log_n};
         KTimer t(c, "rescale_ntt_rows_combine", s);
         CKKS_DISPATCH_LOG1(log1, (fwd_rows<L1>(c, ptr(P.nrows), P.nrows.n, ld, st, s)));
         if (int e = launched("rescale ntt rows")) return e;
@@ -2082,22 +2247,22 @@ void build_rs_plan(const Ctx& c, Blob& b, int level, RsPlan& P)
     P.rows = add_map(b, M, 2);
     M.in_off[0] = 0, M.in_off[1] = 1;
     P.cols = add_map(b, M, 2);
-    LaunchMap N{};
+    BcBuilder bb{b, RS_TPW, P.bc};
+    int32_t mo[MAX_PRIMES], oo[MAX_PRIMES];
+    int8_t pd[MAX_PRIMES];
+    for (int poly = 0; poly < 2; poly++) {
+        for (int i = 0; i < lo; i++) mo[i] = i, oo[i] = poly * lo + i, pd[i] = (int8_t)i;
+        bb.add(poly, 1, lo, mo, oo, pd);
+    }
+    bb.flush();
+    LaunchMap R{};  // the two polynomials' limbs of a prime are neighbours, as in ModDown's combine
     for (int poly = 0; poly < 2; poly++)
         for (int i = 0; i < lo; i++) {
-            const int l = poly * lo + i;
-            N.in_off[l] = poly;
-            N.out_off[l] = l;
-            N.pid[l] = i;
-        }
-    P.ncols = add_map(b, N, 2 * lo);
-    LaunchMap R{};
-    for (int poly = 0; poly < 2; poly++)
-        for (int i = 0; i < lo; i++) {
-            const int l = poly * lo + i;
-            R.in_off[l] = l;
+            const int l = 2 * i + poly;
+            R.in_off[l] = poly * lo + i;
             R.sub_off[l] = poly * level + i;
-            R.out_off[l] = poly * lo + i;
+            R.out_off[l] = i;
+            R.grp[l] = poly;
             R.pid[l] = i;
             R.cidx[l] = (level * c.n_q + i);
         }
@@ -2126,10 +2291,7 @@ void build_rr_plan(const Ctx& c, Blob& b, int level, RrPlan& P)
     P.rows = add_map(b, M, 2 * nd);
     for (int l = 0; l < 2 * nd; l++) M.in_off[l] = l;
     P.cols = add_map(b, M, 2 * nd);
-    // one target per work-group: a few dropped rows convert to a window's
-    // worth of targets, and the launch needs the work-groups more than the
-    // shared input loads
-    BcBuilder bb{b, 1, P.bc};
+    BcBuilder bb{b, RS_TPW, P.bc};
     int32_t mo[MAX_PRIMES], oo[MAX_PRIMES];
     int8_t pd[MAX_PRIMES];
     for (int poly = 0; poly < 2; poly++) {
@@ -2144,8 +2306,8 @@ void build_rr_plan(const Ctx& c, Blob& b, int level, RrPlan& P)
     LaunchMap R{};
     for (int poly = 0; poly < 2; poly++)
         for (int o = 0; o < below; o++) {
-            const int l = poly * below + o, r = ob + o - wb;
-            R.in_off[l] = l;
+            const int l = 2 * o + poly, r = ob + o - wb;
+            R.in_off[l] = poly * below + o;
             R.sub_off[l] = r >= 0 && r < level ? poly * level + r : -1;
             R.out_off[l] = o;
             R.grp[l] = poly;
@@ -2156,11 +2318,6 @@ void build_rr_plan(const Ctx& c, Blob& b, int level, RrPlan& P)
 }
 
 }  // namespace
-
-// The four-pass rescaling runs a few rows: its column passes use the
-// narrowest tiles (twice the work-groups; applied where N >= 2^15, both
-// the lifting INTT and the BConv that reads its tile layout).
-constexpr int RR_COL_THREADS = 128;
 
 int launch_rescale_rational_window(const Ctx& c, int level, const uint32_t* ct, uint32_t* out, void* ws,
                                    hipStream_t s)
@@ -2179,17 +2336,20 @@ int launch_rescale_rational_window(const Ctx& c, int level, const uint32_t* ct, 
         CKKS_DISPATCH_LOG1(log1, (inv_rows<L1>(c, MapByPtr{P.rows.dev}, P.rows.n, ld, st, s)));
         if (int e = launched("rational rescale intt rows")) return e;
     }
-    {
+    if (nd <= RR_FUSE_MAX_IN) {
+        KTimer t(c, "rr_cols", s);
+        if (int e = launch_inv_bconv_list<false>(c, RS_TPW, P.cols, P.bc, w0, c.rr2_c, c.rr2_mat, w2, BcRescale{}, s))
+            return e;
+    } else {
         LdPlain ld{w0, c.log_n};
         StLift st{w1, c.rr2_c, c.log_n};
-        KTimer t(c, "rr_intt_cols", s);
-        CKKS_DISPATCH_LOG1(log1, (inv_cols<L1>(c, MapByPtr{P.cols.dev}, P.cols.n, ld, st, s, 1, RR_COL_THREADS)));
-        if (int e = launched("rational rescale intt cols")) return e;
-    }
-    {
+        {
+            KTimer t(c, "rr_intt_cols", s);
+            CKKS_DISPATCH_LOG1(log1, (inv_cols<L1>(c, MapByPtr{P.cols.dev}, P.cols.n, ld, st, s, 1, true)));
+            if (int e = launched("rational rescale intt cols")) return e;
+        }
         KTimer t(c, "rr_bconv_ntt_cols", s);
-        if (int e = launch_bconv_list<false>(c, 1, P.bc, w1, c.rr2_mat, w2, BcRescale{}, s, RR_COL_THREADS))
-            return e;
+        if (int e = launch_bconv_list<false>(c, RS_TPW, P.bc, w1, c.rr2_mat, w2, BcRescale{}, s, true)) return e;
     }
     {
         LdPlain ld{w2, c.log_n};
@@ -2250,7 +2410,8 @@ int build_plans(Ctx& c)
         }
     for (int level = 2; level <= c.n_q && !c.windowed; level++) {
         RsPlan& P = c.rs_plan[level];
-        fix(P.rows), fix(P.cols), fix(P.ncols), fix(P.nrows);
+        fix(P.rows), fix(P.cols), fix(P.nrows);
+        for (auto& r : P.bc) rebase(r.dev, base);
     }
     for (int level = 1; level <= c.n_q && c.windowed; level++) {
         RrPlan& P = c.rr_plan[level];

@@ -308,12 +308,8 @@ __global__ void __launch_bounds__(CT) k_fwd_cols(NttTables T, MS ms, Ld ld0, St 
     const int c = threadIdx.x % G::C, r = threadIdx.x / G::C;
     const int col = col_tile<LOG1, CT>(T.xcd_pair) * G::C + c;
     uint32_t x[16];
-    if constexpr (Ld::kTileThread) {
-        ld.load16(M, limb, col_tile<LOG1, CT>(T.xcd_pair) * G::TILE + threadIdx.x * 16, pc, x);
-    } else {
 #pragma unroll
-        for (int k = 0; k < 16; k++) x[k] = ld.load(M, limb, (r + G::R * k) * ROW + col, pc);
-    }
+    for (int k = 0; k < 16; k++) x[k] = ld.load(M, limb, (r + G::R * k) * ROW + col, pc);
     by_class(pc.q, [&](auto tag) {
         constexpr bool W = decltype(tag)::value;
         ct_stages<4, W>(x, pc, [&](int u, int b) { return tw[(1 << u) + b]; });
