@@ -95,16 +95,18 @@ struct LdPlain {
         r.base += (size_t)i * step;
         return r;
     }
-    __device__ uint32_t load(const LaunchMap& M, int l, int j, PrimeC) const
+    template <class LM>
+    __device__ uint32_t load(const LM& M, int l, int j, PrimeC) const
     {
         return base[((size_t)M.in_off[l] << log_n) + j];
     }
-    __device__ void load16(const LaunchMap& M, int l, int j, PrimeC, uint32_t (&x)[16]) const
+    template <class LM>
+    __device__ void load16(const LM& M, int l, int j, PrimeC, uint32_t (&x)[16]) const
     {
         load16_u32(base + ((size_t)M.in_off[l] << log_n) + j, x);
     }
-    template <int E>
-    __device__ void loadv(const LaunchMap& M, int l, int j, PrimeC, uint32_t (&x)[E]) const
+    template <int E, class LM>
+    __device__ void loadv(const LM& M, int l, int j, PrimeC, uint32_t (&x)[E]) const
     {
         loadv_u32<E>(base + ((size_t)M.in_off[l] << log_n) + j, x);
     }
@@ -167,33 +169,36 @@ struct StPlain {
         r.base += (size_t)i * step;
         return r;
     }
-    __device__ void store(const LaunchMap& M, int l, int j, uint32_t v, PrimeC) const
+    template <class LM>
+    __device__ void store(const LM& M, int l, int j, uint32_t v, PrimeC) const
     {
         base[((size_t)M.out_off[l] << log_n) + j] = v;
     }
-    __device__ void store16(const LaunchMap& M, int l, int j, const uint32_t (&x)[16], PrimeC) const
+    template <class LM>
+    __device__ void store16(const LM& M, int l, int j, const uint32_t (&x)[16], PrimeC) const
     {
         store16_u32(base + ((size_t)M.out_off[l] << log_n) + j, x);
     }
-    template <int E>
-    __device__ void storev(const LaunchMap& M, int l, int j, const uint32_t (&x)[E], PrimeC) const
+    template <int E, class LM>
+    __device__ void storev(const LM& M, int l, int j, const uint32_t (&x)[E], PrimeC) const
     {
         storev_u32<E>(base + ((size_t)M.out_off[l] << log_n) + j, x);
     }
     // epilogue operands requested ahead of the pass: none
     struct Pre {};
-    template <int E>
-    __device__ Pre prefetch(const LaunchMap&, int, int) const { return {}; }
+    template <int E, class LM>
+    __device__ Pre prefetch(const LM&, int, int) const { return {}; }
     // canonical residues of forward values (class W)
-    template <int E, bool W>
-    __device__ void store_fwd(const LaunchMap& M, int l, int j, const uint32_t (&x)[E], PrimeC pc, Pre) const
+    template <int E, bool W, class LM>
+    __device__ void store_fwd(const LM& M, int l, int j, const uint32_t (&x)[E], PrimeC pc, Pre) const
     {
         uint32_t y[E];
 #pragma unroll
         for (int k = 0; k < E; k++) y[k] = fwd_canon<W>(x[k], pc);
         storev<E>(M, l, j, y, pc);
     }
-    __device__ int4 final_const(const LaunchMap& M, int l) const { return fc[M.cidx[l]]; }
+    template <class LM>
+    __device__ int4 final_const(const LM& M, int l) const { return fc[M.cidx[l]]; }
 };
 
 // centred lift into int32 (input of a base conversion), tile-thread layout
@@ -1398,8 +1403,13 @@ static NttTables tables(const Ctx& c, bool inverse)
     }
 
 template <int L1, class MS, class Ld, class St>
-static void fwd_cols(const Ctx& c, MS ms, int n, Ld ld, St st, hipStream_t s, int items_n = 1)
+static void fwd_cols(const Ctx& c, MS ms, int n, Ld ld, St st, hipStream_t s, int items_n = 1, bool c4 = false)
 {
+    if (c4) {
+        CKKS_LAUNCH((k_fwd_cols4<L1, MS, Ld, St>), dim3(Col4<L1>::TILES, n, items_n), dim3(NTT_THREADS), 0, s,
+                    tables(c, false), ms, ld, st);
+        return;
+    }
     if constexpr (L1 >= 5) {
         if (c.col_threads == 512) {
             CKKS_LAUNCH((k_fwd_cols<L1, MS, Ld, St, 512>), dim3(col_tiles<L1, 512>(), n, items_n), dim3(512), 0, s,
@@ -1531,13 +1541,13 @@ static int launch_bconv_list(const Ctx& c, int tpw, const std::vector<BcRef>& bs
 // passes again for every group of targets and a chain of n_in passes in every
 // work-group.  Measured, HMult + rescale, two launches -> one: one-prime digits
 // 28.6 -> 23.5 us at N = 2^12 and 32.5 -> 29.4 at 2^16 (3 limbs), two-prime
-// digits 28.6 -> 26.3 and 49.6 -> 49.9 (8 limbs), four-prime digits 28.5 ->
-// 28.8 and 45.3 -> 50.2: the line lies at two primes per digit and 2^20
-// repeated residues.  Rescalings convert 1 to 3 dropped primes to one window:
+// digits 28.6 -> 26.3 and 49.6 -> 49.9 (8 limbs; 42.2 -> 40.6 at 6), four-prime
+// digits 28.5 -> 28.8 and 45.3 -> 50.2: the line lies at two primes per digit
+// and 5 2^18 repeated residues.  Rescalings convert 1 to 3 dropped primes to one window:
 // rational 20.1 -> 18.6 us with 3 at N = 2^16, single 30.5 -> 28.2 at 24 limbs
 // and 17.6 -> 15.5 at 8 limbs of N = 2^12.
 constexpr int FUSE_MAX_IN = 2, RR_FUSE_MAX_IN = 3;
-constexpr size_t FUSE_MAX_REPEAT = (size_t)1 << 20;
+constexpr size_t FUSE_MAX_REPEAT = (size_t)5 << 18;
 // targets per work-group of the rescalings' conversions: 1 repeats the input
 // rows' passes twice as often, 4 leaves 5 work-groups per CU (rational
 // rescaling 18.6 us with 2, 20.2 with 4)
@@ -1579,23 +1589,22 @@ static int launch_inv_bconv_list(const Ctx& c, int tpw, const MapRef& cols, cons
 int launch_ntt(const Ctx& c, bool inverse, uint32_t* data, const int32_t* pids, int n_limbs, hipStream_t s)
 {
     const int log1 = c.log_n - ROW_LOG;
+    const bool c4 = col4(c, 1);
     for (int base = 0; base < n_limbs; base += MAX_LAUNCH_LIMBS) {
         const int n = n_limbs - base < MAX_LAUNCH_LIMBS ? n_limbs - base : MAX_LAUNCH_LIMBS;
         MapByVal M{};
         M.m.count = n;
-        for (int l = 0; l < n; l++) {
-            M.m.in_off[l] = M.m.out_off[l] = base + l;
-            M.m.pid[l] = pids[base + l];
-            M.m.cidx[l] = pids[base + l];
-        }
-        LdPlain ld{data, c.log_n};
-        StPlain st{data, c.ninv, c.log_n};
+        for (int l = 0; l < n; l++) M.m.pid.w[l >> 2] |= (uint32_t)pids[base + l] << (8 * (l & 3));
+        M.m.cidx = M.m.pid;
+        uint32_t* d = data + (size_t)base * c.n;
+        LdPlain ld{d, c.log_n};
+        StPlain st{d, c.ninv, c.log_n};
         if (!inverse) {
-            { KTimer t(c, "ntt_cols", s); CKKS_DISPATCH_LOG1(log1, (fwd_cols<L1>(c, M, n, ld, st, s))); }
+            { KTimer t(c, "ntt_cols", s); CKKS_DISPATCH_LOG1(log1, (fwd_cols<L1>(c, M, n, ld, st, s, 1, c4))); }
             { KTimer t(c, "ntt_rows", s); CKKS_DISPATCH_LOG1(log1, (fwd_rows<L1>(c, M, n, ld, st, s))); }
         } else {
             { KTimer t(c, "intt_rows", s); CKKS_DISPATCH_LOG1(log1, (inv_rows<L1>(c, M, n, ld, st, s))); }
-            { KTimer t(c, "intt_cols", s); CKKS_DISPATCH_LOG1(log1, (inv_cols<L1>(c, M, n, ld, st, s))); }
+            { KTimer t(c, "intt_cols", s); CKKS_DISPATCH_LOG1(log1, (inv_cols<L1>(c, M, n, ld, st, s, 1, c4))); }
         }
         if (int e = launched("ntt")) return e;
     }

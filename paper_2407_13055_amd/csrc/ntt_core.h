@@ -207,13 +207,27 @@ __host__ __device__ constexpr int row_tiles() { return (1 << LOG1) / ROWS_PER_WG
 // St::store16 consume outputs (fused epilogues); St::final_const(M, limb) is
 // the constant folded into the last inverse stage.  M.pid[limb] is the prime.
 // ---------------------------------------------------------------------------
-// Launch maps reach the kernels either by value (kernel argument; the
-// stand-alone NTT call with caller-chosen primes) or as a pointer to a map
-// precomputed in device memory at context creation (every internal launch:
-// a 2 KB kernel argument costs more per launch than the kernel's own start).
+// Launch maps reach the kernels as a pointer to a map precomputed in device
+// memory at context creation (every internal launch), or by value for the
+// stand-alone NTT with its caller-chosen primes: limb l of the launch is limb
+// l of the data, so the prime ids are all there is to pass, a byte each in
+// words that are read by scalar loads (264 bytes of kernel argument; a whole
+// LaunchMap, 3.6 KB, cost more per launch than the kernel's own start).
+struct SameLimb {
+    __device__ int operator[](int l) const { return l; }
+};
+struct PackedIds {
+    uint32_t w[MAX_LAUNCH_LIMBS / 4];
+    __device__ int operator[](int l) const { return (int)((w[l >> 2] >> (8 * (l & 3))) & 255u); }
+};
+struct IdMap {
+    int32_t count;
+    SameLimb in_off, out_off;
+    PackedIds pid, cidx;  // the final constants are indexed by prime too
+};
 struct MapByVal {
-    LaunchMap m;
-    __device__ const LaunchMap* get() const { return &m; }
+    IdMap m;
+    __device__ const IdMap* get() const { return &m; }
 };
 struct MapByPtr {
     const LaunchMap* p;
@@ -295,9 +309,9 @@ template <int LOG1, class MS, class Ld, class St, int CT = NTT_THREADS>
 __global__ void __launch_bounds__(CT) k_fwd_cols(NttTables T, MS ms, Ld ld0, St st0)
 {
     // grid.z = batch item; grid.y is sized for the largest map of a batch
-    const LaunchMap* Mp = ms.get();
+    const auto* Mp = ms.get();
     if (!Mp || (int)blockIdx.y >= Mp->count) return;
-    const LaunchMap& M = *Mp;
+    const auto& M = *Mp;
     const Ld ld = ld0.at(blockIdx.z);
     const St st = st0.at(blockIdx.z);
     using G = ColGeom<LOG1, CT>;
@@ -336,9 +350,9 @@ template <int LOG1, class MS, class Ld, class St>
 __global__ void __launch_bounds__(NTT_THREADS) k_fwd_rows(NttTables T, MS ms, Ld ld0, St st0)
 {
     // grid.z = batch item; grid.y is sized for the largest map of a batch
-    const LaunchMap* Mp = ms.get();
+    const auto* Mp = ms.get();
     if (!Mp || (int)blockIdx.y >= Mp->count) return;
-    const LaunchMap& M = *Mp;
+    const auto& M = *Mp;
     const Ld ld = ld0.at(blockIdx.z);
     const St st = st0.at(blockIdx.z);
     __shared__ uint32_t lds[ROW_LDS_WORDS];
@@ -371,9 +385,9 @@ template <int LOG1, class MS, class Ld, class St>
 __global__ void __launch_bounds__(NTT_THREADS) k_inv_rows(NttTables T, MS ms, Ld ld0, St st0)
 {
     // grid.z = batch item; grid.y is sized for the largest map of a batch
-    const LaunchMap* Mp = ms.get();
+    const auto* Mp = ms.get();
     if (!Mp || (int)blockIdx.y >= Mp->count) return;
-    const LaunchMap& M = *Mp;
+    const auto& M = *Mp;
     const Ld ld = ld0.at(blockIdx.z);
     const St st = st0.at(blockIdx.z);
     __shared__ uint32_t lds[ROW_LDS_WORDS];
@@ -536,7 +550,8 @@ struct LimbInfo {
     int count, pid;
     PrimeC pc;
 };
-__device__ __forceinline__ LimbInfo limb_info(const NttTables& T, const LaunchMap& M, int limb)
+template <class LM>
+__device__ __forceinline__ LimbInfo limb_info(const NttTables& T, const LM& M, int limb)
 {
     LimbInfo r;
     r.count = M.count;
@@ -551,9 +566,9 @@ __device__ __forceinline__ LimbInfo limb_info(const NttTables& T, const LaunchMa
 template <int LOG1, class MS, class Ld, class St>
 __global__ void __launch_bounds__(NTT_THREADS) k_fwd_rows4(NttTables T, MS ms, Ld ld0, St st0)
 {
-    const LaunchMap* Mp = ms.get();
+    const auto* Mp = ms.get();
     if (!Mp) return;
-    const LaunchMap& M = *Mp;
+    const auto& M = *Mp;
     const int limb = blockIdx.y;
     const LimbInfo I = limb_info(T, M, limb);
     if (limb >= I.count) return;
@@ -579,9 +594,9 @@ __global__ void __launch_bounds__(NTT_THREADS) k_fwd_rows4(NttTables T, MS ms, L
 template <int LOG1, class MS, class Ld, class St>
 __global__ void __launch_bounds__(NTT_THREADS) k_inv_rows4(NttTables T, MS ms, Ld ld0, St st0)
 {
-    const LaunchMap* Mp = ms.get();
+    const auto* Mp = ms.get();
     if (!Mp) return;
-    const LaunchMap& M = *Mp;
+    const auto& M = *Mp;
     const int limb = blockIdx.y;
     const LimbInfo I = limb_info(T, M, limb);
     if (limb >= I.count) return;
@@ -747,6 +762,34 @@ __device__ __forceinline__ void col4_inv(uint32_t (&x)[4], const PrimeC& p, uint
     }
 }
 
+// forward column pass, 4 residues per thread; leaves forward values
+template <int LOG1, class MS, class Ld, class St>
+__global__ void __launch_bounds__(NTT_THREADS) k_fwd_cols4(NttTables T, MS ms, Ld ld0, St st0)
+{
+    using G = Col4<LOG1>;
+    const auto* Mp = ms.get();
+    if (!Mp) return;
+    const auto& M = *Mp;
+    const int limb = blockIdx.y;
+    const LimbInfo I = limb_info(T, M, limb);
+    if (limb >= I.count) return;
+    const Ld ld = ld0.at(blockIdx.z);
+    const St st = st0.at(blockIdx.z);
+    __shared__ uint32_t lds[G::WORDS];
+    __shared__ int2 twl[1 << LOG1];
+    const int c = threadIdx.x % G::C, t = threadIdx.x / G::C;
+    const int col = col4_tile<LOG1>(T.xcd_pair) * G::C + c;
+    uint32_t x[1][4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) x[0][k] = ld.load(M, limb, (t + k * G::TC) * ROW + col, I.pc);
+    const int32_t* const tws[1] = {T.tw + ((size_t)I.pid << T.log_n)};
+    const PrimeC pcs[1] = {I.pc};
+    col4_stage_twiddles<LOG1, 1>(twl, tws, pcs);
+    col4_fwd<LOG1, 1>(x, pcs, lds, twl, c, t);
+#pragma unroll
+    for (int k = 0; k < 4; k++) st.store(M, limb, (4 * t + k) * ROW + col, x[0][k], I.pc);
+}
+
 // inverse column pass, 4 residues per thread: reads the row-pass output,
 // ends canonical with the constant folded, stores through St (tile-thread
 // layout when St::kTileThread)
@@ -754,9 +797,9 @@ template <int LOG1, class MS, class Ld, class St>
 __global__ void __launch_bounds__(NTT_THREADS) k_inv_cols4(NttTables T, MS ms, Ld ld0, St st0)
 {
     using G = Col4<LOG1>;
-    const LaunchMap* Mp = ms.get();
+    const auto* Mp = ms.get();
     if (!Mp) return;
-    const LaunchMap& M = *Mp;
+    const auto& M = *Mp;
     const int limb = blockIdx.y;
     const LimbInfo I = limb_info(T, M, limb);
     if (limb >= I.count) return;
@@ -790,9 +833,9 @@ template <int LOG1, class MS, class Ld, class St, int CT = NTT_THREADS>
 __global__ void __launch_bounds__(CT) k_inv_cols(NttTables T, MS ms, Ld ld0, St st0)
 {
     // grid.z = batch item; grid.y is sized for the largest map of a batch
-    const LaunchMap* Mp = ms.get();
+    const auto* Mp = ms.get();
     if (!Mp || (int)blockIdx.y >= Mp->count) return;
-    const LaunchMap& M = *Mp;
+    const auto& M = *Mp;
     const Ld ld = ld0.at(blockIdx.z);
     const St st = st0.at(blockIdx.z);
     using G = ColGeom<LOG1, CT>;
