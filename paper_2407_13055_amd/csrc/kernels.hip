@@ -1319,9 +1319,10 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult_sum(NttTables Tf, NttTa
 // reduction each.  The constants come by value (a kernel argument holds 512
 // matrix entries: 8 inputs to 64 targets, 64 inputs to 8; a larger conversion
 // is several launches), so nothing is set up on the device.  Bound by the
-// launch and the load latency; 8 targets of 2 coefficients keep 32 sum
-// registers and the most work-groups that the products' recomputation per
-// target group is worth.
+// launch and the load latency: 8 -> 24 primes at N = 2^16 take 6.8 us on the
+// GPU (12.0 in the three launches of a lifted copy, set-up and one target per
+// thread).  8 targets of 2 coefficients keep 32 sum registers and the most
+// work-groups that the products' recomputation per target group is worth.
 // ---------------------------------------------------------------------------
 constexpr int BC_VEC = 2, BC_TG = 8, BC_CONSTS = 512;
 struct BconvArgs {
