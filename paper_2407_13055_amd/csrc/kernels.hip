@@ -62,6 +62,15 @@ __device__ __forceinline__ void storev_u32(uint32_t* p, const uint32_t (&x)[E])
     for (int i = 0; i < E / 4; i++) v[i] = make_uint4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
 }
 
+// four residues read once by the whole launch (keys and plaintexts of hoisted
+// rotations): non-temporal, so that they do not displace the shared rows in L2
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void load_once(const uint32_t* p, uint32_t (&x)[4])
+{
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    x[0] = v.x, x[1] = v.y, x[2] = v.z, x[3] = v.w;
+}
+
 // Galois element 5^(k mod N/2) mod 2N of a rotation by k slots (Sec. 2.2 Eq. 4)
 __device__ __forceinline__ uint32_t galois_of(int k, int log_n)
 {
@@ -72,14 +81,46 @@ __device__ __forceinline__ uint32_t galois_of(int k, int log_n)
     return g;
 }
 
-// bit-reversed position of the automorphism's source (Eq. 4, X -> X^g):
-// natural slot k takes natural slot k' with 2k'+1 = g(2k+1) mod 2N.
-__device__ __forceinline__ int aut_src(int pos, uint32_t g, int log_n)
-{
-    const uint32_t k = __brev((uint32_t)pos) >> (32 - log_n);
-    const uint32_t kp = (((g * (2u * k + 1u)) & ((2u << log_n) - 1u)) - 1u) >> 1;
-    return (int)(__brev(kp) >> (32 - log_n));
-}
+// The automorphism X -> X^g in the bit-reversed evaluation order (Eq. 4):
+// natural slot k takes natural slot k' with 2k'+1 = g(2k+1) mod 2N.  An
+// aligned group of four positions differs in the two top bits of k, and
+// g N/4 = (g mod 4) N/4 (mod N): the four sources are one aligned group too,
+// rotated among themselves.  So a thread's four residues are one 16-byte load
+// and one address computation instead of four of each.
+struct AutQuad {
+    uint32_t off;   // first position of the source group
+    uint32_t rot;   // natural index u of the group takes (g u + rot) mod 4
+    bool neg;       // g = 3 (mod 4): conjugation
+    // pos: a multiple of 4
+    __device__ __forceinline__ AutQuad(uint32_t pos, uint32_t g, int log_n)
+    {
+        const uint32_t k = __brev(pos >> 2) >> (34 - log_n);                      // low log_n - 2 bits of the natural slot
+        const uint32_t kp = (g * k + (g >> 1)) & ((1u << log_n) - 1u);
+        off = (__brev(kp & ((1u << (log_n - 2)) - 1u)) >> (34 - log_n)) << 2;
+        rot = kp >> (log_n - 2);
+        neg = (g & 2u) != 0;
+    }
+    __device__ __forceinline__ void load(const uint32_t* row, uint32_t* x) const
+    {
+        const uint4 v = *reinterpret_cast<const uint4*>(row + off);
+        arrange(v, x);
+    }
+    __device__ __forceinline__ void arrange(const uint4 v, uint32_t* x) const
+    {
+        // natural order within the group: positions 0, 2, 1, 3
+        uint32_t w0 = v.x, w1 = neg ? v.w : v.z, w2 = v.y, w3 = neg ? v.z : v.w;
+        const uint32_t r = neg ? 4u - rot : rot;
+        if (r & 1u) {
+            const uint32_t t = w0;
+            w0 = w1, w1 = w2, w2 = w3, w3 = t;
+        }
+        const bool half = (r & 2u) != 0;
+        x[0] = half ? w2 : w0;
+        x[2] = half ? w3 : w1;
+        x[1] = half ? w0 : w2;
+        x[3] = half ? w1 : w3;
+    }
+};
 
 // Every loader / storer carries, per pointer, the residue step between
 // consecutive items of a batched launch (0 for a single operation); at(i)
@@ -145,7 +186,7 @@ struct LdOwn {
             loadv_u32<E>(a0 + off + j, x);
         } else {
 #pragma unroll
-            for (int k = 0; k < E; k++) x[k] = a0[off + aut_src(j + k, galois, log_n)];
+            for (int k = 0; k < E; k += 4) AutQuad(j + k, galois, log_n).load(a0 + off, x + k);
         }
     }
     __device__ void load16(const LaunchMap& M, int l, int j, PrimeC pc, uint32_t (&x)[16]) const
@@ -813,6 +854,26 @@ struct KmArgs {
     const BatchItem* items;
     size_t in_step, in2_step, ws_step, key_step, up_step;
     int lo_level, n_keys, n_src;
+    int n_rot;            // rotations of a hoisted launch (one-dimensional grid, XcdRows)
+};
+
+// Work-groups of a hoisted launch, one-dimensional: every rotation of a row
+// reads the row's shared ModUp rows (256 KB each at N = 2^16), so a row's
+// work-groups all run on one XCD (work-groups go to the 8 XCDs in turn), one
+// rotation after the other, and its L2 serves all but the first: 32 hoisted
+// rotations' KeyMult at N = 2^16, 24 limbs 464 -> 403 us with the 16-byte
+// gathers, and 380 us with the key rows loaded past the L2 (load_once).
+struct XcdRows {
+    int row, rot, tile;
+    __device__ __forceinline__ XcdRows(int tiles, int n_rot)
+    {
+        const uint32_t j = blockIdx.x >> 3;
+        tile = (int)(j % (uint32_t)tiles);
+        const uint32_t k = j / (uint32_t)tiles;
+        rot = (int)(k % (uint32_t)n_rot);
+        row = (int)(k / (uint32_t)n_rot) * 8 + (int)(blockIdx.x & 7u);
+    }
+    static unsigned grid(int rows, int tiles, int n_rot) { return 8u * (unsigned)((rows + 7) / 8) * (unsigned)tiles * (unsigned)n_rot; }
 };
 
 // End of a KeyMult row: Q rows store ks; P rows (and the dropped row q_{l-1}
@@ -859,13 +920,13 @@ __device__ __forceinline__ void keymult_store(const NttTables& Ti, const KmArgs&
     }
 }
 
-// Batched KeyMult launch: item blockIdx.z's level, window, key, rotation and
+// Batched KeyMult launch: the item's level, window, key, rotation and
 // pointers replace the launch's; false if the item is skipped.
-__device__ __forceinline__ bool km_item(KmArgs& A, int log_n)
+__device__ __forceinline__ bool km_item(KmArgs& A, int log_n, int item)
 {
     if (!A.items) return true;
-    const BatchItem it = A.items[blockIdx.z];
-    const size_t z = blockIdx.z;
+    const BatchItem it = A.items[item];
+    const size_t z = (size_t)item;
     if (!item_ok(it, A.lo_level, A.level, A.n_keys, A.n_src)) return false;
     A.level = it.level;
     if (A.lv) {  // windowed context: the item's window, and its rescaling's dropped rows
@@ -896,7 +957,7 @@ template <int LOG1, Own OWN, Extra EX>
 __global__ void __launch_bounds__(NTT_THREADS) k_keymult(NttTables Tf, NttTables Ti, KmArgs A)
 {
     __shared__ uint32_t lds[ROW_LDS_WORDS];
-    if (!km_item(A, Tf.log_n)) return;
+    if (!km_item(A, Tf.log_n, blockIdx.z)) return;
     const int r = blockIdx.y;  // row in q_b..q_{b+l-1}, p_0..
     if (r >= A.level + A.n_p) return;
     // window digit j is the part of key digit kd + j inside the window;
@@ -957,7 +1018,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult(NttTables Tf, NttTables
                     load16_u32(A.a0 + off + j0, x);
                 } else {  // Gather, Hoisted: phi_g(a)
 #pragma unroll
-                    for (int k = 0; k < 16; k++) x[k] = A.a0[off + aut_src(j0 + k, A.galois, log_n)];
+                    for (int k = 0; k < 16; k += 4) AutQuad(j0 + k, A.galois, log_n).load(A.a0 + off, x + k);
                 }
                 const uint2 c = A.rinv[pid];
 #pragma unroll
@@ -967,7 +1028,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult(NttTables Tf, NttTables
             // ModUp row already in the evaluation domain: gather phi_g on load
             const uint32_t* src = A.up + (size_t)(j * rows + r) * n;
 #pragma unroll
-            for (int k = 0; k < 16; k++) x[k] = src[aut_src(j0 + k, A.galois, log_n)];
+            for (int k = 0; k < 16; k += 4) AutQuad(j0 + k, A.galois, log_n).load(src, x + k);
         } else {
             const uint32_t* src = A.up + (size_t)(j * rows + r) * n + (size_t)h * ROW;
 #pragma unroll
@@ -996,9 +1057,11 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult(NttTables Tf, NttTables
     if (r < A.level) {
         if constexpr (EX == Extra::HRot) {
             const uint2 c = A.p_r2[pid];
+            uint32_t x[16];
 #pragma unroll
-            for (int k = 0; k < 16; k++)
-                acc0[k] = add_mod(acc0[k], mulc(A.b0[(size_t)r * n + aut_src(j0 + k, A.galois, log_n)], c, q), q);
+            for (int k = 0; k < 16; k += 4) AutQuad(j0 + k, A.galois, log_n).load(A.b0 + (size_t)r * n, x + k);
+#pragma unroll
+            for (int k = 0; k < 16; k++) acc0[k] = add_mod(acc0[k], mulc(x[k], c, q), q);
         }
     }
     keymult_store<LOG1>(Ti, A, r, pid, h, rp, rr, pc, lds, acc0, acc1);
@@ -1061,12 +1124,17 @@ template <int LOG1, Own OWN, Extra EX>
 __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTables Ti, KmArgs A)
 {
     __shared__ uint32_t lds[ROWS4 * ROW4_PITCH];
-    if (!km_item(A, Tf.log_n)) return;
     // row in q_b..q_{b+l-1}, p_0..: the P rows (the longest work: every digit
     // needs its row pass, then two INTT row passes) take the first grid rows,
     // so they are dispatched first and do not form the launch's tail
-    if ((int)blockIdx.y >= A.level + A.n_p) return;
-    const int r = ((int)blockIdx.y + A.level) % (A.level + A.n_p);
+    int gy = blockIdx.y, tile = blockIdx.x, item = blockIdx.z;
+    if constexpr (OWN == Own::Hoisted) {
+        const XcdRows X(row4_tiles<LOG1>(), A.n_rot);
+        gy = X.row, tile = X.tile, item = X.rot;
+    }
+    if (!km_item(A, Tf.log_n, item)) return;
+    if (gy >= A.level + A.n_p) return;
+    const int r = (gy + A.level) % (A.level + A.n_p);
     const int woff = A.base % A.n_p, kd = A.base / A.n_p;  // as in k_keymult
     const int beta = (woff + A.level + A.n_p - 1) / A.n_p;
     const int log_n = Tf.log_n;
@@ -1074,7 +1142,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
     const PrimeC pc = Tf.prime(pid);
     const uint32_t q = pc.q, qinv = pc.qinv;
     const int t = threadIdx.x & 63, w = wave_id();
-    const int h = blockIdx.x * ROWS4 + w;
+    const int h = tile * ROWS4 + w;
     const int j0 = h * ROW + 4 * t;  // this thread's residues: row h, positions 4t .. 4t+3
     // contiguous accesses as a wave-uniform pointer (through row h) plus the
     // lane's 32-bit offset 4t (scalar-base loads and stores)
@@ -1095,6 +1163,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
     const uint2 r1 = A.r1[pid];
     constexpr bool EXTRA = OWN == Own::Tensor && EX == Extra::HMult;
 
+    [[maybe_unused]] const AutQuad quad((uint32_t)j0, A.galois, log_n);
     // The digit whose own rows this row is (none for P rows); its input rows
     // are requested at the start, every digit's key rows and ModUp row one
     // digit ahead of their use.
@@ -1114,21 +1183,25 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
         } else if constexpr (OWN == Own::Plain) {
             loadv_u32<4>(A.a0 + (off + hrow) + l4, o0);
         } else {  // Gather, Hoisted: phi_g(a)
-#pragma unroll
-            for (int k = 0; k < 4; k++) o0[k] = A.a0[off + aut_src(j0 + k, A.galois, log_n)];
+            quad.load(A.a0 + off, o0);
         }
     }
     struct Dig {
         uint32_t kb[4], ka[4], x[4];
     };
     auto issue = [&](int j, Dig& d) {
-        loadv_u32<4>(A.evk + (((size_t)(2 * (kd + j)) * key_rows + pid) * n + hrow) + l4, d.kb);
-        loadv_u32<4>(A.evk + (((size_t)(2 * (kd + j) + 1) * key_rows + pid) * n + hrow) + l4, d.ka);
+        const uint32_t* kb = A.evk + (((size_t)(2 * (kd + j)) * key_rows + pid) * n + hrow) + l4;
+        const uint32_t* ka = A.evk + (((size_t)(2 * (kd + j) + 1) * key_rows + pid) * n + hrow) + l4;
+        if constexpr (OWN == Own::Hoisted) {
+            load_once(kb, d.kb);
+            load_once(ka, d.ka);
+        } else {
+            loadv_u32<4>(kb, d.kb);
+            loadv_u32<4>(ka, d.ka);
+        }
         if (j == jown) return;
         if constexpr (OWN == Own::Hoisted) {  // ModUp row already in the evaluation domain: gather phi_g
-            const uint32_t* src = A.up + (size_t)(j * rows + r) * n;
-#pragma unroll
-            for (int k = 0; k < 4; k++) d.x[k] = src[aut_src(j0 + k, A.galois, log_n)];
+            loadv_u32<4>(A.up + (size_t)(j * rows + r) * n + quad.off, d.x);
         } else {
             const uint32_t* src = A.up + (size_t)(j * rows + r) * n + (size_t)h * ROW;
 #pragma unroll
@@ -1168,9 +1241,11 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
                 for (int k = 0; k < 4; k++) x[k] = mulc(o0[k], c, q);
             }
         } else {
+            if constexpr (OWN == Own::Hoisted) {
+                quad.arrange(make_uint4(cur.x[0], cur.x[1], cur.x[2], cur.x[3]), x);
+            } else {
 #pragma unroll
-            for (int k = 0; k < 4; k++) x[k] = cur.x[k];
-            if constexpr (OWN != Own::Hoisted) {
+                for (int k = 0; k < 4; k++) x[k] = cur.x[k];
                 row4_fwd<W>(x, pc, lds, w, t, twf);
                 if constexpr (!W) {
 #pragma unroll
@@ -1197,9 +1272,10 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
     if (r < A.level) {
         if constexpr (EX == Extra::HRot) {
             const uint2 c = A.p_r2[pid];
+            uint32_t x[4];
+            quad.load(A.b0 + (size_t)r * n, x);
 #pragma unroll
-            for (int k = 0; k < 4; k++)
-                acc0[k] = add_mod(acc0[k], mulc(A.b0[(size_t)r * n + aut_src(j0 + k, A.galois, log_n)], c, q), q);
+            for (int k = 0; k < 4; k++) acc0[k] = add_mod(acc0[k], mulc(x[k], c, q), q);
         }
     }
 
@@ -1233,17 +1309,23 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
 // KeyMult pass over all rotations.  For row r, rotation i: the shared ModUp
 // rows (evaluation domain) and the own digit's input row are gathered
 // through phi_i, multiplied into rotation i's key rows, weighted by the
-// plaintext row pt_i (taken to Montgomery form, so the 2^-64 bookkeeping of
-// ks is unchanged) and accumulated; Q rows also take P * pt_i * phi_i(b).
+// plaintext row pt_i and accumulated; Q rows also take P * pt_i * phi_i(b).
 // One ModDown follows.  items[i] = {level, key, rot, -}.
 // ---------------------------------------------------------------------------
+// One wave per 256-point row, 4 residues per thread, as k_keymult4; the key
+// rows and the ModUp row of the next digit (of the next rotation after the
+// last) are requested while a digit is multiplied.  Bound by the key and
+// plaintext rows, read once each (2 beta + 1 rows per row and rotation): 32
+// rotations at N = 2^16, 24 limbs, three digits (1.9 GB) take 330 us, 5.7 TB/s.
+// 16 residues per thread with single gathers and a Montgomery product per term
+// took 483 us, this kernel with cached key and plaintext loads 398 us.
 template <int LOG1>
 __global__ void __launch_bounds__(NTT_THREADS) k_keymult_sum(NttTables Tf, NttTables Ti, KmArgs A,
-                                                              const uint32_t* pts, size_t pt_step, int n_rot,
-                                                              const uint2* rmont)
+                                                              const uint32_t* pts, size_t pt_step, int n_rot)
 {
-    __shared__ uint32_t lds[ROW_LDS_WORDS];
-    const int r = blockIdx.y;
+    __shared__ uint32_t lds[ROWS4 * ROW4_PITCH];
+    const XcdRows X(row4_tiles<LOG1>(), 1);
+    const int r = X.row;
     if (r >= A.level + A.n_p) return;
     const int woff = A.base % A.n_p, kd = A.base / A.n_p;  // as in k_keymult
     const int beta = (woff + A.level + A.n_p - 1) / A.n_p;
@@ -1251,63 +1333,123 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult_sum(NttTables Tf, NttTa
     const int pid = r < A.level ? A.base + r : A.n_q + (r - A.level);  // also the key and plaintext row
     const PrimeC pc = Tf.prime(pid);
     const uint32_t q = pc.q, qinv = pc.qinv;
-    const int rp = threadIdx.x % 16, rr = threadIdx.x / 16;
-    const int h = blockIdx.x * ROWS_PER_WG + rr;
-    const int j0 = h * ROW + 16 * rp;
-    const size_t n = (size_t)1 << log_n;
+    const int t = threadIdx.x & 63, w = wave_id();
+    const int h = X.tile * ROWS4 + w;
+    const uint32_t j0 = (uint32_t)(h * ROW + 4 * t);
+    const size_t n = (size_t)1 << log_n, hrow = (size_t)h * ROW;
+    const uint32_t l4 = 4u * (uint32_t)t;
     const int rows = A.level + A.n_p, key_rows = A.n_q + A.n_p;
-    const uint2 cm = rmont[pid];  // x -> x 2^32 mod q
+    const uint2 r1 = A.r1[pid];
+    const bool q_row = r < A.level;
+    int jown = -1;
+    for (int j = 0; j < beta; j++)
+        if (r >= max(j * A.n_p - woff, 0) && r < min((j + 1) * A.n_p - woff, A.level)) jown = j;
 
-    uint32_t acc0[16], acc1[16];
-#pragma unroll
-    for (int k = 0; k < 16; k++) acc0[k] = acc1[k] = 0;
-    for (int i = 0; i < n_rot; i++) {
-        const BatchItem it = A.items[i];
-        if (!item_ok(it, A.level, A.level, A.n_keys, 0)) continue;  // uniform across the launch
-        const uint32_t g = galois_of(it.rot, log_n);
-        const uint32_t* evk = A.evk + (size_t)it.key * A.key_step;
-        uint32_t s0[16], s1[16];
-#pragma unroll
-        for (int k = 0; k < 16; k++) s0[k] = s1[k] = 0;
-        for (int j = 0; j < beta; j++) {
-            uint32_t kb[16], ka[16], x[16];
-            load16_u32(evk + ((size_t)(2 * (kd + j)) * key_rows + pid) * n + j0, kb);
-            load16_u32(evk + ((size_t)(2 * (kd + j) + 1) * key_rows + pid) * n + j0, ka);
-            const int lo = max(j * A.n_p - woff, 0), hi = min((j + 1) * A.n_p - woff, A.level);
-            if (r >= lo && r < hi) {  // the digit's own row: phi(a) times R^-1, as in ModUp's own rows
-                const size_t off = (size_t)r * n;
-                const uint2 c = A.rinv[pid];
-#pragma unroll
-                for (int k = 0; k < 16; k++) x[k] = mulc(A.a0[off + aut_src(j0 + k, g, log_n)], c, q);
-            } else {
-                const uint32_t* src = A.up + (size_t)(j * rows + r) * n;
-#pragma unroll
-                for (int k = 0; k < 16; k++) x[k] = src[aut_src(j0 + k, g, log_n)];
+    by_class(q, [&](auto tag) {
+        constexpr bool W = decltype(tag)::value;
+        using Sum = KmSum<W>;
+        struct Dig {
+            uint32_t kb[4], ka[4], x[4];
+        };
+        // the rotation in hand and the one whose first digit is requested next
+        struct Rot {
+            int i;
+            const uint32_t* evk;
+            AutQuad quad;
+        };
+        auto rotation = [&](int i) {  // the first rotation from i on that is not skipped (uniform across the launch)
+            BatchItem it{};
+            for (; i < n_rot; i++) {
+                it = A.items[i];
+                if (item_ok(it, A.level, A.level, A.n_keys, 0)) break;
             }
+            const uint32_t g = i < n_rot ? galois_of(it.rot, log_n) : 1u;
+            return Rot{i, A.evk + (i < n_rot ? (size_t)it.key * A.key_step : 0), AutQuad(j0, g, log_n)};
+        };
+        auto issue = [&](const Rot& R, int j, Dig& d) {
+            load_once(R.evk + (((size_t)(2 * (kd + j)) * key_rows + pid) * n + hrow) + l4, d.kb);
+            load_once(R.evk + (((size_t)(2 * (kd + j) + 1) * key_rows + pid) * n + hrow) + l4, d.ka);
+            loadv_u32<4>((j == jown ? A.a0 + (size_t)r * n : A.up + (size_t)(j * rows + r) * n) + R.quad.off, d.x);
+        };
+        Sum t0[4], t1[4];
 #pragma unroll
-            for (int k = 0; k < 16; k++) {
-                s0[k] = add_mod(s0[k], mont(x[k], kb[k], q, qinv), q);
-                s1[k] = add_mod(s1[k], mont(x[k], ka[k], q, qinv), q);
+        for (int k = 0; k < 4; k++) t0[k].s = t1[k].s = 0;
+        int total = 0;  // what t0 / t1 hold, in KmSum's count
+        const uint2 own_c = q_row ? A.rinv[pid] : make_uint2(0, 0), pb_c = q_row ? A.p_r2[pid] : make_uint2(0, 0);
+        Rot cur = rotation(0);
+        Dig d;
+        if (cur.i < n_rot) issue(cur, 0, d);
+        while (cur.i < n_rot) {
+            uint32_t pm[4], pb[4];
+            load_once(pts + (size_t)cur.i * pt_step + ((size_t)pid * n + hrow) + l4, pm);
+            if (q_row) loadv_u32<4>(A.b0 + (size_t)r * n + cur.quad.off, pb);
+            const Rot next = rotation(cur.i + 1);
+            Sum s0[4], s1[4];
+#pragma unroll
+            for (int k = 0; k < 4; k++) s0[k].s = s1[k].s = 0;
+            int terms = 0;
+            for (int j = 0; j < beta; j++) {
+                Dig nd;
+                const bool last = j + 1 == beta;
+                if (!last || next.i < n_rot) issue(last ? next : cur, last ? 0 : j + 1, nd);
+                if (terms + Sum::CANON > Sum::LIMIT) {
+#pragma unroll
+                    for (int k = 0; k < 4; k++) s0[k].fold(r1, q), s1[k].fold(r1, q);
+                    terms = 1;
+                }
+                terms += Sum::CANON;
+                uint32_t x[4];
+                cur.quad.arrange(make_uint4(d.x[0], d.x[1], d.x[2], d.x[3]), x);
+                if (j == jown) {  // the digit's own row: phi(a) times R^-1, as in ModUp's own rows
+#pragma unroll
+                    for (int k = 0; k < 4; k++) x[k] = mulc(x[k], own_c, q);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; k++) s0[k].mac(x[k], d.kb[k]), s1[k].mac(x[k], d.ka[k]);
+                d = nd;
             }
-        }
-        uint32_t pm[16];
-        load16_u32(pts + (size_t)i * pt_step + (size_t)pid * n + j0, pm);
+            // the weighted sums: canonical products p s (and p P phi(b)), reduced once after the last rotation
+            if (total + 2 * Sum::CANON > Sum::LIMIT) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) {
-            pm[k] = mulc(pm[k], cm, q);  // p 2^32: mont(s, p 2^32) = s p
-            acc0[k] = add_mod(acc0[k], mont(s0[k], pm[k], q, qinv), q);
-            acc1[k] = add_mod(acc1[k], mont(s1[k], pm[k], q, qinv), q);
-        }
-        if (r < A.level) {  // + P * p * phi(b), with the R^-2 of ks
-            const uint2 c = A.p_r2[pid];
-#pragma unroll
-            for (int k = 0; k < 16; k++) {
-                const uint32_t pb = mulc(A.b0[(size_t)r * n + aut_src(j0 + k, g, log_n)], c, q);
-                acc0[k] = add_mod(acc0[k], mont(pb, pm[k], q, qinv), q);
+                for (int k = 0; k < 4; k++) t0[k].fold(r1, q), t1[k].fold(r1, q);
+                total = 1;
             }
+            total += 2 * Sum::CANON;
+            uint32_t bx[4];
+            if (q_row) cur.quad.arrange(make_uint4(pb[0], pb[1], pb[2], pb[3]), bx);
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                t0[k].mac(s0[k].reduce(q, qinv), pm[k]);
+                t1[k].mac(s1[k].reduce(q, qinv), pm[k]);
+                if (q_row) t0[k].mac(mulc(bx[k], pb_c, q), pm[k]);  // P phi(b), with the R^-2 of ks
+            }
+            cur = next;
         }
-    }
-    keymult_store<LOG1>(Ti, A, r, pid, h, rp, rr, pc, lds, acc0, acc1);
+        // the sums carry the R^-2 of ks; their reduction takes one R more, given back here
+        uint32_t acc0[4], acc1[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            acc0[k] = mulc(t0[k].reduce(q, qinv), r1, q);
+            acc1[k] = mulc(t1[k].reduce(q, qinv), r1, q);
+        }
+        if (q_row) {
+            storev_u32<4>(A.ks_q + ((size_t)r * n + hrow) + l4, acc0);
+            storev_u32<4>(A.ks_q + (((size_t)A.level + r) * n + hrow) + l4, acc1);
+            return;
+        }
+        int2 twi[4][3];
+        row4_twiddles<LOG1, true>(Ti.tw + ((size_t)pid << log_n), q, h, t, twi);
+#pragma unroll
+        for (int poly = 0; poly < 2; poly++) {
+            uint32_t x[4];
+#pragma unroll
+            for (int k = 0; k < 4; k++) x[k] = poly ? acc1[k] : acc0[k];
+            row4_inv<W>(x, pc, lds, w, t, twi);
+            uint32_t* dst = A.ks_p + ((size_t)poly * A.n_p + (r - A.level)) * n + hrow;
+#pragma unroll
+            for (int k = 0; k < 4; k++) dst[t + 64 * k] = x[k];
+        }
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -1681,7 +1823,9 @@ template <int L1, Own OWN, Extra EX>
 static void keymult(const Ctx& c, int max_level, int items_n, const KmArgs& A, hipStream_t s)
 {
     if ((items_n == 1 ? c.km_ept1 : c.km_ept) == 4)
-        CKKS_LAUNCH((k_keymult4<L1, OWN, EX>), dim3(row4_tiles<L1>(), max_level + c.n_p, items_n),
+        CKKS_LAUNCH((k_keymult4<L1, OWN, EX>),
+                    OWN == Own::Hoisted ? dim3(XcdRows::grid(max_level + c.n_p, row4_tiles<L1>(), items_n))
+                                        : dim3(row4_tiles<L1>(), max_level + c.n_p, items_n),
                     dim3(NTT_THREADS), 0, s, tables(c, false), tables(c, true), A);
     else
         CKKS_LAUNCH((k_keymult<L1, OWN, EX>), dim3(row_tiles<L1>(), max_level + c.n_p, items_n), dim3(NTT_THREADS),
@@ -1968,6 +2112,7 @@ int launch_hrot_hoisted(const Ctx& c, const uint32_t* b_in, const uint32_t* a_in
     A.key_step = key_step;
     A.ws_step = slice;
     A.up_step = 0;
+    A.n_rot = n_rot;
     if (int e = keymult_launch(c, Own::Hoisted, Extra::HRot, level, n_rot, A, s)) return e;
     const size_t out_step = 2 * (size_t)level * c.n;
     return moddown_phase(R, level, false, outs, outs + (size_t)level * c.n, out_step, s);
@@ -1977,8 +2122,8 @@ template <int L1>
 static void keymult_sum(const Ctx& c, int level, const KmArgs& A, const uint32_t* pts, size_t pt_step, int n_rot,
                         hipStream_t s)
 {
-    CKKS_LAUNCH((k_keymult_sum<L1>), dim3(row_tiles<L1>(), level + c.n_p, 1), dim3(NTT_THREADS), 0, s,
-                tables(c, false), tables(c, true), A, pts, pt_step, n_rot, (const uint2*)c.r1);
+    CKKS_LAUNCH((k_keymult_sum<L1>), dim3(XcdRows::grid(level + c.n_p, row4_tiles<L1>(), 1)), dim3(NTT_THREADS), 0, s,
+                tables(c, false), tables(c, true), A, pts, pt_step, n_rot);
 }
 
 // Sum of plaintext-weighted rotations: the hoisted ModUp (as above), one
