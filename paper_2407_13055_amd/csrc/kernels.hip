@@ -242,7 +242,8 @@ struct StPlain {
     __device__ int4 final_const(const LM& M, int l) const { return fc[M.cidx[l]]; }
 };
 
-// centred lift into int32 (input of a base conversion), tile-thread layout
+// centred lift into int32 (input of a base conversion), tile-thread layout:
+// four points of a column per 16-byte run (Col4)
 struct StLift {
     static constexpr bool kTileThread = true;
     int32_t* base;
@@ -255,17 +256,12 @@ struct StLift {
         r.base += (size_t)i * step;
         return r;
     }
-    template <int E>
-    __device__ void storev(const LaunchMap& M, int l, int j, const uint32_t (&x)[E], PrimeC pc) const
+    __device__ void store4(const LaunchMap& M, int l, int j, const uint32_t (&x)[4], PrimeC pc) const
     {
-        uint32_t y[E];
+        uint32_t y[4];
 #pragma unroll
-        for (int k = 0; k < E; k++) y[k] = (uint32_t)lift(x[k], pc.q);
-        storev_u32<E>(reinterpret_cast<uint32_t*>(base) + ((size_t)M.out_off[l] << log_n) + j, y);
-    }
-    __device__ void store16(const LaunchMap& M, int l, int j, const uint32_t (&x)[16], PrimeC pc) const
-    {
-        storev<16>(M, l, j, x, pc);
+        for (int k = 0; k < 4; k++) y[k] = (uint32_t)lift(x[k], pc.q);
+        storev_u32<4>(reinterpret_cast<uint32_t*>(base) + ((size_t)M.out_off[l] << log_n) + j, y);
     }
     __device__ int4 final_const(const LaunchMap& M, int l) const { return fc[M.cidx[l]]; }
 };
@@ -397,9 +393,18 @@ __global__ void __launch_bounds__(CT) k_bconv_ntt_cols(NttTables T, BS bs, const
     const int col = tile * G::C + c;
     const int n_in = B.n_in[g], n_tg = B.n_tg[g], first = B.first[g];
     const size_t n = (size_t)1 << T.log_n;
-    // inputs in the tile-thread layout: this thread's 16 residues of row s
-    // are contiguous at s*N + tile*4096 + tid*16
-    const int32_t* src = y + (size_t)B.in_off[g] * n + tile * G::TILE + threadIdx.x * 16;
+    // inputs in the tile-thread layout: this thread's 16 residues of row s are
+    // four runs of four, s*N + tile_run(col, r + R m)
+    const int32_t* src = y + (size_t)B.in_off[g] * n;
+    auto load_row = [&](size_t row, uint32_t (&x)[16]) {
+#pragma unroll
+        for (int m = 0; m < 4; m++) {
+            uint32_t v[4];
+            loadv_u32<4>(reinterpret_cast<const uint32_t*>(src + row * n) + tile_run<LOG1>(col, r + G::R * m), v);
+#pragma unroll
+            for (int k = 0; k < 4; k++) x[m + 4 * k] = v[k];
+        }
+    };
 
     int64_t acc[TPW][16];
     int64_t t31[TPW], t32[TPW];
@@ -422,8 +427,7 @@ __global__ void __launch_bounds__(CT) k_bconv_ntt_cols(NttTables T, BS bs, const
 #pragma unroll
         for (int k = 0; k < 16; k++) accl[k] = 0;
     }
-    // one input row at a time (this thread's 16 residues are one 64-byte run);
-    // the next row's load is in flight while this row is accumulated
+    // one input row at a time; the next row's load is in flight while this row is accumulated
     auto mac = [&](const uint32_t (&yv)[16], int s) {
         if (s >= 8 && (s & 3) == 0) {
 #pragma unroll
@@ -448,15 +452,15 @@ __global__ void __launch_bounds__(CT) k_bconv_ntt_cols(NttTables T, BS bs, const
         }
     };
     uint32_t e[RS ? 16 : 1];
-    if constexpr (RS) load16_u32(reinterpret_cast<const uint32_t*>(src + n_in * n), e);  // last limb, used below
+    if constexpr (RS) load_row((size_t)n_in, e);  // last limb, used below
     {
         uint32_t ya[16], yb[16];
-        if (n_in > 0) load16_u32(reinterpret_cast<const uint32_t*>(src), ya);
+        if (n_in > 0) load_row(0, ya);
         int s = 0;
         for (; s + 1 < n_in; s += 2) {
-            load16_u32(reinterpret_cast<const uint32_t*>(src + (s + 1) * n), yb);
+            load_row((size_t)(s + 1), yb);
             mac(ya, s);
-            if (s + 2 < n_in) load16_u32(reinterpret_cast<const uint32_t*>(src + (s + 2) * n), ya);
+            if (s + 2 < n_in) load_row((size_t)(s + 2), ya);
             mac(yb, s + 1);
         }
         if (s < n_in) mac(ya, s);
@@ -1593,15 +1597,21 @@ static void inv_rows(const Ctx& c, MS ms, int n, Ld ld, St st, hipStream_t s, in
         CKKS_LAUNCH((k_inv_rows<L1, MS, Ld, St>), dim3(row_tiles<L1>(), n, items_n), dim3(NTT_THREADS), 0,
                            s, tables(c, true), ms, ld, st);
 }
+// Inverse column passes of 4 residues per thread, where they are asked for
+// (c4), give way to 16 when that leaves 8 work-groups per CU: one LDS exchange
+// instead of three, and 64-byte instead of 16-byte runs of a row per tile.
+// 64 items of 4 to 24 limbs at N = 2^16: ModUp's pass 175 -> 135 us, ModDown's
+// 208 -> 162; one operation's 24 limbs (384 work-groups): 5.7 against 7.1 us.
+constexpr long INV_COLS16_GROUPS = 2048;
 template <int L1, class MS, class Ld, class St>
 static void inv_cols(const Ctx& c, MS ms, int n, Ld ld, St st, hipStream_t s, int items_n = 1, bool c4 = false)
 {
-    if (c4) {  // 4 residues per thread (its BConv consumer must be k_bconv_ntt_cols4)
+    if (c4 && (long)col_tiles<L1>() * n * items_n < INV_COLS16_GROUPS) {
         CKKS_LAUNCH((k_inv_cols4<L1, MS, Ld, St>), dim3(Col4<L1>::TILES, n, items_n), dim3(NTT_THREADS), 0, s,
                     tables(c, true), ms, ld, st);
         return;
     }
-    const int ct = c.col_threads;  // a producer and its BConv consumer must agree
+    const int ct = c4 ? NTT_THREADS : c.col_threads;
     if constexpr (L1 >= 5) {
         if (ct == 512) {
             CKKS_LAUNCH((k_inv_cols<L1, MS, Ld, St, 512>), dim3(col_tiles<L1, 512>(), n, items_n), dim3(512), 0, s,

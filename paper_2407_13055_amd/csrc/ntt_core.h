@@ -170,7 +170,6 @@ struct ColGeom {
     static constexpr int C = CT / R;            // columns per work-group
     static constexpr int NS2 = LOG1 - 4;        // stages in the second round
     static constexpr int LDS = (S1 + S1 / 16) * C;
-    static constexpr int TILE = CT * 16;        // residues per tile (tile-thread layout)
     static_assert(C <= ROW, "column tile wider than a row");
 };
 constexpr int ROW_LDS_WORDS = ROWS_PER_WG * (ROW + ROW / 16);
@@ -624,9 +623,9 @@ __global__ void __launch_bounds__(NTT_THREADS) k_inv_rows4(NttTables T, MS ms, L
 // points are base + k 2^sh, base = ((t >> sh) << (sh + 2)) | (t mod 2^sh);
 // the radix-2 round holds 4t + k.  The forward pass enters with points
 // t + k TC (TC = 2^LOG1 / 4) and leaves with 4t + k; the inverse pass the
-// other way round.  Tile-thread layout of lifted residues (the inverse pass
-// writes it, the BConv pass reads it): thread tid of tile T keeps its four
-// residues at T 1024 + 4 tid.
+// other way round.  Tile-thread layout of lifted residues (inverse passes
+// write it, BConv passes read it, of either width): thread tid of tile T keeps
+// its four residues at T 1024 + 4 tid (tile_run).
 // ---------------------------------------------------------------------------
 template <int LOG1>
 struct Col4 {
@@ -650,6 +649,13 @@ struct Col4 {
     __host__ __device__ static constexpr int ish(int j) { return ODD ? (j == 0 ? -1 : 1 + 2 * (j - 1)) : 2 * j; }
     static_assert(C >= 1 && C * TC == NTT_THREADS, "column tile");
 };
+// where the points t + k TC (k < 4) of a column start in the tile-thread layout
+template <int LOG1>
+__device__ __forceinline__ int tile_run(int col, int t)
+{
+    using G = Col4<LOG1>;
+    return (col / G::C) * G::TILE + (t * G::C + col % G::C) * 4;
+}
 __device__ __forceinline__ int col4_base(int t, int sh) { return sh < 0 ? 4 * t : (((t >> sh) << (sh + 2)) | (t & ((1 << sh) - 1))); }
 __device__ __forceinline__ int col4_step(int sh) { return sh < 0 ? 1 : 1 << sh; }
 
@@ -819,7 +825,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_inv_cols4(NttTables T, MS ms, L
     col4_stage_twiddles<LOG1, 1>(twl, tws, pcs);
     by_class(pc.q, [&](auto tag) { col4_inv<LOG1, decltype(tag)::value>(x, pc, lds, twl, c, t, cst); });
     if constexpr (St::kTileThread) {
-        st.template storev<4>(M, limb, tile * G::TILE + threadIdx.x * 4, x, pc);
+        st.store4(M, limb, tile * G::TILE + threadIdx.x * 4, x, pc);
     } else {
 #pragma unroll
         for (int k = 0; k < 4; k++) st.store(M, limb, (t + k * G::TC) * ROW + col, x[k], pc);
@@ -869,9 +875,12 @@ __global__ void __launch_bounds__(CT) k_inv_cols(NttTables T, MS ms, Ld ld0, St 
         gs_stages<4, W, true>(x, pc, [&](int u, int b) { return tw[(1 << u) + b]; }, cst);
     });
     if constexpr (St::kTileThread) {
-        // internal layout shared with the next column pass: thread tid of
-        // tile t keeps its 16 residues at t*4096 + tid*16 (one 64-byte run)
-        st.store16(M, limb, col_tile<LOG1, CT>(T.xcd_pair) * G::TILE + threadIdx.x * 16, x, pc);
+        // points r + R (m + 4 k) of the column: run r + R m of the tile-thread layout
+#pragma unroll
+        for (int m = 0; m < 4; m++) {
+            const uint32_t v[4] = {x[m], x[m + 4], x[m + 8], x[m + 12]};
+            st.store4(M, limb, tile_run<LOG1>(col, r + G::R * m), v, pc);
+        }
     } else {
 #pragma unroll
         for (int k = 0; k < 16; k++) st.store(M, limb, (r + G::R * k) * ROW + col, x[k], pc);
