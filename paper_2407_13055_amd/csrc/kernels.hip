@@ -1076,7 +1076,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult(NttTables Tf, NttTables
 // per work-group): four times the waves of k_keymult, for launches with few
 // rows in flight.  Same inputs, outputs and residues as k_keymult.
 //  * The ModUp rows finish their NTT row pass as four radix-4 rounds with
-//    three exchanges through the wave's own LDS rows (as k_fwd_rows4); the
+//    three exchanges between registers and lanes (as k_fwd_rows4); the
 //    row's twelve twiddles per thread stay in registers across the digits.
 //  * The digit products of a coefficient are summed exactly in 64 bits and
 //    reduced once: x 2^-32 of the sum is the same residue as the sum of
@@ -1127,7 +1127,6 @@ struct KmSum {
 template <int LOG1, Own OWN, Extra EX>
 __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTables Ti, KmArgs A)
 {
-    __shared__ uint32_t lds[ROWS4 * ROW4_PITCH];
     // row in q_b..q_{b+l-1}, p_0..: the P rows (the longest work: every digit
     // needs its row pass, then two INTT row passes) take the first grid rows,
     // so they are dispatched first and do not form the launch's tail
@@ -1250,7 +1249,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
             } else {
 #pragma unroll
                 for (int k = 0; k < 4; k++) x[k] = cur.x[k];
-                row4_fwd<W>(x, pc, lds, w, t, twf);
+                row4_fwd<W>(x, pc, t, twf);
                 if constexpr (!W) {
 #pragma unroll
                     for (int k = 0; k < 4; k++) x[k] = fwd_canon<W>(x[k], pc);
@@ -1300,7 +1299,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
         uint32_t x[4];
 #pragma unroll
         for (int k = 0; k < 4; k++) x[k] = poly ? acc1[k] : acc0[k];
-        row4_inv<W>(x, pc, lds, w, t, twi);
+        row4_inv<W>(x, pc, t, twi);
         uint32_t* dst = A.ks_p + ((size_t)poly * (A.n_p + A.rs) + slot) * n + (size_t)h * ROW;
 #pragma unroll
         for (int k = 0; k < 4; k++) dst[t + 64 * k] = x[k];
@@ -1327,7 +1326,6 @@ template <int LOG1>
 __global__ void __launch_bounds__(NTT_THREADS) k_keymult_sum(NttTables Tf, NttTables Ti, KmArgs A,
                                                               const uint32_t* pts, size_t pt_step, int n_rot)
 {
-    __shared__ uint32_t lds[ROWS4 * ROW4_PITCH];
     const XcdRows X(row4_tiles<LOG1>(), 1);
     const int r = X.row;
     if (r >= A.level + A.n_p) return;
@@ -1448,7 +1446,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult_sum(NttTables Tf, NttTa
             uint32_t x[4];
 #pragma unroll
             for (int k = 0; k < 4; k++) x[k] = poly ? acc1[k] : acc0[k];
-            row4_inv<W>(x, pc, lds, w, t, twi);
+            row4_inv<W>(x, pc, t, twi);
             uint32_t* dst = A.ks_p + ((size_t)poly * A.n_p + (r - A.level)) * n + hrow;
 #pragma unroll
             for (int k = 0; k < 4; k++) dst[t + 64 * k] = x[k];

@@ -415,29 +415,16 @@ __global__ void __launch_bounds__(NTT_THREADS) k_inv_rows(NttTables T, MS ms, Ld
 
 // ---------------------------------------------------------------------------
 // Row passes with one wave per row (4 residues per thread, 4 rows per
-// work-group): four radix-4 rounds with three exchanges, through the wave's
-// own LDS row or in registers.  Four times the waves of the 16-residue
-// passes: more memory latency hidden per SIMD when a launch has few limbs.
+// work-group): four radix-4 rounds with three exchanges between registers and
+// lanes, no LDS.  Four times the waves of the 16-residue passes: more memory
+// latency hidden per SIMD when a launch has few limbs.
 // Round j of the forward pass holds the 4 points
 // l = blk*2^(sh+2) + pp + k*2^sh (sh = 6 - 2j, blk = t >> sh); the inverse
-// pass walks the same units in the opposite order (sh = 2j).  A round stores
-// its results where it read its inputs, and each point is read by one lane
-// per round, so one buffer serves every round.  Only the wave itself touches
-// its row, and a CU performs one wave's LDS operations in issue order, so
-// the exchanges need no work-group barrier: wave_lds_sync only keeps the
-// compiler from moving LDS accesses across the exchange.
+// pass walks the same units in the opposite order (sh = 2j).
 // ---------------------------------------------------------------------------
 constexpr int ROWS4 = NTT_THREADS / 64;   // rows (waves) per work-group
 // the wave's index in its work-group, as a scalar (the same in every lane)
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
-constexpr int ROW4_PITCH = ROW + ROW / 16;
-__device__ __forceinline__ int row4_lds(int w, int l) { return w * ROW4_PITCH + l + (l >> 4); }
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 template <int LOG1>
 __host__ __device__ constexpr int row4_tiles() { return (1 << LOG1) / ROWS4; }
 
@@ -460,62 +447,80 @@ __device__ __forceinline__ void quad_transpose(uint32_t (&x)[4], int lane)
     for (int b = 0; b < 4; b++) x[b] = ((b ^ lane) & 2) ? y[b] : x[b];
 }
 
+// Exchange of one register bit with one lane bit: of a pair (a: register bit
+// 0, b: bit 1), a lane whose bit LB is 0 keeps a and takes its partner's a as
+// its b, a lane whose bit is 1 keeps b and takes its partner's b as its a.
+// Bits 5 and 4 are the two halves and the odd and even 16-lane rows, which
+// v_permlane32_swap and v_permlane16_swap exchange between two registers; bits
+// 3 and 2 stay in a 16-lane row: a DPP shift by 8 or 4 lanes, written to the
+// banks of four lanes that take it.
+// Row passes need no LDS with these, column passes one exchange through LDS and
+// one barrier instead of three (a swap of two registers takes about 2.5 issue
+// slots, a DPP move one; an LDS exchange of four points 8 LDS operations, their
+// addresses and a wait): HMult + rescale at N = 2^16, 24 limbs 83.5 -> 81.2 us
+// (row passes 1.1 of it), 25-30 system at 15 limbs 63.2 -> 60.9; 64 items of 4
+// to 24 limbs 2130 -> 2040 us, where KeyMult goes from 750 to 692 us (95
+// instead of 106 registers, no LDS).
+template <int LB>
+__device__ __forceinline__ void lane_swap(uint32_t& a, uint32_t& b)
+{
+    static_assert(LB >= 2 && LB <= 5, "lane bits 2..5");
+    if constexpr (LB >= 4) {
+        const auto r = LB == 5 ? __builtin_amdgcn_permlane32_swap(a, b, false, false)
+                               : __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        a = r[0], b = r[1];
+    } else {
+        constexpr int D = 1 << LB;                                   // partner's distance
+        constexpr int ZERO = LB == 3 ? 0x3 : 0x5, ONE = 0xF ^ ZERO;  // banks whose lane bit is 0 / 1
+        const uint32_t b0 = b;
+        b = (uint32_t)__builtin_amdgcn_update_dpp((int)b, (int)a, 0x100 + D, 0xF, ZERO, false);   // row_shl: lane + D
+        a = (uint32_t)__builtin_amdgcn_update_dpp((int)a, (int)b0, 0x110 + D, 0xF, ONE, false);   // row_shr: lane - D
+    }
+}
+// the two register bits of four points with lane bits LB + 1 and LB (LB even:
+// 4 and 2 here, 0 is quad_transpose)
+template <int LB>
+__device__ __forceinline__ void lane_exchange(uint32_t (&x)[4], int lane)
+{
+    if constexpr (LB == 0) {
+        quad_transpose(x, lane);
+    } else {
+        lane_swap<LB + 1>(x[0], x[2]);
+        lane_swap<LB + 1>(x[1], x[3]);
+        lane_swap<LB>(x[0], x[1]);
+        lane_swap<LB>(x[2], x[3]);
+    }
+}
+
 // Forward row pass of the row a wave holds: x[k] = row[t + 64 k] on entry,
 // row[4 t + k] on exit (forward values); tw[j][i]: round j's twiddles (stage 0,
-// then the two of stage 1).  The exchanges after rounds 0 and 1 go through
-// the wave's LDS row; between rounds 2 and 3 the 16 points of a quad of
-// lanes (lane a of quad m holds 16m + a + 4k, and needs 16m + 4a + k) change
-// places with a quad transpose in registers.  SYNC0: order the pass after a
-// previous pass over the same LDS row.
-template <bool W, bool SYNC0 = true>
-__device__ __forceinline__ void row4_fwd(uint32_t (&x)[4], const PrimeC& p, uint32_t* lds, int w, int t,
-                                         const int2 (&tw)[4][3])
+// then the two of stage 1).  Round j's register bits are point bits 7 - 2j and
+// 6 - 2j; the lane bits 5 - 2j and 4 - 2j hold the next round's, so the rounds
+// change places in registers.
+template <bool W>
+__device__ __forceinline__ void row4_fwd(uint32_t (&x)[4], const PrimeC& p, int t, const int2 (&tw)[4][3])
 {
-    if (SYNC0) wave_lds_sync();
 #pragma unroll
     for (int j = 0; j < 4; j++) {
-        const int sh = 6 - 2 * j, pp = t & ((1 << sh) - 1);
-        const int l0 = ((t >> sh) << (sh + 2)) + pp;
-        if (j == 3) {
-            quad_transpose(x, t);
-        } else if (j) {
-            wave_lds_sync();
-#pragma unroll
-            for (int k = 0; k < 4; k++) x[k] = lds[row4_lds(w, l0 + (k << sh))];
-        }
+        if (j == 1) lane_exchange<4>(x, t);
+        if (j == 2) lane_exchange<2>(x, t);
+        if (j == 3) lane_exchange<0>(x, t);
         ct_stages<2, W>(x, p, [&](int u, int b) { return tw[j][u ? 1 + b : 0]; });
-        if (j < 2) {
-#pragma unroll
-            for (int k = 0; k < 4; k++) lds[row4_lds(w, l0 + (k << sh))] = x[k];
-        }
     }
 }
 
 // Inverse row pass: x[k] = row[4 t + k] on entry, row[t + 64 k] on exit
-// (inverse range); tw[j][i] as in row4_fwd for round j of the inverse.  The
-// exchange between rounds 0 and 1 is the quad transpose (the forward pass's
-// last one, undone).
-template <bool W, bool SYNC0 = true>
-__device__ __forceinline__ void row4_inv(uint32_t (&x)[4], const PrimeC& p, uint32_t* lds, int w, int t,
-                                         const int2 (&tw)[4][3])
+// (inverse range); tw[j][i] as in row4_fwd for round j of the inverse; the
+// forward pass's exchanges undone.
+template <bool W>
+__device__ __forceinline__ void row4_inv(uint32_t (&x)[4], const PrimeC& p, int t, const int2 (&tw)[4][3])
 {
-    if (SYNC0) wave_lds_sync();
 #pragma unroll
     for (int j = 0; j < 4; j++) {
-        const int sh = 2 * j, pp = t & ((1 << sh) - 1);
-        const int l0 = ((t >> sh) << (sh + 2)) + pp;
-        if (j == 1) {
-            quad_transpose(x, t);
-        } else if (j) {
-            wave_lds_sync();
-#pragma unroll
-            for (int k = 0; k < 4; k++) x[k] = lds[row4_lds(w, l0 + (k << sh))];
-        }
+        if (j == 1) lane_exchange<0>(x, t);
+        if (j == 2) lane_exchange<2>(x, t);
+        if (j == 3) lane_exchange<4>(x, t);
         gs_stages<2, W, false>(x, p, [&](int u, int b) { return tw[j][u ? 1 + b : 0]; });
-        if (j >= 1 && j < 3) {
-#pragma unroll
-            for (int k = 0; k < 4; k++) lds[row4_lds(w, l0 + (k << sh))] = x[k];
-        }
     }
 }
 
@@ -573,7 +578,6 @@ __global__ void __launch_bounds__(NTT_THREADS) k_fwd_rows4(NttTables T, MS ms, L
     if (limb >= I.count) return;
     const Ld ld = ld0.at(blockIdx.z);
     const St st = st0.at(blockIdx.z);
-    __shared__ uint32_t lds[ROWS4 * ROW4_PITCH];
     const PrimeC pc = I.pc;
     const int t = threadIdx.x & 63, w = wave_id();
     const int h = blockIdx.x * ROWS4 + w;  // exact grid
@@ -585,7 +589,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_fwd_rows4(NttTables T, MS ms, L
     const auto pre = st.template prefetch<4>(M, limb, h * ROW + 4 * t);
     by_class(pc.q, [&](auto tag) {
         constexpr bool W = decltype(tag)::value;
-        row4_fwd<W, false>(x, pc, lds, w, t, tw);
+        row4_fwd<W>(x, pc, t, tw);
         st.template store_fwd<4, W>(M, limb, h * ROW + 4 * t, x, pc, pre);
     });
 }
@@ -601,7 +605,6 @@ __global__ void __launch_bounds__(NTT_THREADS) k_inv_rows4(NttTables T, MS ms, L
     if (limb >= I.count) return;
     const Ld ld = ld0.at(blockIdx.z);
     const St st = st0.at(blockIdx.z);
-    __shared__ uint32_t lds[ROWS4 * ROW4_PITCH];
     const PrimeC pc = I.pc;
     const int t = threadIdx.x & 63, w = wave_id();
     const int h = blockIdx.x * ROWS4 + w;
@@ -609,7 +612,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_inv_rows4(NttTables T, MS ms, L
     ld.template loadv<4>(M, limb, h * ROW + 4 * t, pc, x);
     int2 tw[4][3];
     row4_twiddles<LOG1, true>(T.tw + ((size_t)I.pid << T.log_n), pc.q, h, t, tw);
-    by_class(pc.q, [&](auto tag) { row4_inv<decltype(tag)::value, false>(x, pc, lds, w, t, tw); });
+    by_class(pc.q, [&](auto tag) { row4_inv<decltype(tag)::value>(x, pc, t, tw); });
 #pragma unroll
     for (int k = 0; k < 4; k++) st.store(M, limb, h * ROW + t + 64 * k, x[k], pc);
 }
@@ -618,8 +621,8 @@ __global__ void __launch_bounds__(NTT_THREADS) k_inv_rows4(NttTables T, MS ms, L
 // Column passes with 4 residues per thread.  256 threads hold a tile of
 // C = 1024 / 2^LOG1 columns; thread (c = tid % C, t = tid / C) holds four
 // points of column c.  Radix-4 rounds (plus one radix-2 round when LOG1 is
-// odd) exchange through LDS, one barrier per exchange: four times the waves
-// of the 16-residue passes.  In a radix-4 round with shift sh the thread's
+// odd) exchange once through LDS, across the waves, and then between registers
+// and lanes (col4_lane): four times the waves of the 16-residue passes.  In a radix-4 round with shift sh the thread's
 // points are base + k 2^sh, base = ((t >> sh) << (sh + 2)) | (t mod 2^sh);
 // the radix-2 round holds 4t + k.  The forward pass enters with points
 // t + k TC (TC = 2^LOG1 / 4) and leaves with 4t + k; the inverse pass the
@@ -694,6 +697,36 @@ __device__ __forceinline__ int2 col4_tw(const int2* twl, int t, int sh, int u, i
     return twl[(1 << (s0 + u)) + (blk << u) + b];
 }
 
+// Exchange before forward round J >= 2, or undone (INV) after the inverse of
+// that round.  Thread index t of a column is the wave's two bits and the lane
+// bits above the tile's columns; only the first exchange (point bits LOG1 - 3
+// and LOG1 - 4, held by the waves) crosses waves and goes through LDS.  Round
+// 2's point bits lie in lane bits 5 and 4, round 3's in 3 and 2; the radix-2
+// round of an odd LOG1 takes one, lane bit 5 (LOG1 = 5) or 3 (LOG1 = 7), for
+// the higher register bit, and then the register bits change places.
+template <int LOG1, int J, bool INV>
+__device__ __forceinline__ void col4_lane(uint32_t (&x)[4])
+{
+    using G = Col4<LOG1>;
+    if constexpr (J >= 2 && J < G::NR) {
+        if constexpr (G::fsh(J) >= 0) {
+            lane_exchange<J == 2 ? 4 : 2>(x, 0);  // its own inverse
+        } else {
+            constexpr int LB = LOG1 == 5 ? 5 : 3;
+            if constexpr (INV) {
+                const uint32_t y = x[1];
+                x[1] = x[2], x[2] = y;
+            }
+            lane_swap<LB>(x[0], x[2]);
+            lane_swap<LB>(x[1], x[3]);
+            if constexpr (!INV) {
+                const uint32_t y = x[1];
+                x[1] = x[2], x[2] = y;
+            }
+        }
+    }
+}
+
 // Forward column pass of NT targets held by the work-group: x[i] enters with
 // points t + k TC of column c, leaves with 4t + k (forward values); lds holds
 // one buffer of Col4::WORDS words per target (a round stores its results
@@ -708,12 +741,18 @@ __device__ __forceinline__ void col4_fwd(uint32_t (&x)[NT][4], const PrimeC (&p)
 #pragma unroll
     for (int j = 0; j < G::NR; j++) {
         const int sh = G::fsh(j), base = col4_base(t, sh), step = col4_step(sh);
-        if (j) {
+        if (j == 1) {
             __syncthreads();
 #pragma unroll
             for (int i = 0; i < NT; i++)
 #pragma unroll
                 for (int k = 0; k < 4; k++) x[i][k] = lds[i * G::WORDS + G::lds(base + k * step, c)];
+        } else if (j == 2) {
+#pragma unroll
+            for (int i = 0; i < NT; i++) col4_lane<LOG1, 2, false>(x[i]);
+        } else if (j == 3) {
+#pragma unroll
+            for (int i = 0; i < NT; i++) col4_lane<LOG1, 3, false>(x[i]);
         }
 #pragma unroll
         for (int i = 0; i < NT; i++) {
@@ -726,7 +765,7 @@ __device__ __forceinline__ void col4_fwd(uint32_t (&x)[NT][4], const PrimeC (&p)
                     ct_stages<2, W>(x[i], p[i], [&](int u, int b) { return col4_tw<LOG1>(tl, t, sh, u, b); });
             });
         }
-        if (j < G::NR - 1) {
+        if (j == 0) {
 #pragma unroll
             for (int i = 0; i < NT; i++)
 #pragma unroll
@@ -747,12 +786,16 @@ __device__ __forceinline__ void col4_inv(uint32_t (&x)[4], const PrimeC& p, uint
 #pragma unroll
     for (int j = 0; j < G::NR; j++) {
         const int sh = G::ish(j), base = col4_base(t, sh), step = col4_step(sh);
-        if (j) {
+        const bool last = j == G::NR - 1;
+        if (last) {
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < 4; k++) x[k] = lds[G::lds(base + k * step, c)];
+        } else if (j == 1) {
+            col4_lane<LOG1, G::NR - 1, true>(x);
+        } else if (j == 2) {
+            col4_lane<LOG1, G::NR - 2, true>(x);
         }
-        const bool last = j == G::NR - 1;
         auto tw = [&](int u, int b) { return col4_tw<LOG1>(twl, t, sh, u, b); };
         if (sh < 0) {
             gs_stages<1, W, false>(x, p, [&](int, int b) { return tw(0, b); });
@@ -761,7 +804,7 @@ __device__ __forceinline__ void col4_inv(uint32_t (&x)[4], const PrimeC& p, uint
         } else {
             gs_stages<2, W, false>(x, p, tw);
         }
-        if (!last) {
+        if (j == G::NR - 2) {
 #pragma unroll
             for (int k = 0; k < 4; k++) lds[G::lds(base + k * step, c)] = x[k];
         }
