@@ -160,6 +160,9 @@ struct Ctx {
     int32_t* rr2_mat = nullptr;
     int2* rr2_fin = nullptr;
     int rr2_c_off[MAX_PRIMES + 1] = {}, rr2_mat_off[MAX_PRIMES + 1] = {}, rr2_fin_off[MAX_PRIMES + 1] = {};
+    // ModUp's base conversions need no range fix at their end: n_p inputs of at
+    // most q_max / 2 times constants of at most t / 2 stay within t 2^31
+    int up_nofix = 0;
     // device copy of the per-level window data for batched launches (windowed
     // contexts): [4][MAX_PRIMES + 1] = wbase, rescaling's dropped rows (0: no
     // window below), rr_dlo, rr_dhi

@@ -350,6 +350,7 @@ struct BcRescale {
     const int32_t* pr;     // [n_q] centred [P R^-1]_{q_i}, indexed by target prime
     int n_p;
     int level;             // single operation: its level; batched: taken from the item
+    int nofix = 0;         // every sum of the launch stays within t 2^31 (Ctx::up_nofix)
 };
 
 struct BcByPtr {
@@ -524,13 +525,15 @@ __global__ void __launch_bounds__(CT) k_bconv_ntt_cols(NttTables T, BS bs, const
 // a fix and 4 more: |y| <= 2^30, |m| < t/2), and the rescaling's product adds
 // less than t 2^29: the reduction leaves |x| < (1 + 1/8 + 1/2) t < 2^31 for a
 // wide prime, a forward value as it is.  A 31-bit prime's forward values end
-// at q, which takes the sum within t 2^31.
+// at q, which takes the sum within t 2^31: it is there already when n_in input
+// primes' n_in (q_s / 2) (t / 2) is (ModUp of digits of up to 8 primes below
+// 2^30; nofix), otherwise a range fix takes it there.
 template <bool RS>
 __device__ __forceinline__ void bconv_reduce(const int64_t (&acc)[4], const int32_t (&tl)[RS ? 4 : 1], int64_t mp,
-                                             const PrimeC& p, uint32_t (&x)[4])
+                                             const PrimeC& p, bool nofix, uint32_t (&x)[4])
 {
     const int64_t t31 = (int64_t)p.q << 31, t32 = (int64_t)p.q << 32;
-    if (wide_prime(p.q)) {
+    if (wide_prime(p.q) || (!RS && nofix)) {
 #pragma unroll
         for (int k = 0; k < 4; k++) {
             int64_t a = acc[k];
@@ -686,7 +689,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_bconv_ntt_cols4(NttTables T, BS
     for (int i = 0; i < TPW; i++) {
         int64_t mp = 0;
         if constexpr (RS) mp = X.pr[B.pid[first + (i < n_tg ? i : 0)]];
-        bconv_reduce<RS>(acc[i], tl, mp, tp[i], x[i]);
+        bconv_reduce<RS>(acc[i], tl, mp, tp[i], X.nofix != 0, x[i]);
     }
     col4_fwd<LOG1, TPW>(x, tp, lds, twl, c, t);
 #pragma unroll
@@ -809,7 +812,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_inv_bconv_ntt_cols4(NttTables T
     for (int i = 0; i < TPW; i++) {
         int64_t mp = 0;
         if constexpr (RS) mp = X.pr[B.pid[first + (i < n_tg ? i : 0)]];
-        bconv_reduce<RS>(acc[i], tl, mp, tp[i], x[i]);
+        bconv_reduce<RS>(acc[i], tl, mp, tp[i], X.nofix != 0, x[i]);
     }
     __syncthreads();  // the last row's reads of lds are done
     col4_fwd<LOG1, TPW>(x, tp, lds, twl, c, t);
@@ -1167,28 +1170,10 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
     constexpr bool EXTRA = OWN == Own::Tensor && EX == Extra::HMult;
 
     [[maybe_unused]] const AutQuad quad((uint32_t)j0, A.galois, log_n);
-    // The digit whose own rows this row is (none for P rows); its input rows
-    // are requested at the start, every digit's key rows and ModUp row one
-    // digit ahead of their use.
+    // The digit whose own rows this row is (none for P rows).
     int jown = -1;
     for (int j = 0; j < beta; j++)
         if (r >= max(j * A.n_p - woff, 0) && r < min((j + 1) * A.n_p - woff, A.level)) jown = j;
-    uint32_t o0[4], o1[4], o2[4], o3[4];  // Tensor: a_a, a_b (and b_a, b_b for HMult); else the input row
-    if (jown >= 0) {
-        const size_t off = (size_t)r * n;
-        if constexpr (OWN == Own::Tensor) {
-            loadv_u32<4>(A.a0 + (off + hrow) + l4, o0);
-            loadv_u32<4>(A.a1 + (off + hrow) + l4, o1);
-            if constexpr (EXTRA) {
-                loadv_u32<4>(A.b0 + (off + hrow) + l4, o2);
-                loadv_u32<4>(A.b1 + (off + hrow) + l4, o3);
-            }
-        } else if constexpr (OWN == Own::Plain) {
-            loadv_u32<4>(A.a0 + (off + hrow) + l4, o0);
-        } else {  // Gather, Hoisted: phi_g(a)
-            quad.load(A.a0 + off, o0);
-        }
-    }
     struct Dig {
         uint32_t kb[4], ka[4], x[4];
     };
@@ -1212,10 +1197,10 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
         }
     };
     // digit j from cur; requests digit j + 1 into nxt first
-    auto step = [&](int j, Dig& cur, Dig& nxt) {
+    auto step = [&](int j, const uint32_t (&xo)[4], Dig& cur, Dig& nxt) {
         if (j + 1 < beta) issue(j + 1, nxt);
         const bool own = j == jown;
-        const int more = own || OWN == Own::Hoisted ? Sum::CANON + (EXTRA ? Sum::CANON : 0) : Sum::ROW;
+        const int more = own || OWN == Own::Hoisted ? Sum::CANON : Sum::ROW;
         if (terms + more > Sum::LIMIT) {  // uniform across the row
 #pragma unroll
             for (int k = 0; k < 4; k++) s0[k].fold(r1, q), s1[k].fold(r1, q);
@@ -1224,25 +1209,8 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
         terms += more;
         uint32_t x[4];
         if (own) {
-            if constexpr (OWN == Own::Tensor) {
-                if constexpr (EXTRA) {
-                    // P d0 and P d1 (d0 = b_a b_b, d1 = b_a a_b + a_a b_b) join the sums
-                    const uint32_t pq = A.p_mod_q[pid];
 #pragma unroll
-                    for (int k = 0; k < 4; k++) {
-                        const uint32_t d0 = mont(o2[k], o3[k], q, qinv);
-                        const uint32_t d1 = add_mod(mont(o2[k], o1[k], q, qinv), mont(o0[k], o3[k], q, qinv), q);
-                        s0[k].mac(d0, pq);
-                        s1[k].mac(d1, pq);
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < 4; k++) x[k] = mont(o0[k], o1[k], q, qinv);
-            } else {
-                const uint2 c = A.rinv[pid];
-#pragma unroll
-                for (int k = 0; k < 4; k++) x[k] = mulc(o0[k], c, q);
-            }
+            for (int k = 0; k < 4; k++) x[k] = xo[k];
         } else {
             if constexpr (OWN == Own::Hoisted) {
                 quad.arrange(make_uint4(cur.x[0], cur.x[1], cur.x[2], cur.x[3]), x);
@@ -1263,10 +1231,51 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
         }
     };
     Dig da, db;
-    issue(0, da);
+    // The row's own input is read first and taken at once: the own digit's
+    // operand stays (4 registers instead of 16), and P d0 and P d1 join the sums
+    // (d0 = b_a b_b, d1 = b_a a_b + a_a b_b) while digit 0's rows arrive.
+    uint32_t xo[4];
+    if (jown >= 0) {
+        const size_t off = (size_t)r * n + hrow;
+        uint32_t o0[4], o1[4], o2[4], o3[4];
+        if constexpr (OWN == Own::Tensor) {
+            loadv_u32<4>(A.a0 + off + l4, o0);
+            loadv_u32<4>(A.a1 + off + l4, o1);
+            if constexpr (EXTRA) {
+                loadv_u32<4>(A.b0 + off + l4, o2);
+                loadv_u32<4>(A.b1 + off + l4, o3);
+            }
+        } else if constexpr (OWN == Own::Plain) {
+            loadv_u32<4>(A.a0 + off + l4, o0);
+        } else {  // Gather, Hoisted: phi_g(a)
+            quad.load(A.a0 + (size_t)r * n, o0);
+        }
+        issue(0, da);
+        if constexpr (OWN == Own::Tensor) {
+            if constexpr (EXTRA) {
+                const uint32_t pq = A.p_mod_q[pid];
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const uint32_t d0 = mont(o2[k], o3[k], q, qinv);
+                    const uint32_t d1 = add_mod(mont(o2[k], o1[k], q, qinv), mont(o0[k], o3[k], q, qinv), q);
+                    s0[k].mac(d0, pq);
+                    s1[k].mac(d1, pq);
+                }
+                terms += Sum::CANON;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; k++) xo[k] = mont(o0[k], o1[k], q, qinv);
+        } else {
+            const uint2 c = A.rinv[pid];
+#pragma unroll
+            for (int k = 0; k < 4; k++) xo[k] = mulc(o0[k], c, q);
+        }
+    } else {
+        issue(0, da);
+    }
     for (int j = 0; j < beta; j += 2) {  // two digits per trip: the buffers swap roles without copies
-        step(j, da, db);
-        if (j + 1 < beta) step(j + 1, db, da);
+        step(j, xo, da, db);
+        if (j + 1 < beta) step(j + 1, xo, db, da);
     }
 
     uint32_t acc0[4], acc1[4];
@@ -1927,11 +1936,13 @@ static int modup_phase(const KsRun& R, Own own, const KsIn& in, size_t s0, size_
         }
         if (int e = launched("modup intt rows")) return e;
     }
+    BcRescale X{};
+    X.nofix = c.up_nofix;
     const int4* up_c = own == Own::Tensor ? c.up_c_r : c.up_c;
     if (!R.D && c4 && fuse_list(c, R.P->up_bc)) {
         KTimer t(c, "modup_cols", s);
         return launch_inv_bconv_list<false>(c, c.tpw_up, R.P->up_cols, R.P->up_bc, R.w0, up_c, c.up_mat, R.w2,
-                                            BcRescale{}, s);
+                                            X, s);
     }
     {
         LdPlain ld{R.w0, c.log_n, R.wst};
@@ -1943,8 +1954,8 @@ static int modup_phase(const KsRun& R, Own own, const KsIn& in, size_t s0, size_
     {
         KTimer t(c, "modup_bconv_ntt_cols", s);
         int e;
-        if (R.D) e = launch_bconv_ntt<false>(c, c.tpw_up, BcDir{R.D->up_bc, R.items, R.lo, R.hi, R.nk, R.ns}, R.g.up_bc, R.zn, R.w1, c.up_mat, R.w2, BcRescale{}, R.wst, R.items, s, c4);
-        else e = launch_bconv_list<false>(c, c.tpw_up, R.P->up_bc, R.w1, c.up_mat, R.w2, BcRescale{}, s, c4);
+        if (R.D) e = launch_bconv_ntt<false>(c, c.tpw_up, BcDir{R.D->up_bc, R.items, R.lo, R.hi, R.nk, R.ns}, R.g.up_bc, R.zn, R.w1, c.up_mat, R.w2, X, R.wst, R.items, s, c4);
+        else e = launch_bconv_list<false>(c, c.tpw_up, R.P->up_bc, R.w1, c.up_mat, R.w2, X, s, c4);
         if (e) return e;
     }
     return 0;
@@ -2546,6 +2557,9 @@ int build_plans(Ctx& c)
     auto planned = [&](int rs, int level) {
         return c.has_level(level) && (rs == 0 || (c.windowed ? c.rr_below[level] > 0 : level >= 2));
     };
+    uint64_t q_max = 0;
+    for (int i = 0; i < c.n_q; i++) q_max = std::max(q_max, c.mod[i]);
+    c.up_nofix = (uint64_t)c.n_p * q_max <= (1ull << 33) ? 1 : 0;
     Blob b;
     for (int rs = 0; rs < 2; rs++) {
         c.ks_plan[rs].assign(c.n_q + 1, KsPlan{});

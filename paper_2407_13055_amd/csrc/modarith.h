@@ -43,13 +43,15 @@ __device__ __forceinline__ uint32_t mulc(uint32_t x, uint32_t W, uint32_t Wt, ui
 
 __device__ __forceinline__ uint32_t mulc(uint32_t x, uint2 w, uint32_t q) { return mulc(x, w.x, w.y, q); }
 
-// a*b*2^-32 mod q for a*b < q*2^32 (e.g. both canonical).
+// a*b*2^-32 mod q for a*b < q*2^32 (e.g. both canonical): the 64-bit product
+// plus m q, m = -lo q^-1, is divisible by 2^32 with a quotient in [0, 2q)
+// (a product and two multiply-adds, one correction).
 __device__ __forceinline__ uint32_t mont(uint32_t a, uint32_t b, uint32_t q, uint32_t qinv)
 {
-    uint32_t lo = a * b;
-    uint32_t hi = __umulhi(a, b);
-    uint32_t t = __umulhi(lo * qinv, q);
-    return fix_signed(hi - t, q);
+    const uint64_t p = (uint64_t)a * b;
+    const uint32_t m = (uint32_t)p * (0u - qinv);
+    const uint32_t r = (uint32_t)((p + (uint64_t)m * q) >> 32);
+    return min(r, r - q);
 }
 
 // A prime as the kernels use it: q, q^-1 mod 2^32, -q mod 2^32, round(2^32 / q).
@@ -97,16 +99,16 @@ __device__ __forceinline__ uint32_t red2(uint32_t x, uint32_t m) { return min(x,
 // twisted companion of a Montgomery-form constant W
 __device__ __forceinline__ uint2 twist(uint32_t W, uint32_t qinv) { return make_uint2(W, W * qinv); }
 
-// Signed Montgomery reduction: r = x 2^-32 (mod t) with |r| < t, for odd
-// t < 2^31, tinv = t^-1 mod 2^32 and |x| <= t 2^31.
+// Signed Montgomery reduction: r = x 2^-32 (mod t) with |r| <= |x| / 2^32 +
+// t / 2, below t for |x| <= t 2^31; odd t < 2^31, tinv = t^-1 mod 2^32.
 // Why it works: m = x t^-1 mod 2^32, read as a signed 32-bit value, makes
-// x - m t divisible by 2^32; x and m t then share their low 32 bits, so the
-// exact quotient (x - m t) / 2^32 is the difference of their high halves.
-// |x / 2^32| <= t/2 and |m t / 2^32| <= t/2 bound it by t.
+// x - m t divisible by 2^32 and |m t| <= t 2^31.  One product and one 64-bit
+// multiply-add, whose high word is the quotient. (Two instructions; the high words
+// subtracted took eight, the compiler's 64-bit high product of a signed m.)
 __device__ __forceinline__ int32_t smr64(int64_t x, uint32_t t, uint32_t tinv)
 {
     const int32_t m = (int32_t)((uint32_t)x * tinv);
-    return (int32_t)(x >> 32) - __mulhi(m, (int32_t)t);
+    return (int32_t)((x + (int64_t)m * (int64_t)(0 - (int32_t)t)) >> 32);
 }
 
 // (-t, t) -> [0, t)

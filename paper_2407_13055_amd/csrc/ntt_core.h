@@ -647,6 +647,15 @@ struct Col4 {
     static constexpr int PA = LOG1 == 8 ? 12 : (LOG1 == 4 ? 0 : C);
     static constexpr int WORDS = S1 * C + PA * (S1 >> PS);  // one buffer
     __device__ static int lds(int p, int c) { return p * C + c + PA * (p >> PS); }
+    // words from point base to point base + k 2^sh, the same for every thread
+    // where a step is a multiple of the padding's 2^PS points (one address and
+    // constant offsets for a round's four accesses)
+    __host__ __device__ static constexpr bool fixed(int sh) { return PA == 0 || sh >= PS; }
+    __host__ __device__ static constexpr int stride(int sh) { return (C << sh) + (PA == 0 ? 0 : PA * ((1 << sh) >> PS)); }
+    __device__ static int lds_k(int base, int sh, int k, int c)
+    {
+        return fixed(sh) ? lds(base, c) + k * stride(sh) : lds(base + (k << sh), c);
+    }
     // shift of forward round j (-1: the radix-2 round) and of inverse round j
     __host__ __device__ static constexpr int fsh(int j) { return j < NR4 ? LOG1 - 2 - 2 * j : -1; }
     __host__ __device__ static constexpr int ish(int j) { return ODD ? (j == 0 ? -1 : 1 + 2 * (j - 1)) : 2 * j; }
@@ -660,7 +669,6 @@ __device__ __forceinline__ int tile_run(int col, int t)
     return (col / G::C) * G::TILE + (t * G::C + col % G::C) * 4;
 }
 __device__ __forceinline__ int col4_base(int t, int sh) { return sh < 0 ? 4 * t : (((t >> sh) << (sh + 2)) | (t & ((1 << sh) - 1))); }
-__device__ __forceinline__ int col4_step(int sh) { return sh < 0 ? 1 : 1 << sh; }
 
 // Column tile of a 4-residue column work-group: as col_tile, the tiles that
 // share a 128-byte line run on one XCD.
@@ -740,13 +748,13 @@ __device__ __forceinline__ void col4_fwd(uint32_t (&x)[NT][4], const PrimeC (&p)
     using G = Col4<LOG1>;
 #pragma unroll
     for (int j = 0; j < G::NR; j++) {
-        const int sh = G::fsh(j), base = col4_base(t, sh), step = col4_step(sh);
+        const int sh = G::fsh(j), base = col4_base(t, sh);
         if (j == 1) {
             __syncthreads();
 #pragma unroll
             for (int i = 0; i < NT; i++)
 #pragma unroll
-                for (int k = 0; k < 4; k++) x[i][k] = lds[i * G::WORDS + G::lds(base + k * step, c)];
+                for (int k = 0; k < 4; k++) x[i][k] = lds[i * G::WORDS + G::lds_k(base, sh, k, c)];
         } else if (j == 2) {
 #pragma unroll
             for (int i = 0; i < NT; i++) col4_lane<LOG1, 2, false>(x[i]);
@@ -769,7 +777,7 @@ __device__ __forceinline__ void col4_fwd(uint32_t (&x)[NT][4], const PrimeC (&p)
 #pragma unroll
             for (int i = 0; i < NT; i++)
 #pragma unroll
-                for (int k = 0; k < 4; k++) lds[i * G::WORDS + G::lds(base + k * step, c)] = x[i][k];
+                for (int k = 0; k < 4; k++) lds[i * G::WORDS + G::lds_k(base, sh, k, c)] = x[i][k];
         }
     }
 }
@@ -785,12 +793,12 @@ __device__ __forceinline__ void col4_inv(uint32_t (&x)[4], const PrimeC& p, uint
     using G = Col4<LOG1>;
 #pragma unroll
     for (int j = 0; j < G::NR; j++) {
-        const int sh = G::ish(j), base = col4_base(t, sh), step = col4_step(sh);
+        const int sh = G::ish(j), base = col4_base(t, sh);
         const bool last = j == G::NR - 1;
         if (last) {
             __syncthreads();
 #pragma unroll
-            for (int k = 0; k < 4; k++) x[k] = lds[G::lds(base + k * step, c)];
+            for (int k = 0; k < 4; k++) x[k] = lds[G::lds_k(base, sh, k, c)];
         } else if (j == 1) {
             col4_lane<LOG1, G::NR - 1, true>(x);
         } else if (j == 2) {
@@ -806,7 +814,7 @@ __device__ __forceinline__ void col4_inv(uint32_t (&x)[4], const PrimeC& p, uint
         }
         if (j == G::NR - 2) {
 #pragma unroll
-            for (int k = 0; k < 4; k++) lds[G::lds(base + k * step, c)] = x[k];
+            for (int k = 0; k < 4; k++) lds[G::lds_k(base, sh < 0 ? 0 : sh, k, c)] = x[k];
         }
     }
 }
