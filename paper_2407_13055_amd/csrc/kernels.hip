@@ -151,6 +151,31 @@ struct LdPlain {
     {
         loadv_u32<E>(base + ((size_t)M.in_off[l] << log_n) + j, x);
     }
+    static constexpr bool kQuads = false;
+    template <class LM>
+    __device__ uint32_t load_rc(const LM& M, int l, int h, int col) const
+    {
+        return base[((size_t)M.in_off[l] << log_n) + (size_t)h * ROW + col];
+    }
+};
+
+// a forward column pass's output (quad_row)
+struct LdQuads {
+    static constexpr bool kQuads = true;
+    const uint32_t* base;
+    int log_n;
+    size_t step = 0;
+    __device__ LdQuads at(int i) const
+    {
+        LdQuads r = *this;
+        r.base += (size_t)i * step;
+        return r;
+    }
+    template <class LM>
+    __device__ uint32_t load_rc(const LM& M, int l, int h, int col) const
+    {
+        return (base + (((size_t)M.in_off[l] << log_n) + quad_row(h)))[4 * col];
+    }
 };
 
 // the digit's own rows: a_a*a_b*2^-32 (HMult), d (KeySwitch), phi_g(a) (HRot)
@@ -199,7 +224,7 @@ struct LdOwn {
 // storers
 // ---------------------------------------------------------------------------
 struct StPlain {
-    static constexpr bool kTileThread = false;
+    static constexpr bool kTileThread = false, kInPlace = true;
     uint32_t* base;
     const int4* fc;  // final constant table (inverse passes), row cidx[l]
     int log_n;
@@ -270,7 +295,7 @@ struct StLift {
 // v is a forward value: centred, its difference with the canonical sub lies
 // in (-q, 2q) of a wide prime or (-q, q) of a 31-bit one, an operand of mulr.
 struct StCombine {
-    static constexpr bool kTileThread = false;
+    static constexpr bool kTileThread = false, kInPlace = false;
     uint32_t* out0;
     uint32_t* out1;
     const uint32_t* sub;
@@ -494,7 +519,7 @@ __global__ void __launch_bounds__(CT) k_bconv_ntt_cols(NttTables T, BS bs, const
         }
 #pragma unroll
         for (int k = 0; k < 16; k++) x[k] = (uint32_t)smr64(range_fix(acc[t][k], t31[t], t32[t]), q, qinv);
-        uint32_t* dst = out + (size_t)B.out_off[tg] * n + col;
+        uint32_t* dst = out + (size_t)B.out_off[tg] * n + 4 * col;
         by_class(q, [&](auto tag) {
             constexpr bool W = decltype(tag)::value;
             ct_stages<4, W>(x, pc, [&](int u, int b) { return tw[(1 << u) + b]; });
@@ -510,12 +535,11 @@ __global__ void __launch_bounds__(CT) k_bconv_ntt_cols(NttTables T, BS bs, const
                 });
             }
         });
-        if constexpr (G::NS2 > 0) {
+        // rows 16 r + k (a column of 16 points: r = 0), in row groups of four
 #pragma unroll
-            for (int k = 0; k < 16; k++) dst[(16 * r + k) * ROW] = x[k];
-        } else {
-#pragma unroll
-            for (int k = 0; k < 16; k++) dst[(r + G::R * k) * ROW] = x[k];
+        for (int m = 0; m < 4; m++) {
+            const uint32_t v[4] = {x[4 * m], x[4 * m + 1], x[4 * m + 2], x[4 * m + 3]};
+            storev_u32<4>(dst + quad_row(16 * r + 4 * m), v);
         }
     }
 }
@@ -695,9 +719,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_bconv_ntt_cols4(NttTables T, BS
 #pragma unroll
     for (int i = 0; i < TPW; i++) {
         if (i >= n_tg) break;
-        uint32_t* dst = out + (size_t)B.out_off[first + i] * n + col;
-#pragma unroll
-        for (int k = 0; k < 4; k++) dst[(size_t)(4 * t + k) * ROW] = x[i][k];
+        storev_u32<4>(out + (size_t)B.out_off[first + i] * n + (quad_row(4 * t) + 4 * col), x[i]);
     }
 }
 
@@ -819,9 +841,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_inv_bconv_ntt_cols4(NttTables T
 #pragma unroll
     for (int i = 0; i < TPW; i++) {
         if (i >= n_tg) break;
-        uint32_t* dst = out + (size_t)B.out_off[first + i] * n + col;
-#pragma unroll
-        for (int k = 0; k < 4; k++) dst[(size_t)(4 * t + k) * ROW] = x[i][k];
+        storev_u32<4>(out + (size_t)B.out_off[first + i] * n + (quad_row(4 * t) + 4 * col), x[i]);
     }
 }
 
@@ -975,7 +995,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult(NttTables Tf, NttTables
     const int pid = r < A.level ? A.base + r : A.n_q + (r - A.level);  // also the key row
     const PrimeC pc = Tf.prime(pid);
     const uint32_t q = pc.q, qinv = pc.qinv;
-    const int rp = threadIdx.x % 16, rr = threadIdx.x / 16;
+    const int rp = (threadIdx.x >> 2) & 15, rr = (int)((threadIdx.x & 3) | (threadIdx.x >> 6 << 2));  // as k_fwd_rows
     const int h = blockIdx.x * ROWS_PER_WG + rr;
     const int j0 = h * ROW + 16 * rp;
     const size_t n = (size_t)1 << log_n;
@@ -1037,9 +1057,9 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult(NttTables Tf, NttTables
 #pragma unroll
             for (int k = 0; k < 16; k += 4) AutQuad(j0 + k, A.galois, log_n).load(src, x + k);
         } else {
-            const uint32_t* src = A.up + (size_t)(j * rows + r) * n + (size_t)h * ROW;
+            const uint32_t* src = A.up + (size_t)(j * rows + r) * n + quad_row(h);
 #pragma unroll
-            for (int k = 0; k < 16; k++) x[k] = src[rp + 16 * k];
+            for (int k = 0; k < 16; k++) x[k] = src[4 * (rp + 16 * k)];
             by_class(q, [&](auto tag) {
                 constexpr bool W = decltype(tag)::value;
                 ct_stages<4, W>(x, pc, [&](int u, int b) { return row_tw1(tws, rr, u, b); });
@@ -1191,9 +1211,9 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
         if constexpr (OWN == Own::Hoisted) {  // ModUp row already in the evaluation domain: gather phi_g
             loadv_u32<4>(A.up + (size_t)(j * rows + r) * n + quad.off, d.x);
         } else {
-            const uint32_t* src = A.up + (size_t)(j * rows + r) * n + (size_t)h * ROW;
+            const uint32_t* src = A.up + (size_t)(j * rows + r) * n + quad_row(h);
 #pragma unroll
-            for (int k = 0; k < 4; k++) d.x[k] = src[t + 64 * k];
+            for (int k = 0; k < 4; k++) d.x[k] = src[l4 + 256u * k];
         }
     };
     // digit j from cur; requests digit j + 1 into nxt first
@@ -2002,7 +2022,7 @@ static int moddown_phase(const KsRun& R, int level, bool rescale, uint32_t* out0
     }
     }
     {
-        LdPlain ld{R.w2, c.log_n, R.wst};
+        LdQuads ld{R.w2, c.log_n, R.wst};
         StCombine st{out0, out1, R.w3, rr ? c.rr_fin : rescale ? c.rs_fin : c.dn_pinv, c.log_n, out_step, R.wst};
         KTimer t(c, "moddown_ntt_rows_combine", s);
         KS_MAP(R, dn_rows, CKKS_DISPATCH_LOG1(log1, (fwd_rows<L1>(c, ms, R.g.dn_rows, ld, st, s, R.zn))));
@@ -2110,7 +2130,7 @@ int launch_hrot_hoisted(const Ctx& c, const uint32_t* b_in, const uint32_t* a_in
     in.a0 = a_in;
     if (int e = modup_phase(U, Own::Plain, in, 0, 0, s)) return e;
     {  // complete the ModUp rows in the evaluation domain (row pass in place)
-        LdPlain ld{U.w2, c.log_n};
+        LdQuads ld{U.w2, c.log_n};
         StPlain st{U.w2, nullptr, c.log_n};
         KTimer t(c, "modup_ntt_rows", s);
         CKKS_DISPATCH_LOG1(log1, (fwd_rows<L1>(c, MapByPtr{P.up_nrows.dev}, P.up_nrows.n, ld, st, s)));
@@ -2164,7 +2184,7 @@ int launch_hrot_sum_hoisted(const Ctx& c, const uint32_t* b_in, const uint32_t* 
     in.a0 = a_in;
     if (int e = modup_phase(U, Own::Plain, in, 0, 0, s)) return e;
     {
-        LdPlain ld{U.w2, c.log_n};
+        LdQuads ld{U.w2, c.log_n};
         StPlain st{U.w2, nullptr, c.log_n};
         KTimer t(c, "modup_ntt_rows", s);
         CKKS_DISPATCH_LOG1(log1, (fwd_rows<L1>(c, MapByPtr{P.up_nrows.dev}, P.up_nrows.n, ld, st, s)));
@@ -2227,7 +2247,7 @@ int launch_rescale(const Ctx& c, const uint32_t* in, int level_in, uint32_t* out
             return e;
     }
     {
-        LdPlain ld{w2, c.log_n};
+        LdQuads ld{w2, c.log_n};
         StCombine st{out, out + (size_t)(level_in - 1) * c.n, in, c.rs_qinv, c.log_n};
         KTimer t(c, "rescale_ntt_rows_combine", s);
         CKKS_DISPATCH_LOG1(log1, (fwd_rows<L1>(c, ptr(P.nrows), P.nrows.n, ld, st, s)));
@@ -2526,7 +2546,7 @@ int launch_rescale_rational_window(const Ctx& c, int level, const uint32_t* ct, 
         if (int e = launch_bconv_list<false>(c, RS_TPW, P.bc, w1, c.rr2_mat, w2, BcRescale{}, s, true)) return e;
     }
     {
-        LdPlain ld{w2, c.log_n};
+        LdQuads ld{w2, c.log_n};
         StCombine st{out, out + (size_t)below * n, ct, c.rr2_fin, c.log_n};
         KTimer t(c, "rr_ntt_rows_combine", s);
         CKKS_DISPATCH_LOG1(log1, (fwd_rows<L1>(c, MapByPtr{P.nrows.dev}, P.nrows.n, ld, st, s)));

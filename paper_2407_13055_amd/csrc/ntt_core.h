@@ -31,6 +31,19 @@ constexpr int ROW = 1 << ROW_LOG;
 constexpr int NTT_THREADS = 256;
 constexpr int ROWS_PER_WG = NTT_THREADS / 16;  // row pass: 16 threads per row
 
+// Layout of a forward column pass's output inside key switching and
+// rescaling: rows in groups of four, a group column by column (element (h, l)
+// at 1024 (h / 4) + 4 l + h mod 4).  A column pass leaves four consecutive rows
+// of a column in a thread: one 16-byte store, 64 contiguous bytes per tile and
+// row group, where row-major rows took four stores of 16 bytes per tile, each a
+// request of its own to the L2 (nearly three quarters of the requests of a
+// batch's conversions).  The row pass reads a row with a stride of 16 bytes,
+// and its work-group's other rows find the same lines in the L1.
+// N = 2^16: the conversions of 64 items of 4 to 24 limbs 359 -> 303 and 292 ->
+// 243 us, their combine 259 -> 286, the batch 2024 -> 1968; one HMult + rescale
+// at 24 limbs 80.2 -> 78.1, 25-30 system at 15 limbs 60.7 -> 59.2.
+__host__ __device__ constexpr int quad_row(int h) { return ((h >> 2) << (ROW_LOG + 2)) + (h & 3); }
+
 // ---------------------------------------------------------------------------
 // Butterflies.  Twiddles are centred pairs (w, round(w 2^32 / q)) and a
 // product (mulr) lands in (-3q/4, 3q/4) for any signed 32-bit operand.  Two
@@ -358,11 +371,14 @@ __global__ void __launch_bounds__(NTT_THREADS) k_fwd_rows(NttTables T, MS ms, Ld
     const int limb = blockIdx.y, pid = M.pid[limb];
     const PrimeC pc = T.prime(pid);
     const TwTable tw{T.tw + ((size_t)pid << T.log_n), pc.q};
-    const int rp = threadIdx.x % 16, rr = threadIdx.x / 16;
+    // a wave holds four rows; in row groups of four its neighbouring lanes are
+    // the four rows of one column, so that a load is contiguous
+    const int rp = Ld::kQuads ? (threadIdx.x >> 2) & 15 : threadIdx.x % 16;
+    const int rr = Ld::kQuads ? (int)((threadIdx.x & 3) | (threadIdx.x >> 6 << 2)) : threadIdx.x / 16;
     const int h = blockIdx.x * ROWS_PER_WG + rr;  // 2^LOG1 rows, LOG1 >= 4: exact grid
     uint32_t x[16];
 #pragma unroll
-    for (int k = 0; k < 16; k++) x[k] = ld.load(M, limb, h * ROW + rp + 16 * k, pc);
+    for (int k = 0; k < 16; k++) x[k] = ld.load_rc(M, limb, h, rp + 16 * k);
     by_class(pc.q, [&](auto tag) {
         constexpr bool W = decltype(tag)::value;
         ct_stages<4, W>(x, pc, [&](int u, int b) { return tw[(1 << (LOG1 + u)) + (h << u) + b]; });
@@ -583,7 +599,8 @@ __global__ void __launch_bounds__(NTT_THREADS) k_fwd_rows4(NttTables T, MS ms, L
     const int h = blockIdx.x * ROWS4 + w;  // exact grid
     uint32_t x[4];
 #pragma unroll
-    for (int k = 0; k < 4; k++) x[k] = ld.load(M, limb, h * ROW + t + 64 * k, pc);
+    for (int k = 0; k < 4; k++) x[k] = ld.load_rc(M, limb, h, t + 64 * k);
+    if constexpr (Ld::kQuads && St::kInPlace) __syncthreads();  // the rows of a group are read before one is written
     int2 tw[4][3];
     row4_twiddles<LOG1, false>(T.tw + ((size_t)I.pid << T.log_n), pc.q, h, t, tw);
     const auto pre = st.template prefetch<4>(M, limb, h * ROW + 4 * t);
