@@ -1337,6 +1337,322 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
 }
 
 // ---------------------------------------------------------------------------
+// Key switching at N = 2^12 in four launches.  A limb is 16 KB, so one
+// work-group of 16 waves holds a whole transform: its 16 rows are the waves'
+// (one-wave-per-row passes), its columns of 16 points are a thread's each (four
+// waves, one radix-16 round), with LDS between the two.  The sequence is
+//   k_small_intt      ModUp's INTT of a limb, lifted
+//   k_small_modup     a digit's conversion to one row and its NTT
+//   k_small_keymult   a row of one polynomial over all digits; P rows (and
+//                     dropped ones) go on to ModDown's lifted INTT
+//   k_small_moddown   an output row's conversion, NTT and combine
+// Nothing is large here: a dependent launch costs about 3.5 us and a
+// transform's chain about as much, so the number of launches (seven, or five
+// with narrow digits) was the time.  One launch for conversions and KeyMult
+// (a row's digits and both polynomials in one work-group) took 15.6 us against
+// the two launches' 10: a row's chain is issued by one CU.  HMult + rescale,
+// seven launches -> four: 24 limbs in three digits 29.5 -> 25.4 us, 8 limbs in
+// two 28.8 -> 23.0; HRot 29.1 -> 23.4 and 28.5 -> 21.4.  At N = 2^13 a limb's
+// chain on one CU is twice as long, about what the launches cost: the general
+// sequence stays.  Lifted limbs are row-major.
+// ---------------------------------------------------------------------------
+constexpr int SM_LOG1 = 4, SM_LOG_N = SM_LOG1 + ROW_LOG, SM_ROWS = 1 << SM_LOG1, SM_THREADS = 64 * SM_ROWS;
+constexpr int SM_N = 1 << SM_LOG_N;
+
+// the 15 twiddles of a 16-point column (the same in every thread), requested
+// with a kernel's other operands, ahead of its first barrier
+struct SmallColTw {
+    int32_t w[SM_ROWS - 1];
+    uint32_t q;
+    __device__ __forceinline__ SmallColTw(const int32_t* tw, uint32_t q_) : q(q_)
+    {
+#pragma unroll
+        for (int i = 0; i < SM_ROWS - 1; i++) w[i] = tw[1 + i];
+    }
+    __device__ __forceinline__ int2 operator()(int u, int b) const { return const_from_quot(w[(1 << u) - 1 + b], q); }
+};
+
+// inverse column of 16 points in a thread (rows k of column c), constant folded, canonical
+template <bool W>
+__device__ __forceinline__ void small_inv_col(const uint32_t* buf, int c, const PrimeC& pc, const SmallColTw& tw, int4 cst,
+                                              uint32_t (&y)[16])
+{
+#pragma unroll
+    for (int k = 0; k < 16; k++) y[k] = buf[k * ROW + c];
+    gs_stages<4, W, true>(y, pc, tw, cst);
+}
+template <bool W>
+__device__ __forceinline__ void small_fwd_col(uint32_t* buf, int c, const PrimeC& pc, const SmallColTw& tw)
+{
+    uint32_t y[16];
+#pragma unroll
+    for (int k = 0; k < 16; k++) y[k] = buf[k * ROW + c];
+    ct_stages<4, W>(y, pc, tw);
+#pragma unroll
+    for (int k = 0; k < 16; k++) buf[k * ROW + c] = y[k];
+}
+__device__ __forceinline__ void small_store_lifted(int32_t* dst, int c, const uint32_t (&y)[16], uint32_t q)
+{
+#pragma unroll
+    for (int k = 0; k < 16; k++) dst[k * ROW + c] = lift(y[k], q);
+}
+
+// n_in products of lifted rows y (SM_N apart) with constants m, four residues
+// from index e on: range fixes after 8 products, then every 4
+__device__ __forceinline__ void small_bconv_sums(const int32_t* y, int e, int n_in, const int32_t* m, uint32_t q,
+                                                 int64_t (&acc)[4])
+{
+#pragma unroll
+    for (int k = 0; k < 4; k++) acc[k] = 0;
+    for (int s0 = 0; s0 < n_in; s0 += 4) {
+        uint32_t v[4][4];
+        int32_t mv[4];
+#pragma unroll
+        for (int s = 0; s < 4; s++) {  // past the inputs: the last row again, times zero (BCONV_MAT_PAD)
+            loadv_u32<4>(reinterpret_cast<const uint32_t*>(y) + (size_t)min(s0 + s, n_in - 1) * SM_N + e, v[s]);
+            const int32_t c = m[s0 + s];
+            mv[s] = s0 + s < n_in ? c : 0;
+        }
+        if (s0 >= 8) {
+#pragma unroll
+            for (int k = 0; k < 4; k++) acc[k] = range_fix(acc[k], (int64_t)q << 31, (int64_t)q << 32);
+        }
+#pragma unroll
+        for (int s = 0; s < 4; s++)
+#pragma unroll
+            for (int k = 0; k < 4; k++) acc[k] += (int64_t)(int32_t)v[s][k] * (int64_t)mv[s];
+    }
+}
+
+template <Own OWN>
+__global__ void __launch_bounds__(SM_THREADS) k_small_intt(NttTables T, const LaunchMap* Mr, const LaunchMap* Mc,
+                                                           LdOwn<OWN> ld, const int4* fc, int32_t* out)
+{
+    __shared__ uint32_t buf[SM_N];
+    const int limb = blockIdx.x, pid = Mr->pid[limb];
+    const PrimeC pc = T.prime(pid);
+    const int t = threadIdx.x & 63, h = wave_id();
+    const int32_t* twt = T.tw + (size_t)pid * SM_N;
+    const SmallColTw tw(twt, pc.q);
+    uint32_t x[4];
+    ld.template loadv<4>(*Mr, limb, h * ROW + 4 * t, pc, x);
+    int2 twr[4][3];
+    row4_twiddles<SM_LOG1, true>(twt, pc.q, h, t, twr);
+    const int4 cst = fc[Mc->cidx[limb]];
+    by_class(pc.q, [&](auto tag) {
+        constexpr bool W = decltype(tag)::value;
+        row4_inv<W>(x, pc, t, twr);
+#pragma unroll
+        for (int k = 0; k < 4; k++) buf[h * ROW + t + 64 * k] = x[k];
+        __syncthreads();
+        if (h < ROW / 64) {
+            uint32_t y[16];
+            small_inv_col<W>(buf, threadIdx.x, pc, tw, cst, y);
+            small_store_lifted(out + (size_t)limb * SM_N, threadIdx.x, y, pc.q);
+        }
+    });
+}
+
+// digit blockIdx.y to row blockIdx.x of the level (own rows: nothing to do);
+// out: evaluation domain, digit j's row r at (j rows + r)
+struct SmallUp {
+    const int32_t* y;      // lifted limbs of the level
+    const int32_t* mat;    // constants of the level: digit jk, prime pid at (jk n_primes + pid) n_p
+    uint32_t* out;
+    int level, base, n_q, n_p, n_primes, nofix;
+};
+__global__ void __launch_bounds__(SM_THREADS) k_small_modup(NttTables T, SmallUp U)
+{
+    __shared__ uint32_t buf[SM_N];
+    const int r = blockIdx.x, j = blockIdx.y;
+    const int woff = U.base % U.n_p, kd = U.base / U.n_p;
+    const int lo = max(j * U.n_p - woff, 0), hi = min((j + 1) * U.n_p - woff, U.level);
+    if (r >= lo && r < hi) return;
+    const int pid = r < U.level ? U.base + r : U.n_q + (r - U.level);
+    const PrimeC pc = T.prime(pid);
+    const int t = threadIdx.x & 63, h = wave_id(), e = h * ROW + 4 * t;
+    const int32_t* twt = T.tw + (size_t)pid * SM_N;
+    const SmallColTw tw(twt, pc.q);
+    int2 twr[4][3];
+    row4_twiddles<SM_LOG1, false>(twt, pc.q, h, t, twr);
+    int64_t acc[4];
+    small_bconv_sums(U.y + (size_t)lo * SM_N, e, hi - lo, U.mat + ((size_t)(kd + j) * U.n_primes + pid) * U.n_p, pc.q, acc);
+    uint32_t x[4];
+    const int32_t none[1] = {0};
+    bconv_reduce<false>(acc, none, 0, pc, U.nofix != 0, x);
+    storev_u32<4>(buf + e, x);
+    __syncthreads();
+    by_class(pc.q, [&](auto tag) {
+        constexpr bool W = decltype(tag)::value;
+        if (h < ROW / 64) small_fwd_col<W>(buf, threadIdx.x, pc, tw);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; k++) x[k] = buf[h * ROW + t + 64 * k];
+        row4_fwd<W>(x, pc, t, twr);
+#pragma unroll
+        for (int k = 0; k < 4; k++) x[k] = fwd_canon<W>(x[k], pc);
+    });
+    storev_u32<4>(U.out + (size_t)(j * (U.level + U.n_p) + r) * SM_N + e, x);
+}
+
+// row blockIdx.x of polynomial blockIdx.y (k_keymult4's sums over evaluation-
+// domain rows); dn: ModDown's INTT column map, the constant of slot k at cidx[k]
+template <Own OWN, Extra EX>
+__global__ void __launch_bounds__(SM_THREADS) k_small_keymult(NttTables Ti, KmArgs A, const LaunchMap* dn, const int4* fc,
+                                                              int32_t* dn_y)
+{
+    __shared__ uint32_t buf[SM_N];
+    const int rows = A.level + A.n_p, key_rows = A.n_q + A.n_p;
+    const int r = blockIdx.x, poly = blockIdx.y;
+    const int woff = A.base % A.n_p, kd = A.base / A.n_p;
+    const int beta = (woff + A.level + A.n_p - 1) / A.n_p;
+    const int pid = r < A.level ? A.base + r : A.n_q + (r - A.level);
+    const PrimeC pc = Ti.prime(pid);
+    const uint32_t q = pc.q, qinv = pc.qinv;
+    const int t = threadIdx.x & 63, h = wave_id(), e = h * ROW + 4 * t;
+    const int32_t* twt = Ti.tw + (size_t)pid * SM_N;
+    const SmallColTw tw(twt, q);
+    const uint2 r1 = A.r1[pid];
+    const int dhi = A.dhi < 0 ? A.level - 1 : A.dhi;
+    const bool dropped = A.rs && r < A.level && (r < A.dlo || r >= dhi);
+    by_class(q, [&](auto tag) {
+        constexpr bool W = decltype(tag)::value;
+        using Sum = KmSum<W>;
+        Sum s[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) s[k].s = 0;
+        int terms = 0;
+        auto room = [&](int more) {  // uniform across the work-group
+            if (terms + more > Sum::LIMIT) {
+#pragma unroll
+                for (int k = 0; k < 4; k++) s[k].fold(r1, q);
+                terms = 1;
+            }
+            terms += more;
+        };
+        for (int j = 0; j < beta; j++) {
+            uint32_t key[4], x[4];
+            loadv_u32<4>(A.evk + ((size_t)(2 * (kd + j) + poly) * key_rows + pid) * SM_N + e, key);
+            if (r >= max(j * A.n_p - woff, 0) && r < min((j + 1) * A.n_p - woff, A.level)) {  // the digit's own row
+                const size_t off = (size_t)r * SM_N + e;
+                if constexpr (OWN == Own::Tensor) {
+                    uint32_t a0[4], a1[4];
+                    loadv_u32<4>(A.a0 + off, a0);
+                    loadv_u32<4>(A.a1 + off, a1);
+                    if constexpr (EX == Extra::HMult) {  // P d0 or P d1, as k_keymult4
+                        uint32_t b0[4], b1[4];
+                        loadv_u32<4>(A.b0 + off, b0);
+                        loadv_u32<4>(A.b1 + off, b1);
+                        const uint32_t pq = A.p_mod_q[pid];
+                        room(Sum::CANON);
+#pragma unroll
+                        for (int k = 0; k < 4; k++)
+                            s[k].mac(poly ? add_mod(mont(b0[k], a1[k], q, qinv), mont(a0[k], b1[k], q, qinv), q)
+                                          : mont(b0[k], b1[k], q, qinv), pq);
+                    }
+#pragma unroll
+                    for (int k = 0; k < 4; k++) x[k] = mont(a0[k], a1[k], q, qinv);
+                } else {
+                    if constexpr (OWN == Own::Plain) loadv_u32<4>(A.a0 + off, x);
+                    else AutQuad((uint32_t)e, A.galois, SM_LOG_N).load(A.a0 + (size_t)r * SM_N, x);
+                    const uint2 ri = A.rinv[pid];
+#pragma unroll
+                    for (int k = 0; k < 4; k++) x[k] = mulc(x[k], ri, q);
+                }
+            } else {
+                loadv_u32<4>(A.up + (size_t)(j * rows + r) * SM_N + e, x);
+            }
+            room(Sum::CANON);
+#pragma unroll
+            for (int k = 0; k < 4; k++) s[k].mac(x[k], key[k]);
+        }
+        uint32_t acc[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) acc[k] = s[k].reduce(q, qinv);
+        if constexpr (EX == Extra::HRot) {
+            if (r < A.level && poly == 0) {
+                const uint2 cb = A.p_r2[pid];
+                uint32_t x[4];
+                AutQuad((uint32_t)e, A.galois, SM_LOG_N).load(A.b0 + (size_t)r * SM_N, x);
+#pragma unroll
+                for (int k = 0; k < 4; k++) acc[k] = add_mod(acc[k], mulc(x[k], cb, q), q);
+            }
+        }
+        if (r < A.level && !dropped) {
+            storev_u32<4>(A.ks_q + ((size_t)poly * A.level + r) * SM_N + e, acc);
+            return;
+        }
+        const int slot = r >= A.level ? r - A.level : A.n_p + (r < A.dlo ? r : A.dlo + (r - dhi));
+        int2 twr[4][3];
+        row4_twiddles<SM_LOG1, true>(twt, q, h, t, twr);
+        row4_inv<W>(acc, pc, t, twr);
+#pragma unroll
+        for (int k = 0; k < 4; k++) buf[h * ROW + t + 64 * k] = acc[k];
+        __syncthreads();
+        if (h < ROW / 64) {
+            uint32_t y[16];
+            small_inv_col<W>(buf, threadIdx.x, pc, tw, fc[dn->cidx[slot]], y);
+            small_store_lifted(dn_y + (size_t)(poly * (A.n_p + A.rs) + slot) * SM_N, threadIdx.x, y, q);
+        }
+    });
+}
+
+struct SmallDown {
+    const int32_t* y;      // lifted rows of the two polynomials, `rows` each
+    const int32_t* mat;    // output row i's constants at mat + i stride
+    int rows, n_in, stride;
+};
+
+// launch limb l of M (ModDown's combine map) is an output row of one polynomial
+template <bool RS>
+__global__ void __launch_bounds__(SM_THREADS) k_small_moddown(NttTables T, const LaunchMap* Mp, SmallDown S, StCombine st,
+                                                              BcRescale X)
+{
+    __shared__ uint32_t buf[SM_N];
+    const LaunchMap& M = *Mp;
+    const int l = blockIdx.x, pid = M.pid[l], poly = M.grp[l], i = M.out_off[l];
+    const PrimeC pc = T.prime(pid);
+    const int t = threadIdx.x & 63, h = wave_id(), e = h * ROW + 4 * t;
+    const int32_t* twt = T.tw + (size_t)pid * SM_N;
+    const SmallColTw tw(twt, pc.q);
+    const int32_t* y = S.y + (size_t)(poly * S.rows) * SM_N;
+    int2 twr[4][3];
+    row4_twiddles<SM_LOG1, false>(twt, pc.q, h, t, twr);
+    const auto pre = st.template prefetch<4>(M, l, e);
+    int64_t acc[4];
+    small_bconv_sums(y, e, S.n_in, S.mat + (size_t)i * S.stride, pc.q, acc);
+    int32_t tl[RS ? 4 : 1];
+    int64_t mp = 0;
+    if constexpr (RS) {  // t = lift(e - conv_{l-1} P^-1), the dropped limb of the result (BcRescale)
+        const PrimeC pl = T.prime(X.level - 1);
+        int64_t al[4];
+        uint32_t er[4];
+        loadv_u32<4>(reinterpret_cast<const uint32_t*>(y) + (size_t)S.n_in * SM_N + e, er);
+        small_bconv_sums(y, e, S.n_in, X.mlast + (size_t)(X.level - 1) * X.n_p, pl.q, al);
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const uint32_t cl = canon_signed(smr64(range_fix(al[k], (int64_t)pl.q << 31, (int64_t)pl.q << 32), pl.q, pl.qinv), pl.q);
+            const int32_t ei = (int32_t)er[k];
+            tl[k] = lift(sub_mod(ei < 0 ? (uint32_t)(ei + (int32_t)pl.q) : (uint32_t)ei, cl, pl.q), pl.q);
+        }
+        mp = X.pr[pid];
+    }
+    uint32_t x[4];
+    bconv_reduce<RS>(acc, tl, mp, pc, false, x);
+    storev_u32<4>(buf + e, x);
+    __syncthreads();
+    by_class(pc.q, [&](auto tag) {
+        constexpr bool W = decltype(tag)::value;
+        if (h < ROW / 64) small_fwd_col<W>(buf, threadIdx.x, pc, tw);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; k++) x[k] = buf[h * ROW + t + 64 * k];
+        row4_fwd<W>(x, pc, t, twr);
+        st.template store_fwd<4, W>(M, l, e, x, pc, pre);
+    });
+}
+
+// ---------------------------------------------------------------------------
 // Sum of plaintext-weighted rotations (Sec. 5 Par.4/Par.5, Eq. 5): one
 // KeyMult pass over all rotations.  For row r, rotation i: the shared ModUp
 // rows (evaluation domain) and the own digit's input row are gathered
@@ -2074,6 +2390,72 @@ static KmArgs km_args(const Ctx& c, const KsRun& R, const KsIn& in, const uint32
     return A;
 }
 
+// One operation at N = 2^12 (the launch-bound ring) takes the four-launch
+// sequence; the settings other than one wave per row and 4-residue columns
+// keep the general one.
+static bool small_ring(const Ctx& c, int level)
+{
+    // up to four one-prime digits: the general sequence's conversions fuse into
+    // five launches of smaller work-groups (3 limbs: 22.3 against 23.4 us)
+    if (c.n_p == 1 && c.digits(level) <= 4) return false;
+    return c.log_n == SM_LOG_N && c.rows_ept1 == 4 && c.km_ept1 == 4 && c.col_ept1 == 4;
+}
+
+static int small_keyswitch(const Ctx& c, const KsRun& R, Own own, Extra extra, const KsIn& in, int level,
+                           const uint32_t* evk, uint32_t* out0, uint32_t* out1, hipStream_t s, bool rescale)
+{
+    const KsPlan& P = *R.P;
+    const bool rr = rescale && c.windowed;
+    const int pst = c.n_p + (rescale ? c.rs_drop(level) : 0), wb = c.wbase[level];
+    const NttTables Tf = tables(c, false), Ti = tables(c, true);
+    const uint32_t gal = (uint32_t)in.galois;
+    {
+        KTimer t(c, "modup_intt", s);
+        const int4* fc = own == Own::Tensor ? c.up_c_r : c.up_c;
+#define CKKS_SMALL_INTT(OWN)                                                                                     \
+    CKKS_LAUNCH((k_small_intt<OWN>), dim3(level), dim3(SM_THREADS), 0, s, Ti, P.up_rows.dev, P.up_cols.dev,        \
+                (LdOwn<OWN>{in.a0, in.a1, gal, c.log_n, 0, 0, nullptr}), fc, R.w1)
+        if (own == Own::Tensor) CKKS_SMALL_INTT(Own::Tensor);
+        else if (own == Own::Gather) CKKS_SMALL_INTT(Own::Gather);
+        else CKKS_SMALL_INTT(Own::Plain);
+#undef CKKS_SMALL_INTT
+        if (int e = launched("modup intt")) return e;
+    }
+    {
+        KTimer t(c, "modup", s);
+        const SmallUp U{R.w1, c.up_mat + (size_t)level * c.dnum * c.n_primes * c.n_p, R.w2, level, wb, c.n_q, c.n_p,
+                        c.n_primes, c.up_nofix};
+        CKKS_LAUNCH(k_small_modup, dim3(level + c.n_p, c.digits(level)), dim3(SM_THREADS), 0, s, Tf, U);
+        if (int e = launched("modup")) return e;
+    }
+    {
+        KTimer t(c, "keymult", s);
+        const KmArgs A = km_args(c, R, in, evk, level, rescale);
+        const LaunchMap* dn = P.dn_cols.dev;
+        const int4* fc = rr ? c.rr_c : c.dn_c;
+        int32_t* dn_y = reinterpret_cast<int32_t*>(R.w0);
+        const dim3 grid(level + c.n_p, 2);
+        if (own == Own::Tensor && extra == Extra::HMult)
+            CKKS_LAUNCH((k_small_keymult<Own::Tensor, Extra::HMult>), grid, dim3(SM_THREADS), 0, s, Ti, A, dn, fc, dn_y);
+        else if (own == Own::Plain && extra == Extra::None)
+            CKKS_LAUNCH((k_small_keymult<Own::Plain, Extra::None>), grid, dim3(SM_THREADS), 0, s, Ti, A, dn, fc, dn_y);
+        else if (own == Own::Gather && extra == Extra::HRot)
+            CKKS_LAUNCH((k_small_keymult<Own::Gather, Extra::HRot>), grid, dim3(SM_THREADS), 0, s, Ti, A, dn, fc, dn_y);
+        else return set_error(-1, "unsupported key-switch variant");
+        if (int e = launched("keymult")) return e;
+    }
+    {
+        KTimer t(c, "moddown", s);
+        const SmallDown S{reinterpret_cast<const int32_t*>(R.w0), rr ? c.rr_mat + c.rr_mat_off[level] : c.dn_mat + (size_t)wb * c.n_p,
+                          pst, rr ? pst : c.n_p, rr ? pst : c.n_p};
+        const StCombine st{out0, out1, R.w3, rr ? c.rr_fin : rescale ? c.rs_fin : c.dn_pinv, c.log_n};
+        const BcRescale X{c.rs_mlast, c.rs_pr, c.n_p, level};
+        if (rescale && !rr) CKKS_LAUNCH((k_small_moddown<true>), dim3(P.dn_rows.n), dim3(SM_THREADS), 0, s, Tf, P.dn_rows.dev, S, st, X);
+        else CKKS_LAUNCH((k_small_moddown<false>), dim3(P.dn_rows.n), dim3(SM_THREADS), 0, s, Tf, P.dn_rows.dev, S, st, X);
+        return launched("moddown");
+    }
+}
+
 // Shared sequence of a single (b == nullptr) or batched key switch.
 static int keyswitch_seq(const Ctx& c, Own own, Extra extra, const KsIn& in, int level, const KsBatch* b,
                          const uint32_t* evk, uint32_t* out0, uint32_t* out1, void* ws, hipStream_t s, bool rescale)
@@ -2097,6 +2479,7 @@ static int keyswitch_seq(const Ctx& c, Own own, Extra extra, const KsIn& in, int
         if (!R.P->up_rows.dev) return set_error(-5, "no launch plan for this level");
         R.g.up_rows = R.P->up_rows.n, R.g.up_cols = R.P->up_cols.n;
         R.g.dn_cols = R.P->dn_cols.n, R.g.dn_rows = R.P->dn_rows.n;
+        if (small_ring(c, level)) return small_keyswitch(c, R, own, extra, in, level, evk, out0, out1, s, rescale);
     }
     if (int e = modup_phase(R, own, in, b ? b->in_step : 0, b ? b->in2_step : 0, s)) return e;
     KmArgs A = km_args(c, R, in, evk, top, rescale);
