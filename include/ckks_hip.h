@@ -154,7 +154,8 @@ typedef struct {
     int32_t keymult_rows_single; /* the same for launches of one operation (default 4); 0 = keymult_rows */
     int32_t cols_per_thread;  /* residues per thread of key switching's column passes (INTT columns, BConv +
                                  NTT columns): 16 (col_threads tiles) or 4 (default; 256-thread tiles of
-                                 1024 / 2^(log_n - 8) columns, radix-4 rounds) */
+                                 1024 / 2^(log_n - 8) columns, radix-4 rounds); the INTT columns of large
+                                 batched launches take 16 either way */
     int32_t cols_per_thread_single; /* the same for launches of one operation (default 4);
                                        0 = cols_per_thread */
 } ckks_tuning;

@@ -13,7 +13,7 @@ namespace ckks {
 constexpr int MAX_PRIMES = 64;  // q's + p's
 constexpr int MAX_LAUNCH_LIMBS = 128;
 
-// Per-launch limb map (passed by value as a kernel argument, at most 4 KB).
+// Per-launch limb map (in device memory, written at context creation).
 // Launch limb l reads input limb in_off[l] and writes output limb
 // out_off[l] (offsets in units of N residues from the functor's base
 // pointer, output base chosen by grp[l]), has prime id pid[l], uses row

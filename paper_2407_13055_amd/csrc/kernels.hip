@@ -1424,9 +1424,9 @@ __device__ __forceinline__ void small_bconv_sums(const int32_t* y, int e, int n_
     }
 }
 
-template <Own OWN>
-__global__ void __launch_bounds__(SM_THREADS) k_small_intt(NttTables T, const LaunchMap* Mr, const LaunchMap* Mc,
-                                                           LdOwn<OWN> ld, const int4* fc, int32_t* out)
+template <class Ld>
+__global__ void __launch_bounds__(SM_THREADS) k_small_intt(NttTables T, const LaunchMap* Mr, const LaunchMap* Mc, Ld ld,
+                                                           const int4* fc, int32_t* out)
 {
     __shared__ uint32_t buf[SM_N];
     const int limb = blockIdx.x, pid = Mr->pid[limb];
@@ -1449,6 +1449,68 @@ __global__ void __launch_bounds__(SM_THREADS) k_small_intt(NttTables T, const La
             uint32_t y[16];
             small_inv_col<W>(buf, threadIdx.x, pc, tw, cst, y);
             small_store_lifted(out + (size_t)limb * SM_N, threadIdx.x, y, pc.q);
+        }
+    });
+}
+
+// stand-alone transforms of a limb, in place
+__global__ void __launch_bounds__(SM_THREADS) k_small_ntt(NttTables T, IdMap M, uint32_t* data)
+{
+    __shared__ uint32_t buf[SM_N];
+    const int limb = blockIdx.x, pid = M.pid[limb];
+    const PrimeC pc = T.prime(pid);
+    const int t = threadIdx.x & 63, h = wave_id(), c = threadIdx.x % ROW;
+    const int32_t* twt = T.tw + (size_t)pid * SM_N;
+    const SmallColTw tw(twt, pc.q);
+    uint32_t* d = data + (size_t)limb * SM_N;
+    uint32_t y[16], x[4];
+    if (h < ROW / 64) {
+#pragma unroll
+        for (int k = 0; k < 16; k++) y[k] = d[k * ROW + c];
+    }
+    int2 twr[4][3];
+    row4_twiddles<SM_LOG1, false>(twt, pc.q, h, t, twr);
+    by_class(pc.q, [&](auto tag) {
+        constexpr bool W = decltype(tag)::value;
+        if (h < ROW / 64) {
+            ct_stages<4, W>(y, pc, tw);
+#pragma unroll
+            for (int k = 0; k < 16; k++) buf[k * ROW + c] = y[k];
+        }
+        __syncthreads();  // every column is read before a row is written
+#pragma unroll
+        for (int k = 0; k < 4; k++) x[k] = buf[h * ROW + t + 64 * k];
+        row4_fwd<W>(x, pc, t, twr);
+#pragma unroll
+        for (int k = 0; k < 4; k++) x[k] = fwd_canon<W>(x[k], pc);
+    });
+    storev_u32<4>(d + h * ROW + 4 * t, x);
+}
+__global__ void __launch_bounds__(SM_THREADS) k_small_intt_plain(NttTables T, IdMap M, uint32_t* data, const int4* ninv)
+{
+    __shared__ uint32_t buf[SM_N];
+    const int limb = blockIdx.x, pid = M.pid[limb];
+    const PrimeC pc = T.prime(pid);
+    const int t = threadIdx.x & 63, h = wave_id(), c = threadIdx.x % ROW;
+    const int32_t* twt = T.tw + (size_t)pid * SM_N;
+    const SmallColTw tw(twt, pc.q);
+    uint32_t* d = data + (size_t)limb * SM_N;
+    uint32_t x[4];
+    loadv_u32<4>(d + h * ROW + 4 * t, x);
+    int2 twr[4][3];
+    row4_twiddles<SM_LOG1, true>(twt, pc.q, h, t, twr);
+    const int4 cst = ninv[pid];
+    by_class(pc.q, [&](auto tag) {
+        constexpr bool W = decltype(tag)::value;
+        row4_inv<W>(x, pc, t, twr);
+#pragma unroll
+        for (int k = 0; k < 4; k++) buf[h * ROW + t + 64 * k] = x[k];
+        __syncthreads();
+        if (h < ROW / 64) {
+            uint32_t y[16];
+            small_inv_col<W>(buf, c, pc, tw, cst, y);
+#pragma unroll
+            for (int k = 0; k < 16; k++) d[k * ROW + c] = y[k];
         }
     });
 }
@@ -2078,6 +2140,30 @@ static int launch_inv_bconv_list(const Ctx& c, int tpw, const MapRef& cols, cons
     return launched("intt cols + bconv + ntt cols");
 }
 
+// Single operations at N = 2^12 (the launch-bound ring) run whole limbs per
+// work-group: key switching in four launches, rescalings in two, transforms in
+// one.  A dependent launch costs about 3.5 us, more than the second pass of a
+// limb adds to a work-group's chain: NTT 7.5 -> 5.1, INTT 7.4 -> 5.1, rescaling
+// 11.0 -> 9.8, rational rescaling 13.3 -> 10.7 us.
+// The settings other than one wave per row and 4-residue columns keep the
+// general passes.
+static bool small_ring(const Ctx& c)
+{
+    return c.log_n == SM_LOG_N && c.rows_ept1 == 4 && c.km_ept1 == 4 && c.col_ept1 == 4;
+}
+// a rescaling at N = 2^12: INTT of the dropped rows (`drop` per polynomial,
+// lifted into y), then every output row's conversion, NTT and combine
+static int small_rescale(const Ctx& c, const MapRef& rows, const MapRef& cols, const MapRef& out, const uint32_t* in,
+                         const int4* fc, int drop, const int32_t* mat, const StCombine& st, int32_t* y, hipStream_t s)
+{
+    KTimer t(c, "rescale_small", s);
+    CKKS_LAUNCH((k_small_intt<LdPlain>), dim3(rows.n), dim3(SM_THREADS), 0, s, tables(c, true), rows.dev, cols.dev,
+                (LdPlain{in, c.log_n}), fc, y);
+    CKKS_LAUNCH((k_small_moddown<false>), dim3(out.n), dim3(SM_THREADS), 0, s, tables(c, false), out.dev,
+                (SmallDown{y, mat, drop, drop, drop}), st, BcRescale{});
+    return launched("rescale");
+}
+
 // ---------------------------------------------------------------------------
 // stand-alone NTT / INTT over a list of limbs (caller-chosen primes: maps by
 // value)
@@ -2093,6 +2179,13 @@ int launch_ntt(const Ctx& c, bool inverse, uint32_t* data, const int32_t* pids, 
         for (int l = 0; l < n; l++) M.m.pid.w[l >> 2] |= (uint32_t)pids[base + l] << (8 * (l & 3));
         M.m.cidx = M.m.pid;
         uint32_t* d = data + (size_t)base * c.n;
+        if (small_ring(c)) {
+            KTimer t(c, inverse ? "intt" : "ntt", s);
+            if (inverse) CKKS_LAUNCH(k_small_intt_plain, dim3(n), dim3(SM_THREADS), 0, s, tables(c, true), M.m, d, c.ninv);
+            else CKKS_LAUNCH(k_small_ntt, dim3(n), dim3(SM_THREADS), 0, s, tables(c, false), M.m, d);
+            if (int e = launched("ntt")) return e;
+            continue;
+        }
         LdPlain ld{d, c.log_n};
         StPlain st{d, c.ninv, c.log_n};
         if (!inverse) {
@@ -2390,15 +2483,13 @@ static KmArgs km_args(const Ctx& c, const KsRun& R, const KsIn& in, const uint32
     return A;
 }
 
-// One operation at N = 2^12 (the launch-bound ring) takes the four-launch
-// sequence; the settings other than one wave per row and 4-residue columns
-// keep the general one.
-static bool small_ring(const Ctx& c, int level)
+// One operation at N = 2^12 takes the four-launch sequence.
+static bool small_switch(const Ctx& c, int level)
 {
     // up to four one-prime digits: the general sequence's conversions fuse into
     // five launches of smaller work-groups (3 limbs: 22.3 against 23.4 us)
     if (c.n_p == 1 && c.digits(level) <= 4) return false;
-    return c.log_n == SM_LOG_N && c.rows_ept1 == 4 && c.km_ept1 == 4 && c.col_ept1 == 4;
+    return small_ring(c);
 }
 
 static int small_keyswitch(const Ctx& c, const KsRun& R, Own own, Extra extra, const KsIn& in, int level,
@@ -2413,7 +2504,7 @@ static int small_keyswitch(const Ctx& c, const KsRun& R, Own own, Extra extra, c
         KTimer t(c, "modup_intt", s);
         const int4* fc = own == Own::Tensor ? c.up_c_r : c.up_c;
 #define CKKS_SMALL_INTT(OWN)                                                                                     \
-    CKKS_LAUNCH((k_small_intt<OWN>), dim3(level), dim3(SM_THREADS), 0, s, Ti, P.up_rows.dev, P.up_cols.dev,        \
+    CKKS_LAUNCH((k_small_intt<LdOwn<OWN>>), dim3(level), dim3(SM_THREADS), 0, s, Ti, P.up_rows.dev, P.up_cols.dev,        \
                 (LdOwn<OWN>{in.a0, in.a1, gal, c.log_n, 0, 0, nullptr}), fc, R.w1)
         if (own == Own::Tensor) CKKS_SMALL_INTT(Own::Tensor);
         else if (own == Own::Gather) CKKS_SMALL_INTT(Own::Gather);
@@ -2479,7 +2570,7 @@ static int keyswitch_seq(const Ctx& c, Own own, Extra extra, const KsIn& in, int
         if (!R.P->up_rows.dev) return set_error(-5, "no launch plan for this level");
         R.g.up_rows = R.P->up_rows.n, R.g.up_cols = R.P->up_cols.n;
         R.g.dn_cols = R.P->dn_cols.n, R.g.dn_rows = R.P->dn_rows.n;
-        if (small_ring(c, level)) return small_keyswitch(c, R, own, extra, in, level, evk, out0, out1, s, rescale);
+        if (small_switch(c, level)) return small_keyswitch(c, R, own, extra, in, level, evk, out0, out1, s, rescale);
     }
     if (int e = modup_phase(R, own, in, b ? b->in_step : 0, b ? b->in2_step : 0, s)) return e;
     KmArgs A = km_args(c, R, in, evk, top, rescale);
@@ -2615,6 +2706,10 @@ int launch_rescale(const Ctx& c, const uint32_t* in, int level_in, uint32_t* out
     const int log1 = c.log_n - ROW_LOG;
     const RsPlan& P = c.rs_plan[level_in];
     if (!P.rows.dev) return set_error(-5, "no launch plan for this level");
+    if (small_ring(c))
+        return small_rescale(c, P.rows, P.cols, P.nrows, in, c.ninv, 1, c.rs_mat,
+                             StCombine{out, out + (size_t)(level_in - 1) * c.n, in, c.rs_qinv, c.log_n},
+                             static_cast<int32_t*>(ws), s);
     uint32_t* w0 = static_cast<uint32_t*>(ws);  // [2] INTT row pass of the last limbs
     uint32_t* w2 = w0 + 4 * (size_t)c.n;        // [2 (l-1)] NTT column pass of [t]_{q_i}
     {
@@ -2903,6 +2998,10 @@ int launch_rescale_rational_window(const Ctx& c, int level, const uint32_t* ct, 
     if (!P.rows.dev) return set_error(-5, "no rational rescaling plan for this level");
     const int log1 = c.log_n - ROW_LOG, nd = c.rr_drop(level), below = c.rr_below[level];
     const size_t n = c.n;
+    if (small_ring(c))
+        return small_rescale(c, P.rows, P.cols, P.nrows, ct, c.rr2_c, nd, c.rr2_mat + c.rr2_mat_off[level],
+                             StCombine{out, out + (size_t)below * n, ct, c.rr2_fin, c.log_n},
+                             static_cast<int32_t*>(ws), s);
     uint32_t* w0 = static_cast<uint32_t*>(ws);
     int32_t* w1 = reinterpret_cast<int32_t*>(w0 + 2 * (size_t)nd * n);
     uint32_t* w2 = reinterpret_cast<uint32_t*>(w1 + 2 * (size_t)nd * n);

@@ -58,3 +58,36 @@ def test_key_switching(n_q, n_p):
             torch.cuda.synchronize()
             assert np.array_equal(ck.to_host(rs), oracle.rescale(P, prod, level))
     C.close()
+
+
+@pytest.mark.parametrize("n_limbs", [1, 9, 131])
+def test_transforms(n_limbs):
+    """Stand-alone transforms of a limb per work-group, both prime classes, one
+    launch and more than one."""
+    P = oracle.Params(LOG_N, oracle.prime_chain(30, LOG_N, 6), oracle.prime_chain(31, LOG_N, 3))
+    C = ck.Context(LOG_N, P.q, P.p)
+    mods = P.q + P.p
+    pids = [(5 * i) % len(mods) for i in range(n_limbs)]
+    x = synth.stream(92, "gpu/small/ntt/%d" % n_limbs).residues([mods[i] for i in pids], P.n)
+    want = oracle.ntt(x, [mods[i] for i in pids], LOG_N)
+    d = ck.to_device(x)
+    C.ntt(d, pids)
+    torch.cuda.synchronize()
+    assert np.array_equal(ck.to_host(d), want)
+    C.intt(d, pids)
+    torch.cuda.synchronize()
+    assert np.array_equal(ck.to_host(d), x)
+    C.close()
+
+
+@pytest.mark.parametrize("n_q", [2, 7])
+def test_rescale(n_q):
+    P = oracle.Params(LOG_N, oracle.prime_chain(30, LOG_N, n_q), oracle.prime_chain(31, LOG_N, 1))
+    C = ck.Context(LOG_N, P.q, P.p)
+    a = draw(synth.stream(93, "gpu/small/rescale/%d" % n_q), P.q, P.n)
+    for level in sorted({2, n_q}):
+        out = torch.full((2, level - 1, P.n), -1, dtype=torch.int32, device="cuda")
+        C.rescale(ck.to_device(np.ascontiguousarray(a[:, :level])), out)
+        torch.cuda.synchronize()
+        assert np.array_equal(ck.to_host(out), oracle.rescale(P, np.ascontiguousarray(a[:, :level]), level))
+    C.close()
