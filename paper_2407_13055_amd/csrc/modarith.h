@@ -96,9 +96,6 @@ __device__ __forceinline__ int2 const_from_quot(int32_t ws, uint32_t q)
 // [0, 2m) -> [0, m)
 __device__ __forceinline__ uint32_t red2(uint32_t x, uint32_t m) { return min(x, x - m); }
 
-// twisted companion of a Montgomery-form constant W
-__device__ __forceinline__ uint2 twist(uint32_t W, uint32_t qinv) { return make_uint2(W, W * qinv); }
-
 // Signed Montgomery reduction: r = x 2^-32 (mod t) with |r| <= |x| / 2^32 +
 // t / 2, below t for |x| <= t 2^31; odd t < 2^31, tinv = t^-1 mod 2^32.
 // Why it works: m = x t^-1 mod 2^32, read as a signed 32-bit value, makes
