@@ -314,13 +314,10 @@ class Context:
         least `numel` elements of `dtype` (int32 residues or uint8 bytes)."""
         torch = _torch()
         want = torch.int32 if dtype == "int32" else torch.uint8
-        try:
-            if t.get_device() == self.device and t.is_cuda and t.dtype is want and t.is_contiguous() and t.numel() >= numel:
-                return t.data_ptr()
-        except AttributeError:
-            pass
         if not isinstance(t, torch.Tensor):
             raise CkksError("%s: expected a torch tensor, got %s" % (name, type(t).__name__))
+        if t.get_device() == self.device and t.is_cuda and t.dtype is want and t.is_contiguous() and t.numel() >= numel:
+            return t.data_ptr()
         if not t.is_cuda or t.device.index != self.device:
             raise CkksError("%s: must be on cuda:%d (got %s)" % (name, self.device, t.device))
         if t.dtype != want:
