@@ -18,6 +18,7 @@
 
 #include "internal.h"
 #include "ntt_core.h"
+#include "xcd_rows.h"
 
 namespace ckks {
 
@@ -881,26 +882,7 @@ struct KmArgs {
     const BatchItem* items;
     size_t in_step, in2_step, ws_step, key_step, up_step;
     int lo_level, n_keys, n_src;
-    int n_rot;            // rotations of a hoisted launch (one-dimensional grid, XcdRows)
-};
-
-// Work-groups of a hoisted launch, one-dimensional: every rotation of a row
-// reads the row's shared ModUp rows (256 KB each at N = 2^16), so a row's
-// work-groups all run on one XCD (work-groups go to the 8 XCDs in turn), one
-// rotation after the other, and its L2 serves all but the first: 32 hoisted
-// rotations' KeyMult at N = 2^16, 24 limbs 464 -> 403 us with the 16-byte
-// gathers, and 380 us with the key rows loaded past the L2 (load_once).
-struct XcdRows {
-    int row, rot, tile;
-    __device__ __forceinline__ XcdRows(int tiles, int n_rot)
-    {
-        const uint32_t j = blockIdx.x >> 3;
-        tile = (int)(j % (uint32_t)tiles);
-        const uint32_t k = j / (uint32_t)tiles;
-        rot = (int)(k % (uint32_t)n_rot);
-        row = (int)(k / (uint32_t)n_rot) * 8 + (int)(blockIdx.x & 7u);
-    }
-    static unsigned grid(int rows, int tiles, int n_rot) { return 8u * (unsigned)((rows + 7) / 8) * (unsigned)tiles * (unsigned)n_rot; }
+    int n_rot;            // rotations of a hoisted launch (XcdRows)
 };
 
 // End of a KeyMult row: Q rows store ks; P rows (and the dropped row q_{l-1}
@@ -1155,7 +1137,8 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
     // so they are dispatched first and do not form the launch's tail
     int gy = blockIdx.y, tile = blockIdx.x, item = blockIdx.z;
     if constexpr (OWN == Own::Hoisted) {
-        const XcdRows X(row4_tiles<LOG1>(), A.n_rot);
+        const XcdRows X(XcdGrid{blockIdx.x, blockIdx.y, blockIdx.z}, A.level + A.n_p, row4_tiles<LOG1>(), A.n_rot);
+        if (X.row < 0) return;
         gy = X.row, tile = X.tile, item = X.rot;
     }
     if (!km_item(A, Tf.log_n, item)) return;
@@ -1733,9 +1716,9 @@ template <int LOG1>
 __global__ void __launch_bounds__(NTT_THREADS) k_keymult_sum(NttTables Tf, NttTables Ti, KmArgs A,
                                                               const uint32_t* pts, size_t pt_step, int n_rot)
 {
-    const XcdRows X(row4_tiles<LOG1>(), 1);
+    const XcdRows X(XcdGrid{blockIdx.x, blockIdx.y, blockIdx.z}, A.level + A.n_p, row4_tiles<LOG1>(), 1);
     const int r = X.row;
-    if (r >= A.level + A.n_p) return;
+    if (r < 0) return;
     const int woff = A.base % A.n_p, kd = A.base / A.n_p;  // as in k_keymult
     const int beta = (woff + A.level + A.n_p - 1) / A.n_p;
     const int log_n = Tf.log_n;
@@ -2265,12 +2248,18 @@ static KsLayout ks_layout(const Ctx& c, int level)
 
 size_t keyswitch_ws_bytes(const Ctx& c, int level) { return ks_layout(c, level).total * 4; }
 
+static dim3 xcd_grid(int rows, int tiles, int n_rot)
+{
+    const XcdGrid g = XcdRows::grid((uint32_t)rows, (uint32_t)tiles, (uint32_t)n_rot);
+    return dim3(g.x, g.y, g.z);
+}
+
 template <int L1, Own OWN, Extra EX>
 static void keymult(const Ctx& c, int max_level, int items_n, const KmArgs& A, hipStream_t s)
 {
     if ((items_n == 1 ? c.km_ept1 : c.km_ept) == 4)
         CKKS_LAUNCH((k_keymult4<L1, OWN, EX>),
-                    OWN == Own::Hoisted ? dim3(XcdRows::grid(max_level + c.n_p, row4_tiles<L1>(), items_n))
+                    OWN == Own::Hoisted ? xcd_grid(max_level + c.n_p, row4_tiles<L1>(), items_n)
                                         : dim3(row4_tiles<L1>(), max_level + c.n_p, items_n),
                     dim3(NTT_THREADS), 0, s, tables(c, false), tables(c, true), A);
     else
@@ -2635,7 +2624,7 @@ template <int L1>
 static void keymult_sum(const Ctx& c, int level, const KmArgs& A, const uint32_t* pts, size_t pt_step, int n_rot,
                         hipStream_t s)
 {
-    CKKS_LAUNCH((k_keymult_sum<L1>), dim3(XcdRows::grid(level + c.n_p, row4_tiles<L1>(), 1)), dim3(NTT_THREADS), 0, s,
+    CKKS_LAUNCH((k_keymult_sum<L1>), xcd_grid(level + c.n_p, row4_tiles<L1>(), 1), dim3(NTT_THREADS), 0, s,
                 tables(c, false), tables(c, true), A, pts, pt_step, n_rot);
 }
 
