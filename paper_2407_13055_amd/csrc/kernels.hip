@@ -1137,7 +1137,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
     // so they are dispatched first and do not form the launch's tail
     int gy = blockIdx.y, tile = blockIdx.x, item = blockIdx.z;
     if constexpr (OWN == Own::Hoisted) {
-        const XcdRows X(XcdGrid{blockIdx.x, blockIdx.y, blockIdx.z}, A.level + A.n_p, row4_tiles<LOG1>(), A.n_rot);
+        const XcdRows X(XcdGrid{blockIdx.x, blockIdx.y, blockIdx.z}, gridDim.y, A.level + A.n_p, row4_tiles<LOG1>(), A.n_rot);
         if (X.row < 0) return;
         gy = X.row, tile = X.tile, item = X.rot;
     }
@@ -1716,7 +1716,7 @@ template <int LOG1>
 __global__ void __launch_bounds__(NTT_THREADS) k_keymult_sum(NttTables Tf, NttTables Ti, KmArgs A,
                                                               const uint32_t* pts, size_t pt_step, int n_rot)
 {
-    const XcdRows X(XcdGrid{blockIdx.x, blockIdx.y, blockIdx.z}, A.level + A.n_p, row4_tiles<LOG1>(), 1);
+    const XcdRows X(XcdGrid{blockIdx.x, blockIdx.y, blockIdx.z}, gridDim.y, A.level + A.n_p, row4_tiles<LOG1>(), 1);
     const int r = X.row;
     if (r < 0) return;
     const int woff = A.base % A.n_p, kd = A.base / A.n_p;  // as in k_keymult

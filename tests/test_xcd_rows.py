@@ -29,7 +29,7 @@ int main(int argc, char** argv)
             for (uint32_t z = 0; z < g.z; z++)
                 for (uint32_t y = 0; y < g.y; y++)
                     for (uint32_t x = 0; x < g.x; x++, linear++) {
-                        const XcdRows X(XcdGrid{x, y, z}, rows, tiles, n_rot);
+                        const XcdRows X(XcdGrid{x, y, z}, g.y, rows, tiles, n_rot);
                         if (X.row < 0) continue;
                         if (X.row >= (int)rows || X.rot < 0 || X.rot >= (int)n_rot || X.tile < 0 || X.tile >= (int)tiles) out++;
                         else seen[((size_t)X.row * n_rot + X.rot) * tiles + X.tile]++, xcd[linear & 7]++;
@@ -77,3 +77,10 @@ def test_grid_limits(order):
 def test_every_item_once(order):
     for size, r in zip(SIZES, order(True, SIZES)):
         assert r[3:6] == [0, 0, 0], size
+
+
+def test_balance(order):
+    """No XCD has more than its eighth of the items, up to a row's last tiles."""
+    for size, r in zip(SIZES, order(True, SIZES)):
+        rows, tiles, n_rot = size
+        assert max(r[6:]) <= rows * tiles * n_rot / 8 + rows % 8, size
