@@ -883,6 +883,7 @@ struct KmArgs {
     size_t in_step, in2_step, ws_step, key_step, up_step;
     int lo_level, n_keys, n_src;
     int n_rot;            // rotations of a hoisted launch (XcdRows)
+    int once;             // hoisted: key rows are loaded past the caches (KEYS_ONCE_BYTES)
 };
 
 // End of a KeyMult row: Q rows store ks; P rows (and the dropped row q_{l-1}
@@ -1184,8 +1185,13 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
         const uint32_t* kb = A.evk + (((size_t)(2 * (kd + j)) * key_rows + pid) * n + hrow) + l4;
         const uint32_t* ka = A.evk + (((size_t)(2 * (kd + j) + 1) * key_rows + pid) * n + hrow) + l4;
         if constexpr (OWN == Own::Hoisted) {
-            load_once(kb, d.kb);
-            load_once(ka, d.ka);
+            if (A.once) {
+                load_once(kb, d.kb);
+                load_once(ka, d.ka);
+            } else {
+                loadv_u32<4>(kb, d.kb);
+                loadv_u32<4>(ka, d.ka);
+            }
         } else {
             loadv_u32<4>(kb, d.kb);
             loadv_u32<4>(ka, d.ka);
@@ -2573,6 +2579,16 @@ static int keyswitch_seq(const Ctx& c, Own own, Extra extra, const KsIn& in, int
     return moddown_phase(R, level, rescale, out0, out1, b ? b->out_step : 0, s);
 }
 
+// A hoisted launch loads its keys past the caches (load_once) where they are
+// more than half of the 256 MB last-level cache: a program rotates by the same
+// keys again, and keys that it holds from the last call are read from there.
+// 32 rotations at N = 2^12, past the caches -> through them: 25 rows in three
+// digits (77 MB) 76.9 -> 70.0 us, 32 rows (100 MB) 85.9 -> 80.2, 25 rows in four
+// (105 MB) 80.5 -> 74.7; N = 2^14, 8 rotations of 25 rows (79 MB) 78.6 -> 75.0;
+// beyond the line 17 rows in two digits (142 MB) 125.7 -> 131.3, 25 in three
+// (314 MB) 191 -> 205.5; N = 2^12, 64 rotations of 32 rows (201 MB) 130 -> 141.
+constexpr size_t KEYS_ONCE_BYTES = (size_t)128 << 20;
+
 // Hoisted HRot: one ModUp of a (materialised in the evaluation domain),
 // then KeyMult with the automorphism gathered on load and ModDown for every
 // rotation at once (grid.z = rotation).  Workspace: one key-switch layout
@@ -2615,6 +2631,8 @@ int launch_hrot_hoisted(const Ctx& c, const uint32_t* b_in, const uint32_t* a_in
     A.ws_step = slice;
     A.up_step = 0;
     A.n_rot = n_rot;
+    const size_t key_bytes = (size_t)2 * c.digits(level) * (level + c.n_p) * c.n * 4;  // rows that a rotation reads
+    A.once = (size_t)std::min(n_rot, n_keys) * key_bytes > KEYS_ONCE_BYTES;
     if (int e = keymult_launch(c, Own::Hoisted, Extra::HRot, level, n_rot, A, s)) return e;
     const size_t out_step = 2 * (size_t)level * c.n;
     return moddown_phase(R, level, false, outs, outs + (size_t)level * c.n, out_step, s);
