@@ -1943,23 +1943,33 @@ static NttTables tables(const Ctx& c, bool inverse)
     default: return set_error(-5, "unsupported ring degree"); \
     }
 
+// Forward column passes of 4 residues per thread (c4) store rows in runs of a
+// tile's columns, 16 bytes at N = 2^16 and 32 at 2^15, where 16 residues give
+// runs of 64 and 128; once the 16-residue work-groups fill the chip, that is
+// what counts.  NTT of n limbs (both passes), 4 -> 16 residues: N = 2^16, 8
+// limbs 9.0 -> 9.3 us, 16 11.8 -> 11.4, 48 22.3 -> 20.4, 128 36.9 -> 30.4; 2^15,
+// 48 limbs 13.6 -> 13.8, 64 16.0 -> 16.0, 128 24.4 -> 23.7; 2^14 (64-byte runs)
+// 128 limbs 15.7 -> 16.3.
+template <int L1>
+static bool fwd_cols16(long groups) { return L1 == 8 ? groups >= 256 : L1 == 7 ? groups >= 512 : false; }
 template <int L1, class MS, class Ld, class St>
 static void fwd_cols(const Ctx& c, MS ms, int n, Ld ld, St st, hipStream_t s, int items_n = 1, bool c4 = false)
 {
-    if (c4) {
+    if (c4 && !fwd_cols16<L1>((long)col_tiles<L1>() * n * items_n)) {
         CKKS_LAUNCH((k_fwd_cols4<L1, MS, Ld, St>), dim3(Col4<L1>::TILES, n, items_n), dim3(NTT_THREADS), 0, s,
                     tables(c, false), ms, ld, st);
         return;
     }
+    const int ct = c4 ? NTT_THREADS : c.col_threads;
     if constexpr (L1 >= 5) {
-        if (c.col_threads == 512) {
+        if (ct == 512) {
             CKKS_LAUNCH((k_fwd_cols<L1, MS, Ld, St, 512>), dim3(col_tiles<L1, 512>(), n, items_n), dim3(512), 0, s,
                         tables(c, false), ms, ld, st);
             return;
         }
     }
     if constexpr (L1 >= 7) {
-        if (c.col_threads == 128) {
+        if (ct == 128) {
             CKKS_LAUNCH((k_fwd_cols<L1, MS, Ld, St, 128>), dim3(col_tiles<L1, 128>(), n, items_n), dim3(128), 0, s,
                         tables(c, false), ms, ld, st);
             return;
