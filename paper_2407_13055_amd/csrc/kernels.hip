@@ -2002,15 +2002,20 @@ static void inv_rows(const Ctx& c, MS ms, int n, Ld ld, St st, hipStream_t s, in
                            s, tables(c, true), ms, ld, st);
 }
 // Inverse column passes of 4 residues per thread, where they are asked for
-// (c4), give way to 16 when that leaves 8 work-groups per CU: one LDS exchange
-// instead of three, and 64-byte instead of 16-byte runs of a row per tile.
-// 64 items of 4 to 24 limbs at N = 2^16: ModUp's pass 175 -> 135 us, ModDown's
-// 208 -> 162; one operation's 24 limbs (384 work-groups): 5.7 against 7.1 us.
-constexpr long INV_COLS16_GROUPS = 2048;
+// (c4), give way to 16 in large launches: 64-byte instead of 16-byte runs of a
+// row per tile at N = 2^16.
+//  * Lifted residues (key switching), from 8 work-groups per CU on: 64 items of
+//    4 to 24 limbs at N = 2^16 2070 -> 1995 us.
+//  * Row-major residues (stand-alone INTT): the stores have the same short runs,
+//    and two work-groups per CU are enough.  INTT of n limbs (both passes) at
+//    N = 2^16: 24 limbs 14.3 -> 14.8, 32 17.4 -> 17.1, 48 22.2 -> 21.7, 64 25.5 ->
+//    24.2, 96 30.8 -> 28.2, 128 36.6 -> 33.4; at 2^15 128 limbs 25.0 -> 25.4.
+template <int L1, class St>
+static bool inv_cols16(long groups) { return St::kTileThread ? groups >= 2048 : L1 == 8 && groups >= 512; }
 template <int L1, class MS, class Ld, class St>
 static void inv_cols(const Ctx& c, MS ms, int n, Ld ld, St st, hipStream_t s, int items_n = 1, bool c4 = false)
 {
-    if (c4 && (long)col_tiles<L1>() * n * items_n < INV_COLS16_GROUPS) {
+    if (c4 && !inv_cols16<L1, St>((long)col_tiles<L1>() * n * items_n)) {
         CKKS_LAUNCH((k_inv_cols4<L1, MS, Ld, St>), dim3(Col4<L1>::TILES, n, items_n), dim3(NTT_THREADS), 0, s,
                     tables(c, true), ms, ld, st);
         return;

@@ -13,7 +13,7 @@ torch = pytest.importorskip("torch")
 import paper_2407_13055_amd as ck  # noqa: E402
 
 
-@pytest.mark.parametrize("log_n,counts", [(16, (1, 15, 16, 17)), (15, (63, 64, 65)), (14, (129,))])
+@pytest.mark.parametrize("log_n,counts", [(16, (1, 15, 16, 17, 31, 32)), (15, (63, 64, 65)), (14, (129,))])
 def test_limb_counts(log_n, counts):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
