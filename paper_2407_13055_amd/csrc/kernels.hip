@@ -2004,14 +2004,20 @@ static void inv_rows(const Ctx& c, MS ms, int n, Ld ld, St st, hipStream_t s, in
 // Inverse column passes of 4 residues per thread, where they are asked for
 // (c4), give way to 16 in large launches: 64-byte instead of 16-byte runs of a
 // row per tile at N = 2^16.
-//  * Lifted residues (key switching), from 8 work-groups per CU on: 64 items of
-//    4 to 24 limbs at N = 2^16 2070 -> 1995 us.
+//  * Lifted residues (key switching), from 11 work-groups per CU on, where the
+//    launch is counted as sized for its top level (a batch at uneven levels
+//    leaves up to half of it empty).  Batches of multiplications and rotations,
+//    4 -> 16: 2070 to 2392 work-groups at uneven levels 167.4 -> 171.7 us (45
+//    items at N = 2^13), 190.0 -> 193.1 (24 at 2^14), 198.0 -> 201.8 (13 at
+//    2^15), at even levels 337.5 -> 341; 2688 and 2760 the same; 3072 and more
+//    271.2 -> 269.9 (8 items of 4 to 24 limbs at 2^16), 374.2 -> 365.3 (26 at
+//    2^15), 2070 -> 1995 (64 at 2^16).
 //  * Row-major residues (stand-alone INTT): the stores have the same short runs,
 //    and two work-groups per CU are enough.  INTT of n limbs (both passes) at
 //    N = 2^16: 24 limbs 14.3 -> 14.8, 32 17.4 -> 17.1, 48 22.2 -> 21.7, 64 25.5 ->
 //    24.2, 96 30.8 -> 28.2, 128 36.6 -> 33.4; at 2^15 128 limbs 25.0 -> 25.4.
 template <int L1, class St>
-static bool inv_cols16(long groups) { return St::kTileThread ? groups >= 2048 : L1 == 8 && groups >= 512; }
+static bool inv_cols16(long groups) { return St::kTileThread ? groups >= 2816 : L1 == 8 && groups >= 512; }
 template <int L1, class MS, class Ld, class St>
 static void inv_cols(const Ctx& c, MS ms, int n, Ld ld, St st, hipStream_t s, int items_n = 1, bool c4 = false)
 {
