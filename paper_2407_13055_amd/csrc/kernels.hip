@@ -731,7 +731,7 @@ __global__ void __launch_bounds__(NTT_THREADS) k_bconv_ntt_cols4(NttTables T, BS
 // the inverse column pass one after the other, lifts each and adds it to its
 // targets' sums, and goes on as k_bconv_ntt_cols4.  The input rows' passes are
 // repeated by every group of targets; that is what the launch it saves must
-// outweigh (fuse_cols).  Launch limb in_off + s of M is input row s.
+// outweigh (fuse_list).  Launch limb in_off + s of M is input row s.
 // ---------------------------------------------------------------------------
 template <int LOG1, int TPW, bool RS>
 __global__ void __launch_bounds__(NTT_THREADS) k_inv_bconv_ntt_cols4(NttTables Tf, NttTables Ti, const LaunchMap* Mp,
@@ -2106,29 +2106,29 @@ static int launch_bconv_list(const Ctx& c, int tpw, const std::vector<BcRef>& bs
 // Conversions that run as one launch from the INTT row pass to the NTT column
 // pass (k_inv_bconv_ntt_cols4) instead of two.  It saves a launch (about 3 us
 // of a dependent sequence, as much host time) and costs the input rows' column
-// passes again for every group of targets and a chain of n_in passes in every
-// work-group.  Measured, HMult + rescale, two launches -> one: one-prime digits
-// 28.6 -> 23.5 us at N = 2^12 and 32.5 -> 29.4 at 2^16 (3 limbs), two-prime
-// digits 28.6 -> 26.3 and 49.6 -> 49.9 (8 limbs; 42.2 -> 40.6 at 6), four-prime
-// digits 28.5 -> 28.8 and 45.3 -> 50.2: the line lies at two primes per digit
-// and 5 2^18 repeated residues.  Rescalings convert 1 to 3 dropped primes to one window:
-// rational 20.1 -> 18.6 us with 3 at N = 2^16, single 30.5 -> 28.2 at 24 limbs
-// and 17.6 -> 15.5 at 8 limbs of N = 2^12.
+// passes again for every group of targets (a fused rescaling's row e among
+// them) and a chain of them in every work-group.  HMult + rescale, neither
+// conversion in one launch -> both that the rule takes: one-prime digits 29.6 ->
+// 23.1 us at N = 2^13 and 30.5 -> 27.8 at 2^16 (3 limbs), 53.1 -> 52.4 at 2^16 (8
+// limbs, ModDown alone); two-prime digits 30.1 -> 26.5 at 2^13 and 36.8 -> 34.8 at
+// 2^15 (8 limbs), 39.0 -> 38.1 at 2^16 (6 limbs; the largest repeat, 18 2^16).
+// Past the line 10 limbs in two-prime digits at 2^16 (ModDown, 30 2^16) 50.0 ->
+// 51.0, 16 limbs at 2^15 (24 2^16) 52.5 -> 53.0; with four-prime digits 12 limbs
+// 45.3 -> 50.2.  Rescalings convert 1 to 3 dropped primes to one window:
+// rational 20.1 -> 18.6 us with 3 at N = 2^16, single 30.5 -> 26.1 at 24 limbs,
+// 44.6 -> 38.8 at 48 and 20.6 -> 13.5 at 4.
 constexpr int FUSE_MAX_IN = 2, RR_FUSE_MAX_IN = 3;
 constexpr size_t FUSE_MAX_REPEAT = (size_t)5 << 18;
 // targets per work-group of the rescalings' conversions: 1 repeats the input
 // rows' passes twice as often, 4 leaves 5 work-groups per CU (rational
 // rescaling 18.6 us with 2, 20.2 with 4)
 constexpr int RS_TPW = 2;
-static bool fuse_cols(const Ctx& c, int n_in, int groups)
-{
-    return n_in <= FUSE_MAX_IN && (((size_t)n_in * groups) << c.log_n) <= FUSE_MAX_REPEAT;
-}
-static bool fuse_list(const Ctx& c, const std::vector<BcRef>& bs)
+// extra: rows that pass through the inverse columns besides the inputs
+static bool fuse_list(const Ctx& c, const std::vector<BcRef>& bs, int extra)
 {
     int n_in = 0, groups = 0;
     for (const BcRef& B : bs) n_in = std::max(n_in, B.n_in_max), groups += B.groups;
-    return fuse_cols(c, n_in, groups);
+    return n_in <= FUSE_MAX_IN && (((size_t)(n_in + extra) * groups) << c.log_n) <= FUSE_MAX_REPEAT;
 }
 
 template <bool RS>
@@ -2384,7 +2384,7 @@ static int modup_phase(const KsRun& R, Own own, const KsIn& in, size_t s0, size_
     BcRescale X{};
     X.nofix = c.up_nofix;
     const int4* up_c = own == Own::Tensor ? c.up_c_r : c.up_c;
-    if (!R.D && c4 && fuse_list(c, R.P->up_bc)) {
+    if (!R.D && c4 && fuse_list(c, R.P->up_bc, 0)) {
         KTimer t(c, "modup_cols", s);
         return launch_inv_bconv_list<false>(c, c.tpw_up, R.P->up_cols, R.P->up_bc, R.w0, up_c, c.up_mat, R.w2,
                                             X, s);
@@ -2418,7 +2418,7 @@ static int moddown_phase(const KsRun& R, int level, bool rescale, uint32_t* out0
     const int4* dn_c = rr ? c.rr_c : c.dn_c;
     const int32_t* dn_mat = rr ? c.rr_mat : c.dn_mat;
     const BcRescale X{c.rs_mlast, c.rs_pr, c.n_p, level};
-    if (!R.D && c4 && fuse_list(c, R.P->dn_bc)) {
+    if (!R.D && c4 && fuse_list(c, R.P->dn_bc, rescale && !rr ? 1 : 0)) {
         KTimer t(c, "moddown_cols", s);
         if (int e = rescale && !rr
                         ? launch_inv_bconv_list<true>(c, c.tpw_dn, R.P->dn_cols, R.P->dn_bc, R.w0, dn_c, dn_mat, R.w2, X, s)
