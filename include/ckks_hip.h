@@ -140,7 +140,7 @@ typedef struct {
     int32_t bconv_tpw_up;    /* ModUp BConv targets per work-group: 1, 2 or 4 (default 2) */
     int32_t bconv_tpw_down;  /* ModDown BConv targets per work-group: 1, 2 or 4 (default 2) */
     int32_t xcd_pair;        /* 1: the column tiles of one 128-byte line run on one XCD (default) */
-    int32_t rows_per_thread; /* residues per thread of the stand-alone NTT row passes: 16 (default) or 4
+    int32_t rows_per_thread; /* residues per thread of the NTT and INTT row passes: 16 (default) or 4
                                 (one wave per 256-point row, four radix-4 rounds) */
     int32_t col_threads;     /* threads per column-pass tile: 256 (16 columns, default), 512 (32 columns:
                                 whole 128-byte rows; used where a column is >= 32 points, N >= 2^13) or
@@ -148,16 +148,18 @@ typedef struct {
     int32_t rows_per_thread_single; /* the same knob for launches of one operation (grid.z = 1): a single
                                        HMult has too few waves to hide memory latency with 16 residues per
                                        thread, a batched call has enough; default 4;
-                                       0 = rows_per_thread */
+                                       0 = rows_per_thread.  (At N = 2^12 single operations with all three
+                                       *_single widths 4 run whole limbs per work-group.) */
     int32_t keymult_rows;    /* residues per thread of KeyMult (with its NTT and INTT row passes): 16 or
                                 4 (default; one wave per row, digit products summed in 64 bits) */
     int32_t keymult_rows_single; /* the same for launches of one operation (default 4); 0 = keymult_rows */
     int32_t cols_per_thread;  /* residues per thread of key switching's column passes (INTT columns, BConv +
                                  NTT columns): 16 (col_threads tiles) or 4 (default; 256-thread tiles of
                                  1024 / 2^(log_n - 8) columns, radix-4 rounds); the INTT columns of large
-                                 batched launches take 16 either way */
-    int32_t cols_per_thread_single; /* the same for launches of one operation (default 4);
-                                       0 = cols_per_thread */
+                                 batched launches take 16 either way, rescalings' conversions 4 */
+    int32_t cols_per_thread_single; /* the same for launches of one operation, the stand-alone transforms'
+                                       column passes among them, of which large ones at N >= 2^15 take 16
+                                       either way (default 4); 0 = cols_per_thread */
 } ckks_tuning;
 
 /* Set the knobs and rebuild the context's launch plans.  Synchronizes the
@@ -183,7 +185,8 @@ int ckks_intt(const ckks_ctx* ctx, uint32_t* data, const int32_t* prime_ids, int
  *   out_t = sum_s lift_s(in_s * [S_s^-1]_s) * S_s  (mod t),  S_s = prod(S)/s,
  * lift_s(v) = v if 2v < s else v - s.  in [n_in][N], out [n_out][N];
  * in_ids (distinct) / out_ids are host arrays of prime ids; n_in, n_out <= 64.
- * Workspace: ckks_workspace_size(CKKS_OP_BCONV, 0, n_in, n_out). */
+ * Workspace: ckks_workspace_size(CKKS_OP_BCONV, 0, n_in, n_out); the call
+ * checks it and does not touch it (the constants travel with the launch). */
 int ckks_bconv(const ckks_ctx* ctx, const uint32_t* in, const int32_t* in_ids, int n_in, uint32_t* out,
                const int32_t* out_ids, int n_out, void* ws, size_t ws_bytes, void* stream);
 

@@ -241,11 +241,6 @@ struct StPlain {
     {
         base[((size_t)M.out_off[l] << log_n) + j] = v;
     }
-    template <class LM>
-    __device__ void store16(const LM& M, int l, int j, const uint32_t (&x)[16], PrimeC) const
-    {
-        store16_u32(base + ((size_t)M.out_off[l] << log_n) + j, x);
-    }
     template <int E, class LM>
     __device__ void storev(const LM& M, int l, int j, const uint32_t (&x)[E], PrimeC) const
     {
@@ -1335,9 +1330,9 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
 //   k_small_keymult   a row of one polynomial over all digits; P rows (and
 //                     dropped ones) go on to ModDown's lifted INTT
 //   k_small_moddown   an output row's conversion, NTT and combine
-// Nothing is large here: a dependent launch costs about 3.5 us and a
-// transform's chain about as much, so the number of launches (seven, or five
-// with narrow digits) was the time.  One launch for conversions and KeyMult
+// Nothing is large here: a dependent launch and its kernel's shortest chain take
+// about 3.5 us together and a whole transform's chain little more, so the number
+// of launches (seven, or five with narrow digits) was the time.  One launch for conversions and KeyMult
 // (a row's digits and both polynomials in one work-group) took 15.6 us against
 // the two launches' 10: a row's chain is issued by one CU.  HMult + rescale,
 // seven launches -> four: 24 limbs in three digits 29.5 -> 25.4 us, 8 limbs in
@@ -2152,8 +2147,8 @@ static int launch_inv_bconv_list(const Ctx& c, int tpw, const MapRef& cols, cons
 
 // Single operations at N = 2^12 (the launch-bound ring) run whole limbs per
 // work-group: key switching in four launches, rescalings in two, transforms in
-// one.  A dependent launch costs about 3.5 us, more than the second pass of a
-// limb adds to a work-group's chain: NTT 7.5 -> 5.1, INTT 7.4 -> 5.1, rescaling
+// one.  A launch and its kernel's chain take about 3.5 us together, more than
+// the second pass of a limb adds to a work-group's chain: NTT 7.5 -> 5.1, INTT 7.4 -> 5.1, rescaling
 // 11.0 -> 9.8, rational rescaling 13.3 -> 10.7 us.
 // The settings other than one wave per row and 4-residue columns keep the
 // general passes.
@@ -2502,8 +2497,12 @@ static KmArgs km_args(const Ctx& c, const KsRun& R, const KsIn& in, const uint32
 // One operation at N = 2^12 takes the four-launch sequence.
 static bool small_switch(const Ctx& c, int level)
 {
-    // up to four one-prime digits: the general sequence's conversions fuse into
-    // five launches of smaller work-groups (3 limbs: 22.3 against 23.4 us)
+    // Up to four one-prime digits the general sequence's conversions fuse into
+    // five launches of smaller work-groups.  HMult + rescale, general against
+    // four launches, one-prime digits: 3 limbs 22.3 : 22.9 us, 4 23.3 : 23.6, 5
+    // 24.4 : 24.2, 8 26.9 : 25.9, 12 34.6 : 28.8, 24 65.2 : 43.0, 48 153 : 73;
+    // two-prime: 4 limbs 24.2 : 22.8, 8 25.4 : 23.9, 48 91 : 50; four-prime: 12
+    // limbs 25.9 : 23.5, 48 60.5 : 38.1; eight: 24 limbs 27.2 : 25.5, 56 51.9 : 33.1.
     if (c.n_p == 1 && c.digits(level) <= 4) return false;
     return small_ring(c);
 }

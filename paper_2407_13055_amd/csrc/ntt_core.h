@@ -50,9 +50,15 @@ __host__ __device__ constexpr int quad_row(int h) { return ((h >> 2) << (ROW_LOG
 // classes of primes, chosen per work-group (uniform branch):
 //   q < 2^30 ("wide"): forward values are signed 32-bit integers.  A stage
 //     that first centres its a (two multiply-adds) and one that does not
-//     alternate: from any 32-bit input, a centring stage leaves at most
-//     (3/2) q and the stage after it at most 2^31 again (a centred, the sum
-//     grows by |t| <= q/2 + |x| q / 2^33 per stage).  A butterfly is 3
+//     alternate.  A centred a is at most q/2 + |x| q e / 2^32, where e =
+//     |2^32/q - round(2^32/q)| <= 1/2 (the centring's quotient is that rounded
+//     reciprocal), and a product t at most q/2 + |x| q / 2^33.  From any 32-bit
+//     input a centring stage leaves at most (5/4 + e/2) q, the stage after it
+//     (7/4 + e/2 + (5/4 + e/2) q / 2^33) q, and that is below 0.963 2^31 for
+//     every q < 2^30, because e is near 0 where q is near 2^30; the largest is
+//     2.17 q at e = 1/2, q = 2^32 / 4.5 = 0.889 2^30.  (With e = 1/2 at 2^30 it
+//     would be 2.19 q, beyond 2^31: the class limit and the reciprocal belong
+//     together.)  A butterfly is 3
 //     instructions for the product, 2 for the sums and on average 1 for the
 //     centring.  Inverse values lie in [0, 2q): the difference is signed by
 //     itself and the product's multiply-add adds q: 3 + 1, and 3 for the sum
@@ -214,10 +220,12 @@ __host__ __device__ constexpr int row_tiles() { return (1 << LOG1) / ROWS_PER_WG
 // ---------------------------------------------------------------------------
 // Pass kernels.  Ld::at(item) / St::at(item) return copies whose pointers
 // are advanced to batch item `item` (identity for a single operation).
-// Ld::load(M, limb, j, pc) / Ld::load16(M, limb, j0, pc, x)
-// produce input residues (fused prologues); St::store(M, limb, j, v, pc) /
-// St::store16 consume outputs (fused epilogues); St::final_const(M, limb) is
-// the constant folded into the last inverse stage.  M.pid[limb] is the prime.
+// Ld::load(M, limb, j, pc), load16, loadv<E> (E residues from j0 on) and
+// load_rc (row, column) produce input residues (fused prologues);
+// St::store(M, limb, j, v, pc), store4 (a run of lifted residues) and
+// store_fwd<E, W> (E forward values, with the operands that prefetch<E>
+// requested) consume outputs (fused epilogues); St::final_const(M, limb) is the
+// constant folded into the last inverse stage.  M.pid[limb] is the prime.
 // ---------------------------------------------------------------------------
 // Launch maps reach the kernels as a pointer to a map precomputed in device
 // memory at context creation (every internal launch), or by value for the
