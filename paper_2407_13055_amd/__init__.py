@@ -16,7 +16,6 @@ import array
 import ctypes
 import functools
 import os
-import sys
 
 import numpy as np
 
@@ -28,6 +27,7 @@ OP_BCONV, OP_KEYSWITCH, OP_HMULT, OP_HROT, OP_RESCALE, OP_HROT_HOISTED, OP_HROT_
 OP_RESCALE_RATIONAL = 8
 
 _lib = None
+_torch_module = None
 
 
 class CkksError(RuntimeError):
@@ -158,10 +158,11 @@ def _ids(ids) -> ctypes.Array:
 
 def _torch():
     """The torch module (a call's fast path: no import statement to run)."""
-    t = sys.modules.get("torch")
-    if t is None:
-        import torch as t
-    return t
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _raw_stream(device: int) -> int:
@@ -314,7 +315,7 @@ class Context:
         least `numel` elements of `dtype` (int32 residues or uint8 bytes)."""
         torch = _torch()
         want = torch.int32 if dtype == "int32" else torch.uint8
-        if not isinstance(t, torch.Tensor):
+        if type(t) is not torch.Tensor and not isinstance(t, torch.Tensor):
             raise CkksError("%s: expected a torch tensor, got %s" % (name, type(t).__name__))
         if t.get_device() == self.device and t.is_cuda and t.dtype is want and t.is_contiguous() and t.numel() >= numel:
             return t.data_ptr()
