@@ -878,7 +878,7 @@ struct KmArgs {
     size_t in_step, in2_step, ws_step, key_step, up_step;
     int lo_level, n_keys, n_src;
     int n_rot;            // rotations of a hoisted launch (XcdRows)
-    int once;             // hoisted: key rows are loaded past the caches (KEYS_ONCE_BYTES)
+    bool once;            // hoisted: key rows are loaded past the caches (KEYS_ONCE_BYTES)
 };
 
 // End of a KeyMult row: Q rows store ks; P rows (and the dropped row q_{l-1}
@@ -1125,7 +1125,9 @@ struct KmSum {
     }
 };
 
-template <int LOG1, Own OWN, Extra EX>
+// ONCE: the key rows are loaded past the caches (hoisted launches; a branch in
+// the kernel instead costs 0.25 % of a call of 32 rotations at N = 2^16)
+template <int LOG1, Own OWN, Extra EX, bool ONCE = false>
 __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTables Ti, KmArgs A)
 {
     // row in q_b..q_{b+l-1}, p_0..: the P rows (the longest work: every digit
@@ -1179,14 +1181,9 @@ __global__ void __launch_bounds__(NTT_THREADS) k_keymult4(NttTables Tf, NttTable
     auto issue = [&](int j, Dig& d) {
         const uint32_t* kb = A.evk + (((size_t)(2 * (kd + j)) * key_rows + pid) * n + hrow) + l4;
         const uint32_t* ka = A.evk + (((size_t)(2 * (kd + j) + 1) * key_rows + pid) * n + hrow) + l4;
-        if constexpr (OWN == Own::Hoisted) {
-            if (A.once) {
-                load_once(kb, d.kb);
-                load_once(ka, d.ka);
-            } else {
-                loadv_u32<4>(kb, d.kb);
-                loadv_u32<4>(ka, d.ka);
-            }
+        if constexpr (ONCE) {
+            load_once(kb, d.kb);
+            load_once(ka, d.ka);
         } else {
             loadv_u32<4>(kb, d.kb);
             loadv_u32<4>(ka, d.ka);
@@ -2279,14 +2276,22 @@ static dim3 xcd_grid(int rows, int tiles, int n_rot)
 template <int L1, Own OWN, Extra EX>
 static void keymult(const Ctx& c, int max_level, int items_n, const KmArgs& A, hipStream_t s)
 {
-    if ((items_n == 1 ? c.km_ept1 : c.km_ept) == 4)
-        CKKS_LAUNCH((k_keymult4<L1, OWN, EX>),
-                    OWN == Own::Hoisted ? xcd_grid(max_level + c.n_p, row4_tiles<L1>(), items_n)
-                                        : dim3(row4_tiles<L1>(), max_level + c.n_p, items_n),
-                    dim3(NTT_THREADS), 0, s, tables(c, false), tables(c, true), A);
-    else
-        CKKS_LAUNCH((k_keymult<L1, OWN, EX>), dim3(row_tiles<L1>(), max_level + c.n_p, items_n), dim3(NTT_THREADS),
-                    0, s, tables(c, false), tables(c, true), A);
+    const int rows = max_level + c.n_p;
+    if ((items_n == 1 ? c.km_ept1 : c.km_ept) != 4) {
+        CKKS_LAUNCH((k_keymult<L1, OWN, EX>), dim3(row_tiles<L1>(), rows, items_n), dim3(NTT_THREADS), 0, s,
+                    tables(c, false), tables(c, true), A);
+        return;
+    }
+    if constexpr (OWN == Own::Hoisted) {
+        const dim3 grid = xcd_grid(rows, row4_tiles<L1>(), items_n);
+        if (A.once)
+            CKKS_LAUNCH((k_keymult4<L1, OWN, EX, true>), grid, dim3(NTT_THREADS), 0, s, tables(c, false), tables(c, true), A);
+        else
+            CKKS_LAUNCH((k_keymult4<L1, OWN, EX>), grid, dim3(NTT_THREADS), 0, s, tables(c, false), tables(c, true), A);
+    } else {
+        CKKS_LAUNCH((k_keymult4<L1, OWN, EX>), dim3(row4_tiles<L1>(), rows, items_n), dim3(NTT_THREADS), 0, s,
+                    tables(c, false), tables(c, true), A);
+    }
 }
 
 template <Own OWN, Extra EX>
