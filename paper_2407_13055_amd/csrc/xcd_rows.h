@@ -16,8 +16,8 @@ namespace ckks {
 // 8 XCDs in turn), one rotation after the other, and its L2 serves all but the
 // first.  Rows past the last multiple of 8 would leave XCDs without work: each
 // of them is shared by 8, 4 or 2 XCDs (every p-th tile of all its rotations),
-// so that every XCD has the same share at every number of rows; P rows, the
-// longer ones, come first and are whole where there are 8 rows and more.
+// so that every XCD has the same share at every number of rows.  P rows, the
+// longer ones, are the first rows.
 // 32 hoisted rotations at N = 2^16, by (tile, row, rotation) -> whole rows only
 // -> this order: 32 rows 1048 -> 953 -> 955 us, 25 rows 822 -> 797 -> 753,
 // 19 rows 539 -> 544 -> 516, 9 rows 221 -> 265 -> 220, 3 rows 101 -> 150 -> 102;
